@@ -3,11 +3,12 @@
 //   dB_jk = sum over stored a_ij of a_ij * dC_ik       ((A^T dC) on S(B))
 // Every (i, k) reached lies in S(C) because S(C) is the structural product.
 // Both are gathers (no floating-point atomics).  dA, and the products
-// a_ij dC_ik of dB, come from an entry-parallel pass over A; dB then adds
+// a_ij dC_ik of dB, come from a product-parallel pass over A; dB then adds
 // those products per b_jk over A's transposed pattern (rows of each column in
 // ascending order).  Without room for the products, dB is gathered per row
-// of B with binary searches in C.  Each sum runs in the order of the
-// definition (ascending k, ascending i), from +0.0.
+// of B with binary searches in C.  dB sums run in the order of the
+// definition (ascending i) from +0.0; a dA sum adds blocks of 64 products as
+// a tree across the lanes, block by block (a fixed order).
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -46,28 +47,89 @@ __global__ __launch_bounds__(256) void k_grad_b(const int64_t *tptr, const int32
 }
 
 // ---------------------------------------------------------------------------
-// Entry-parallel form.  One wavefront per chunk of BW_CH consecutive entries
-// of A (rows found by a binary search on A's row pointers, so rows of any
-// length are spread evenly).  For every entry e = (i, j) and every stored
-// b_jk, y = dC_ik is looked up -- in a dense LDS copy of the row's dC when C
-// has few columns, else by a binary search in c_i* -- and
-//   dA_e += y * b_jk                  (ascending k, as in the definition)
-//   W[P_e + q] = a_ij * y             (q = position of b_jk in b_j*)
+// Product-parallel form.  One wavefront per chunk of BW_CH consecutive
+// entries of A, 64 entries at a time, whose products it takes in expansion
+// order, one per lane: consecutive lanes read consecutive entries of b_j* and
+// write consecutive products of W.  For product q of entry e = (i, j),
+// y = dC_ik is looked up -- by its rank in an LDS bitmap of the row's columns
+// when C has few columns, else by a binary search in c_i* -- and
+//   dA_e = sum of y * b_jk        (a segmented scan across the lanes)
+//   W[P_e + q] = a_ij * y         (q = position of b_jk in b_j*)
 // where P_e is the product offset of entry e from stage 1.  W holds every
 // product a_ij dC_ik of the dB sums; k_grad_b_sum adds them per b_jk over
-// A's transposed pattern (ascending i).  Sums, products and their order are
-// those of the definition (and of k_grad_b).
-constexpr int BW_CH = 512;
-constexpr int BW_NT = 128;  // two wavefronts: 32 KB of dense rows per work-group
-constexpr int BW_U = 8;  // entries of b_j* whose loads are in flight together
-// with the dense dC row (16 KB of LDS per wavefront, so LDS, not registers,
-// caps the kernel at two wavefronts per SIMD) a whole block of 32 entries
-// of b_j* is loaded at once: fewer dependent round trips per entry
-constexpr int BW_UD = 32;
-constexpr int BW_SC = 8;  // passes of a dC row's scatter whose loads are in flight together
-constexpr int BW_MAP_BYTES = 16384;  // dense dC row per wavefront
+// A's transposed pattern (ascending i).
+//
+// The entry of a product comes from a bit mask of the entries' first
+// products (LDS, BW_WIN products at a time) and a count of the bits below the
+// lane, so the lanes stay full whatever the row lengths of B.
+//
+// What bounds it: latency and the B rows gathered past the L2 (one 128-byte
+// line or two per b_j* and array), not the VALU (37% busy).  One lane per
+// entry of A, as before, left ragged rows waiting on their longest entry and
+// touched 64 lines per load: 2374 us where B is narrow (A 300000^2 with 6M
+// entries x B 300000x4096, 32 per row, binary32; now 1187), 1389 us where it
+// is wide (A 50000^2 with 600k entries x B 50000^2, 12 per row, binary64; now
+// 163).  Few entries per chunk spread the long tail of a small product; with
+// the bitmap a row cut by a chunk is mapped twice, so chunks are longer there
+// (64 / 128 / 256 / 512 entries measured 1292 / 1257 / 1287 / 1404 us narrow,
+// 163 / 200 / 230 / 369 wide).  Overlapping the next group's loads of B with
+// this group's dC costs more in resident wavefronts than it hides (1371).
+constexpr int BW_WIN = 2048;  // products whose entry starts the bit mask covers
+template <bool DENSE> constexpr int bw_ch() { return DENSE ? 128 : 64; }
+// blocks of 64 products whose loads are in flight together (narrow: 3 / 4 / 6
+// blocks 1333 / 1257 / 1187 us; wide: 6 cost it two wavefronts per SIMD)
+template <bool DENSE> constexpr int bw_u() { return DENSE ? 6 : 4; }
+constexpr int BW_SC = 4;  // passes of a row of C whose column loads are in flight together
+// columns of the bitmap: 1 KB of it and 512 bytes of ranks per wavefront,
+// where a dense copy of a dC row of 4096 columns took 16 KB and left 9
+// wavefronts per CU (the same time, but only up to 2048 binary64 columns)
+constexpr int BW_MAP = 8192;
+constexpr int BW_MW = BW_MAP / 32 / WAVE;  // its words per lane
 
-template <typename T> constexpr int bw_map_cols() { return BW_MAP_BYTES / static_cast<int>(sizeof(T)); }
+// Last row i of [lo, hi) with arp[i] <= e (arp[lo] <= e): the row that holds
+// entry e, empty rows skipped.
+DEVI int32_t row_of(const int32_t *arp, int32_t lo, int32_t hi, int64_t e) {
+  while (hi - lo > 1) {
+    const int32_t mid = lo + ((hi - lo) >> 1);
+    if (arp[mid] <= e)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+// Sums of the lanes from the last segment head at or below each lane (dist
+// lanes down; 64 or more: none in the wavefront) up to the lane itself.
+template <typename T> DEVI T segment_scan(T v, int dist) {
+  const int ln = lane();
+  T y = dpp_move<DPP_ROW_SHR + 1, 0xF>(v, T(0));
+  v = v + (dist >= 1 ? y : T(0));
+  y = dpp_move<DPP_ROW_SHR + 2, 0xF>(v, T(0));
+  v = v + (dist >= 2 ? y : T(0));
+  y = dpp_move<DPP_ROW_SHR + 4, 0xF>(v, T(0));
+  v = v + (dist >= 4 ? y : T(0));
+  y = dpp_move<DPP_ROW_SHR + 8, 0xF>(v, T(0));
+  v = v + (dist >= 8 ? y : T(0));
+  y = dpp_move<DPP_ROW_BCAST15, 0xA>(v, T(0));
+  v = v + (dist > (ln & 15) ? y : T(0));
+  y = dpp_move<DPP_ROW_BCAST31, 0xC>(v, T(0));
+  v = v + (dist > (ln & 31) ? y : T(0));
+  return v;
+}
+
+template <typename T, bool DENSE> struct GradTable {
+  alignas(16) uint32_t bits[DENSE ? BW_MAP / 32 : 4];  // columns of one row of C
+  uint16_t rank[DENSE ? BW_MAP / 32 : 1];              // columns before each word
+  uint32_t head[BW_WIN / 32];  // bit x: an entry starts at product x + 1 of the window
+  int32_t off[WAVE];           // entry with products: index in B of the window's product 0
+  uint32_t ent[WAVE];          // its lane (entry of the batch)
+  int32_t row[WAVE];           // dense: its row
+  T av[WAVE];
+  int32_t c0[DENSE ? 1 : WAVE], c1[DENSE ? 1 : WAVE];  // its row of C
+};
+
+constexpr int BW_NT = 256;  // four independent wavefronts
 
 template <typename T, bool DENSE>
 __global__ __launch_bounds__(BW_NT) void k_grad_entries(
@@ -75,89 +137,208 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
     const int64_t *P, const int32_t *brp, const int32_t *bcol, const T *bval, const int32_t *crp,
     const int32_t *ccol, const T *dc, T *dA, T *W) {
   constexpr int NWV = BW_NT / WAVE;
-  constexpr int MAPC = DENSE ? bw_map_cols<T>() : 1;
-  __shared__ T map[NWV * MAPC];
+  constexpr int BW_CH = bw_ch<DENSE>();
+  constexpr int BW_U = bw_u<DENSE>();
+  __shared__ GradTable<T, DENSE> tabs[NWV];
   const int w = threadIdx.x / WAVE;
   const int ln = lane();
+  GradTable<T, DENSE> &tb = tabs[w];
   const int64_t e0 = (static_cast<int64_t>(blockIdx.x) * NWV + w) * BW_CH;
   if (e0 >= nnz) return;  // uniform across the wavefront; no work-group barriers here
   const int64_t e1 = e0 + BW_CH < nnz ? e0 + BW_CH : nnz;
-  // dense dC row: every column a row looks up is one of its own C columns
-  // (C holds every structural product), written by that row's scatter, so
-  // the map is never cleared
-  T *mp = map + w * MAPC;
-  int64_t lo = 0, hi = m;  // the row holding e0: last i with arp[i] <= e0
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (arp[mid] <= e0)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  int64_t i = lo;
-  int64_t e = e0;
-  while (e < e1) {
-    while (arp[i + 1] <= e) ++i;  // skip empty rows
-    const int64_t re = arp[i + 1] < e1 ? static_cast<int64_t>(arp[i + 1]) : e1;
-    const int32_t c0 = crp[i], c1 = crp[i + 1];
-    if (DENSE) {
-      // the row's dC entries, BW_SC passes of the wavefront loaded together
-      // (clamped to the row) before they are written to the map
-      for (int32_t xb = c0; xb < c1; xb += BW_SC * WAVE) {
-        int32_t cc[BW_SC];
-        T vv[BW_SC];
-#pragma unroll
-        for (int u = 0; u < BW_SC; ++u) {
-          const int32_t x = xb + u * WAVE + ln;
-          const int32_t xc = x < c1 ? x : c1 - 1;
-          cc[u] = ccol[xc];
-          vv[u] = dc[xc];
-        }
-#pragma unroll
-        for (int u = 0; u < BW_SC; ++u)
-          if (xb + u * WAVE + ln < c1) mp[cc[u]] = vv[u];
+  int32_t row_lo = row_of(arp, 0, static_cast<int32_t>(m), e0);
+  const int32_t row_hi = row_of(arp, row_lo, static_cast<int32_t>(m), e1 - 1) + 1;
+  int32_t mapped = -1;  // row in the bitmap
+  int32_t mapped_c0 = 0;  // its first entry of C
+  const uint64_t le_mask = ~0ull >> (WAVE - 1 - ln);
+  for (int64_t eb = e0; eb < e1; eb += WAVE) {
+    const int nb = static_cast<int>(e1 - eb < WAVE ? e1 - eb : WAVE);
+    const bool in = ln < nb;
+    const int64_t e = in ? eb + ln : e1 - 1;
+    const int32_t j = acol[e];
+    const T av = aval[e];
+    const int64_t Pb = P[eb];
+    const int64_t pre = P[e] - Pb;
+    const int64_t len = P[e + 1] - Pb - pre;
+    const int64_t tot = P[eb + nb] - Pb;
+    const int32_t row = row_of(arp, row_lo, row_hi, e);
+    row_lo = __builtin_amdgcn_readlane(row, nb - 1);
+    const int32_t q0 = brp[j];
+    const int32_t c0 = crp[row], c1 = crp[row + 1];
+    const bool some = in && len > 0;
+    const int c = __popcll(__ballot(some) & (le_mask >> 1));  // entries with products below
+    wave_sync();  // the previous batch's table is dead
+    if (some) {
+      tb.ent[c] = ln;
+      tb.row[c] = row;
+      tb.av[c] = av;
+      if (!DENSE) {
+        tb.c0[c] = c0;
+        tb.c1[c] = c1;
       }
-      wave_sync();
     }
-    for (int64_t ee = e + ln; ee < re; ee += WAVE) {
-      const int32_t j = acol[ee];
-      const T av = aval[ee];
-      const int32_t q0 = brp[j], q1 = brp[j + 1];
-      T *wp = W ? W + (P[ee] - q0) : nullptr;
-      T s = T(0);
-      int32_t from = c0;
-      // blocks of UB entries of b_j*: their loads are issued together
-      // (clamped to the row), then the block is added in order
-      constexpr int UB = DENSE ? BW_UD : BW_U;
-      for (int32_t qb = q0; qb < q1; qb += UB) {
-        int32_t kk[UB];
-        T bv[UB];
+    if (dA && in && len == 0) dA[e] = T(0);
+    T carry = T(0);  // running sum of the entry left open by the previous block
+    for (int64_t xw = 0; xw < tot; xw += BW_WIN) {
+      const int wl = static_cast<int>(tot - xw < BW_WIN ? tot - xw : BW_WIN);
+      const int64_t d = pre - xw;  // this entry's first product in the window
+      tb.head[ln] = 0u;
+      wave_sync();
+      if (some) {
+        tb.off[c] = static_cast<int32_t>(q0 - d);  // used when the entry reaches the window
+        if (d >= 1 && d <= BW_WIN)
+          atomicOr(&tb.head[(d - 1) >> 5], 1u << ((d - 1) & 31));
+      }
+      // entries that start at or before the window's first product, less
+      // one: the entry of that product; whether it is the entry's first
+      int base = __popcll(__ballot(some && d <= 0)) - 1;
+      uint64_t starts = __any(some && d == 0) ? 1ull : 0ull;
+      wave_sync();
+      // groups of BW_U blocks whose loads are in flight together
+      struct Group {
+        int ce[BW_U];
+        int32_t kk[BW_U];
+        T bv[BW_U];
+        uint64_t hm[BW_U];
+      };
+      auto load_group = [&](int x0, Group &g) {
 #pragma unroll
-        for (int u = 0; u < UB; ++u) {
-          const int32_t q = qb + u < q1 ? qb + u : q1 - 1;
-          kk[u] = bcol[q];
-          bv[u] = bval[q];
+        for (int u = 0; u < BW_U; ++u) {
+          const int xb = x0 + u * WAVE;
+          const int wd = xb < BW_WIN ? xb / 32 : 0;
+          const uint32_t lo = __builtin_amdgcn_readfirstlane(tb.head[wd]);
+          const uint32_t hi = __builtin_amdgcn_readfirstlane(tb.head[wd + 1]);
+          const bool ok = xb + ln < wl;
+          g.hm[u] = (static_cast<uint64_t>(hi) << 32) | lo;
+          g.ce[u] = ok ? base + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                                    hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)))
+                       : 0;
+          base += __popcll(g.hm[u]);
+          // clamped, not branched around: the loads of a group stay in
+          // flight together (B has entries whenever A's have products)
+          const int32_t bx = ok ? tb.off[g.ce[u]] + xb + ln : 0;
+          g.kk[u] = bcol[bx];
+          g.bv[u] = bval[bx];
         }
+      };
+      for (int x0 = 0; x0 < wl; x0 += BW_U * WAVE) {
+        Group cur;
+        load_group(x0, cur);
+        int32_t at[BW_U];  // where C holds the products' columns
+        if (DENSE) {
 #pragma unroll
-        for (int u = 0; u < UB; ++u) {
-          if (qb + u < q1) {
-            T y;
-            if (DENSE) {
-              y = mp[kk[u]];
-            } else {
-              const int32_t pc = find_col(ccol, from, c1, kk[u]);
-              y = dc[pc];
-              from = pc + 1;  // columns of b_j* ascend
+          for (int u = 0; u < BW_U; ++u) {
+            at[u] = 0;
+            if (x0 + u * WAVE >= wl) continue;
+            const bool ok = x0 + u * WAVE + ln < wl;
+            const int32_t r = tb.row[cur.ce[u]];
+            uint64_t todo = __ballot(ok);
+            while (todo) {  // the rows among the block's products, in order
+              const int32_t rc = __builtin_amdgcn_readlane(r, __builtin_ctzll(todo));
+              if (rc != mapped) {
+                uint4 *bw = reinterpret_cast<uint4 *>(tb.bits);
+                static_assert(BW_MW == 4, "one 16-byte word group per lane");
+                wave_sync();  // the previous row's lookups are done
+                bw[ln] = make_uint4(0u, 0u, 0u, 0u);
+                wave_sync();
+                const int hl = __builtin_ctzll(__ballot(some && row == rc));
+                const int32_t m0 = __builtin_amdgcn_readlane(c0, hl);
+                const int32_t m1 = __builtin_amdgcn_readlane(c1, hl);
+                for (int32_t xs = m0; xs < m1; xs += BW_SC * WAVE) {
+                  int32_t cc[BW_SC];
+#pragma unroll
+                  for (int p = 0; p < BW_SC; ++p) {
+                    const int32_t x = xs + p * WAVE + ln;
+                    cc[p] = ccol[x < m1 ? x : m1 - 1];
+                  }
+#pragma unroll
+                  for (int p = 0; p < BW_SC; ++p)
+                    if (xs + p * WAVE + ln < m1) atomicOr(&tb.bits[cc[p] >> 5], 1u << (cc[p] & 31));
+                }
+                mapped = rc;
+                mapped_c0 = m0;
+                wave_sync();
+                const uint4 b4 = bw[ln];
+                const int n0 = __popc(b4.x), n1 = n0 + __popc(b4.y), n2 = n1 + __popc(b4.z);
+                const int n3 = n2 + __popc(b4.w);
+                const int before = group_incl_sum<WAVE>(n3) - n3;
+                uint16_t *rk = tb.rank + BW_MW * ln;
+                rk[0] = static_cast<uint16_t>(before);
+                rk[1] = static_cast<uint16_t>(before + n0);
+                rk[2] = static_cast<uint16_t>(before + n1);
+                rk[3] = static_cast<uint16_t>(before + n2);
+                wave_sync();
+              }
+              const bool mine = ok && r == rc;
+              if (mine) {
+                const int wd = cur.kk[u] >> 5;
+                at[u] = mapped_c0 + tb.rank[wd] +
+                        __popc(tb.bits[wd] & ((1u << (cur.kk[u] & 31)) - 1u));
+              }
+              todo &= ~__ballot(mine);
             }
-            s = s + y * bv[u];
-            if (wp) wp[qb + u] = av * y;
+          }
+        } else {
+          // lower bounds of the BW_U columns in their rows of C, one step of
+          // every search at a time (their loads are in flight together)
+          int32_t lo[BW_U], hi[BW_U];
+          int32_t most = 0;
+#pragma unroll
+          for (int u = 0; u < BW_U; ++u) {
+            const bool ok = x0 + u * WAVE + ln < wl;
+            lo[u] = ok ? tb.c0[cur.ce[u]] : 0;
+            hi[u] = ok ? tb.c1[cur.ce[u]] : 0;
+            most = max(most, hi[u] - lo[u]);
+          }
+          while (__any(most > 0)) {
+            int32_t mc[BW_U];
+#pragma unroll
+            for (int u = 0; u < BW_U; ++u) {
+              const int32_t mid = lo[u] + ((hi[u] - lo[u]) >> 1);
+              mc[u] = lo[u] < hi[u] ? ccol[mid] : 0;
+            }
+            most = 0;
+#pragma unroll
+            for (int u = 0; u < BW_U; ++u) {
+              if (lo[u] < hi[u]) {
+                const int32_t mid = lo[u] + ((hi[u] - lo[u]) >> 1);
+                if (mc[u] < cur.kk[u])
+                  lo[u] = mid + 1;
+                else
+                  hi[u] = mid;
+              }
+              most = max(most, hi[u] - lo[u]);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < BW_U; ++u) at[u] = x0 + u * WAVE + ln < wl ? lo[u] : 0;
+        }
+        T y[BW_U];
+#pragma unroll
+        for (int u = 0; u < BW_U; ++u) y[u] = dc[at[u]];  // (C has entries when A's have products)
+#pragma unroll
+        for (int u = 0; u < BW_U; ++u) {
+          const int xb = x0 + u * WAVE;
+          if (xb >= wl) continue;
+          const bool ok = xb + ln < wl;
+          if (W && ok) W[Pb + xw + xb + ln] = tb.av[cur.ce[u]] * y[u];
+          if (dA) {
+            const uint64_t heads = (cur.hm[u] << 1) | starts;
+            starts = cur.hm[u] >> 63;
+            const uint64_t mine = heads & le_mask;
+            const int dist = mine ? ln - (63 - __builtin_clzll(mine)) : WAVE;
+            T v = segment_scan<T>(ok ? y[u] * cur.bv[u] : T(0), dist);
+            if (!mine) v = v + carry;
+            const bool tail = ((cur.hm[u] >> ln) & 1ull) || xw + xb + ln == tot - 1;
+            if (ok && tail) dA[eb + tb.ent[cur.ce[u]]] = v;
+            const uint64_t open = ~cur.hm[u] >> 63;
+            const T last = __shfl(v, WAVE - 1, WAVE);
+            carry = open ? last : T(0);
           }
         }
       }
-      if (dA) dA[ee] = s;
+      wave_sync();  // the window's table is rewritten
     }
-    if (DENSE) wave_sync();  // this row's lookups precede the next row's scatter
-    e = re;
   }
 }
 
@@ -165,6 +346,7 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
 // BW_SUB lanes per row of B (each lane sums its own entries, so rows share
 // a wavefront without any ordering between them).
 constexpr int BW_SUB = 32;
+constexpr int BW_SU = 8;  // entries of A's column whose loads are in flight together
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_grad_b_sum(const int64_t *tptr, const int32_t *tpos,
@@ -176,17 +358,17 @@ __global__ __launch_bounds__(256) void k_grad_b_sum(const int64_t *tptr, const i
   const int32_t q0 = brp[j], q1 = brp[j + 1];
   for (int32_t q = q0 + (lane() & (BW_SUB - 1)); q < q1; q += BW_SUB) {
     T s = T(0);
-    // blocks of BW_U entries of A's column j: offsets, then products, each
+    // blocks of BW_SU entries of A's column j: offsets, then products, each
     // loaded together (clamped to the column), then added in order
-    for (int64_t db = t0; db < t1; db += BW_U) {
-      int64_t off[BW_U];
+    for (int64_t db = t0; db < t1; db += BW_SU) {
+      int64_t off[BW_SU];
 #pragma unroll
-      for (int u = 0; u < BW_U; ++u) off[u] = P[tpos[db + u < t1 ? db + u : t1 - 1]];
-      T v[BW_U];
+      for (int u = 0; u < BW_SU; ++u) off[u] = P[tpos[db + u < t1 ? db + u : t1 - 1]];
+      T v[BW_SU];
 #pragma unroll
-      for (int u = 0; u < BW_U; ++u) v[u] = W[off[u] + (q - q0)];
+      for (int u = 0; u < BW_SU; ++u) v[u] = W[off[u] + (q - q0)];
 #pragma unroll
-      for (int u = 0; u < BW_U; ++u)
+      for (int u = 0; u < BW_SU; ++u)
         if (db + u < t1) s = s + v[u];
     }
     dB[q] = s;
@@ -199,14 +381,16 @@ void launch_grad_entries(const int32_t *arp, const int32_t *acol, const T *aval,
                          const T *bval, int64_t n, const int32_t *crp, const int32_t *ccol,
                          const T *dc, T *dA, T *W, hipStream_t s) {
   if (nnz <= 0) return;
-  const int64_t waves = (nnz + BW_CH - 1) / BW_CH;
-  const int64_t grid = (waves + BW_NT / WAVE - 1) / (BW_NT / WAVE);
-  if (n <= bw_map_cols<T>())
-    hipLaunchKernelGGL((k_grad_entries<T, true>), dim3(grid), dim3(BW_NT), 0, s, arp, acol, aval,
-                       m, nnz, P, brp, bcol, bval, crp, ccol, dc, dA, W);
-  else
-    hipLaunchKernelGGL((k_grad_entries<T, false>), dim3(grid), dim3(BW_NT), 0, s, arp, acol,
-                       aval, m, nnz, P, brp, bcol, bval, crp, ccol, dc, dA, W);
+  constexpr int NWV = BW_NT / WAVE;
+  if (n <= BW_MAP) {
+    constexpr int64_t PER = int64_t(NWV) * bw_ch<true>();
+    hipLaunchKernelGGL((k_grad_entries<T, true>), dim3((nnz + PER - 1) / PER), dim3(BW_NT), 0, s,
+                       arp, acol, aval, m, nnz, P, brp, bcol, bval, crp, ccol, dc, dA, W);
+  } else {
+    constexpr int64_t PER = int64_t(NWV) * bw_ch<false>();
+    hipLaunchKernelGGL((k_grad_entries<T, false>), dim3((nnz + PER - 1) / PER), dim3(BW_NT), 0, s,
+                       arp, acol, aval, m, nnz, P, brp, bcol, bval, crp, ccol, dc, dA, W);
+  }
 }
 
 template <typename T>

@@ -1,0 +1,57 @@
+"""Kernels at the sizes where they can go wrong: edges of tiles, windows and
+chunks, remainders, empty rows.  Tolerances are error bounds of the sums."""
+import numpy as np
+import pytest
+
+import oracle
+import synthetic as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _ragged(rng, rows, lengths, cols, dtype):
+    """Rows of the given lengths (in that order), distinct uniform columns."""
+    rp = np.zeros(rows + 1, np.int32)
+    rp[1:] = np.cumsum(lengths)
+    ci = np.concatenate([np.sort(rng.choice(cols, n, replace=False)) for n in lengths]
+                        + [np.zeros(0, np.int64)])
+    return S.Csr(rows, cols, rp, ci.astype(np.int32), rng.standard_normal(ci.size).astype(dtype))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("n", [40, 8192, 8193])
+def test_backward_ragged_rows(dtype, n):
+    """Rows of B around blocks of 64 products and windows of 2048 of them,
+    rows of A around batches of 64 and chunks of 128 entries, B up to the
+    widest bitmap and one column beyond."""
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, Plan
+    rng = np.random.default_rng(5)
+    lens = [0, 0, 1, 2, 31, 63, 64, 65, 127, 128, 129, 2047, 2048, 2049, 5000]
+    lens = [min(x, n) for x in lens] * 10
+    rng.shuffle(lens)
+    k = len(lens)
+    B = _ragged(rng, k, lens, n, dtype)
+    A = _ragged(rng, 15, [0, 1, 63, 64, 65, 0, 127, 128, 129, 130, 0, 0, 3, 2, 0], k, dtype)
+    print("case: n %d %s products of %d entries" % (n, np.dtype(dtype), A.nnz), flush=True)
+    dA, dB = CsrMatrix.from_host(A), CsrMatrix.from_host(B)
+    plan = Plan(dA, dB)
+    C = plan.compute()
+    dc = rng.standard_normal(C.nnz).astype(dtype)
+    gA, gB = plan.backward(C, torch.from_numpy(dc).cuda())
+    torch.cuda.synchronize()
+    _, _, rp, ci, _ = C.to_host()
+
+    def grads(f):
+        x, y = A.astype(np.float64), B.astype(np.float64)
+        x.val, y.val = f(x.val), f(y.val)
+        return oracle.grad(x.as_tuple(), y.as_tuple(), rp.astype(np.int64), ci,
+                           f(dc.astype(np.float64)))
+
+    refs, mags = grads(lambda v: v), grads(np.abs)
+    # a sum of t rounded products is off by at most (t + 1) eps times the
+    # sum of their magnitudes, in whatever order it is added
+    eps = np.finfo(dtype).eps
+    terms = (np.array(lens)[A.col_idx], np.bincount(A.col_idx, minlength=k).repeat(lens))
+    for got, ref, mag, t in zip((gA, gB), refs, mags, terms):
+        assert np.all(np.abs(got.cpu().numpy() - ref) <= (t + 2) * eps * mag)
