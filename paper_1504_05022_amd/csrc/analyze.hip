@@ -14,12 +14,37 @@ constexpr int SCAN_TILE = SCAN_NT * SCAN_IPT;
 
 int64_t scan_part_len(int64_t n) { return (n + SCAN_TILE - 1) / SCAN_TILE + 1; }
 
+// brp[j] and brp[j + 1] in one load (4-byte alignment is enough).
+struct __attribute__((packed, aligned(4))) RowBounds {
+  int32_t begin, end;
+};
+// Length of b_{acol[e]*}.  Phase 1 of the scan gathers the row bounds, keeps
+// where the row starts (bst) and leaves the length, 32 bits, inside the
+// tile's own part of the output, where phase 3 (TileLenFn) reads it before
+// it writes: gathering the bounds twice was L2-request bound (3.2M entries:
+// 20 + 21 us; with the kept lengths 22 + 10).
+DEVI int64_t scan_tile_base(int64_t e) { return e / SCAN_TILE * SCAN_TILE; }
 struct RowLenFn {
   const int32_t *acol;
   const int32_t *brp;
+  int32_t *bst;
+  int64_t *out;
+  DEVI void keep(int64_t e, const RowBounds &r) const {
+    const int64_t base = scan_tile_base(e);
+    bst[e] = r.begin;
+    reinterpret_cast<int32_t *>(out + base)[e - base] = r.end - r.begin;
+  }
   DEVI int64_t operator()(int64_t e) const {
-    const int32_t j = acol[e];
-    return static_cast<int64_t>(brp[j + 1]) - brp[j];
+    const RowBounds r = *reinterpret_cast<const RowBounds *>(brp + acol[e]);
+    keep(e, r);
+    return static_cast<int64_t>(r.end) - r.begin;
+  }
+};
+struct TileLenFn {
+  const int64_t *out;
+  DEVI int64_t operator()(int64_t e) const {
+    const int64_t base = scan_tile_base(e);
+    return reinterpret_cast<const int32_t *>(out + base)[e - base];
   }
 };
 struct I64Fn {
@@ -35,17 +60,58 @@ struct PieceFn {
   DEVI int64_t operator()(int64_t e) const { return p[e].cnt; }
 };
 
+// Elements base + j * SCAN_NT + t of a tile.  A whole tile's loads carry no
+// bounds checks, so that they are in flight together (a checked load is
+// waited for before the next is issued: 29 against 12 us for the two
+// dependent loads of 3.2M row lengths); the last tile checks.
+template <typename F>
+DEVI void scan_tile_load(const F &f, int64_t n, int64_t base, int64_t (&v)[SCAN_IPT]) {
+  if (base + SCAN_TILE <= n) {
+#pragma unroll
+    for (int j = 0; j < SCAN_IPT; ++j) v[j] = f(base + j * SCAN_NT + threadIdx.x);
+  } else {
+#pragma unroll
+    for (int j = 0; j < SCAN_IPT; ++j) {
+      const int64_t e = base + j * SCAN_NT + threadIdx.x;
+      v[j] = e < n ? f(e) : 0;
+    }
+  }
+}
+
+// Row lengths of a whole tile: all columns, then all row bounds, then the
+// stores (which the compiler may not move loads across).
+DEVI void scan_tile_load(const RowLenFn &f, int64_t n, int64_t base, int64_t (&v)[SCAN_IPT]) {
+  if (base + SCAN_TILE <= n) {
+    int32_t c[SCAN_IPT];
+    RowBounds r[SCAN_IPT];
+#pragma unroll
+    for (int j = 0; j < SCAN_IPT; ++j) c[j] = f.acol[base + j * SCAN_NT + threadIdx.x];
+#pragma unroll
+    for (int j = 0; j < SCAN_IPT; ++j) r[j] = *reinterpret_cast<const RowBounds *>(f.brp + c[j]);
+#pragma unroll
+    for (int j = 0; j < SCAN_IPT; ++j) {
+      f.keep(base + j * SCAN_NT + threadIdx.x, r[j]);
+      v[j] = static_cast<int64_t>(r[j].end) - r[j].begin;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < SCAN_IPT; ++j) {
+      const int64_t e = base + j * SCAN_NT + threadIdx.x;
+      v[j] = e < n ? f(e) : 0;
+    }
+  }
+}
+
 // Phase 1: sum of every tile.
 template <typename F>
 __global__ __launch_bounds__(SCAN_NT) void k_scan_reduce(F f, int64_t n, int64_t *part) {
   __shared__ int64_t sm[SCAN_NT / WAVE + 1];
   const int64_t base = static_cast<int64_t>(blockIdx.x) * SCAN_TILE;
+  int64_t v[SCAN_IPT];
+  scan_tile_load(f, n, base, v);
   int64_t s = 0;
 #pragma unroll
-  for (int j = 0; j < SCAN_IPT; ++j) {
-    const int64_t e = base + j * SCAN_NT + threadIdx.x;
-    if (e < n) s += f(e);
-  }
+  for (int j = 0; j < SCAN_IPT; ++j) s += v[j];
   int64_t tot;
   block_excl_sum<SCAN_NT>(s, sm, tot);
   if (threadIdx.x == 0) part[blockIdx.x] = tot;
@@ -92,14 +158,11 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan_down(F f, int64_t n, const int
   } else {
     offset = part[blockIdx.x];
   }
-#pragma unroll
-  for (int j = 0; j < SCAN_IPT; ++j) {
-    const int i = j * SCAN_NT + t;
-    const int64_t e = base + i;
-    tile[scan_lds_ix(i)] = e < n ? f(e) : 0;
-  }
-  __syncthreads();
   int64_t v[SCAN_IPT];
+  scan_tile_load(f, n, base, v);
+#pragma unroll
+  for (int j = 0; j < SCAN_IPT; ++j) tile[scan_lds_ix(j * SCAN_NT + t)] = v[j];
+  __syncthreads();
   int64_t s = 0;
 #pragma unroll
   for (int j = 0; j < SCAN_IPT; ++j) {
@@ -130,40 +193,40 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan_down(F f, int64_t n, const int
 // tiles up to which a work-group of phase 3 sums the earlier tile sums itself
 constexpr int64_t SCAN_SELF_MAX_TILES = 4096;
 
-template <typename F>
-static void scan_with(F f, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
+template <typename F, typename G>
+static void scan_with(F f, G down, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
   const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
   if (nb == 0) {
     // out[0] = 0
     hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(SCAN_NT), 0, s, part, int64_t(0));
-    hipLaunchKernelGGL((k_scan_down<F, false>), dim3(1), dim3(SCAN_NT), 0, s, f, n, part,
+    hipLaunchKernelGGL((k_scan_down<G, false>), dim3(1), dim3(SCAN_NT), 0, s, down, n, part,
                        int64_t(0), out);
     return;
   }
   hipLaunchKernelGGL((k_scan_reduce<F>), dim3(nb), dim3(SCAN_NT), 0, s, f, n, part);
   if (nb <= SCAN_SELF_MAX_TILES) {
-    hipLaunchKernelGGL((k_scan_down<F, true>), dim3(nb), dim3(SCAN_NT), 0, s, f, n, part, nb,
+    hipLaunchKernelGGL((k_scan_down<G, true>), dim3(nb), dim3(SCAN_NT), 0, s, down, n, part, nb,
                        out);
     return;
   }
   hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(SCAN_NT), 0, s, part, nb);
-  hipLaunchKernelGGL((k_scan_down<F, false>), dim3(nb), dim3(SCAN_NT), 0, s, f, n, part, nb,
+  hipLaunchKernelGGL((k_scan_down<G, false>), dim3(nb), dim3(SCAN_NT), 0, s, down, n, part, nb,
                      out);
 }
 
 void scan_row_lengths(const int32_t *acol, const int32_t *brp, int64_t n, int64_t *out,
-                      int64_t *part, hipStream_t s) {
-  scan_with(RowLenFn{acol, brp}, n, out, part, s);
+                      int32_t *bst, int64_t *part, hipStream_t s) {
+  scan_with(RowLenFn{acol, brp, bst, out}, TileLenFn{out}, n, out, part, s);
 }
 void scan_i64(const int64_t *v, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
-  scan_with(I64Fn{v}, n, out, part, s);
+  scan_with(I64Fn{v}, I64Fn{v}, n, out, part, s);
 }
 void scan_i32(const int32_t *v, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
-  scan_with(I32Fn{v}, n, out, part, s);
+  scan_with(I32Fn{v}, I32Fn{v}, n, out, part, s);
 }
 void scan_piece_counts(const Piece *pieces, int64_t n, int64_t *out, int64_t *part,
                        hipStream_t s) {
-  scan_with(PieceFn{pieces}, n, out, part, s);
+  scan_with(PieceFn{pieces}, PieceFn{pieces}, n, out, part, s);
 }
 
 // ------------------------------------------------------------ validation
@@ -309,27 +372,36 @@ void launch_row_stats(const RowStatsArgs &a, hipStream_t s) {
 // Stable scatter: rows keep ascending order inside each bin.
 __global__ __launch_bounds__(256) void k_bin_scatter(const int64_t *u, int64_t m, BinEdges be,
                                                      const int64_t *hist_scan, int64_t nwaves,
-                                                     int32_t *binlist) {
+                                                     const int32_t *arp, int32_t *binlist,
+                                                     RowRec *recs) {
   const int w = threadIdx.x / WAVE;
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const bool valid = i < m;
-  const int bin = valid ? bin_of(u[i], be) : 0;
+  const int64_t ui = valid ? u[i] : 0;
+  const int bin = valid ? bin_of(ui, be) : 0;
+  RowRec rec{static_cast<int32_t>(i), static_cast<int32_t>(ui < INT32_MAX ? ui : INT32_MAX), 0, 0};
+  if (valid) {
+    rec.e0 = arp[i];
+    rec.ne = arp[i + 1] - rec.e0;
+  }
   const int64_t gw = static_cast<int64_t>(blockIdx.x) * (256 / WAVE) + w;
   const uint64_t lt = (lane() == 0) ? 0ull : (~0ull >> (WAVE - lane()));
   for_each_bin_in_wave(valid, bin, [&](int b, uint64_t mask) {
     if (valid && bin == b) {
       const int64_t pos = hist_scan[b * nwaves + gw] + __popcll(mask & lt);
       binlist[pos] = static_cast<int32_t>(i);
+      recs[pos] = rec;
     }
   });
 }
 
 void launch_bin_scatter(const int64_t *u, int64_t m, BinEdges be, const int64_t *hist_scan,
-                        int64_t nwaves, int32_t *binlist, hipStream_t s) {
+                        int64_t nwaves, const int32_t *arp, int32_t *binlist, RowRec *recs,
+                        hipStream_t s) {
   const int64_t nb = (m + 255) / 256;
   if (nb == 0) return;
   hipLaunchKernelGGL(k_bin_scatter, dim3(nb), dim3(256), 0, s, u, m, be, hist_scan, nwaves,
-                     binlist);
+                     arp, binlist, recs);
 }
 
 __global__ __launch_bounds__(256) void k_summary(const int64_t *P, int64_t nnzA,

@@ -178,7 +178,8 @@ struct spgemm_plan_s {
   size_t ws_bytes = 0;
   int64_t *P = nullptr, *u = nullptr, *h = nullptr, *cto = nullptr, *rownnz = nullptr,
           *rowoff = nullptr, *hist_scan = nullptr, *part = nullptr;
-  int32_t *hist = nullptr, *binlist = nullptr;
+  int32_t *hist = nullptr, *binlist = nullptr, *bst = nullptr;
+  RowRec *recs = nullptr;
   int64_t *bpart = nullptr;
   int64_t nblocks = 0;
   LongParams lp{};
@@ -469,6 +470,8 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   const size_t opart = L.add<int64_t>(partn);
   const size_t ohist = L.add<int32_t>(nh);
   const size_t obl = L.add<int32_t>(m);
+  const size_t orec = L.add<RowRec>(m);
+  const size_t obst = L.add<int32_t>(p->nnzA);
   const size_t obp = L.add<int64_t>(p->nblocks * kBlockStats);
   const size_t osum = L.add<Summary>(1);
   const size_t ostat = L.add<ComputeStatus>(1);
@@ -489,6 +492,8 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   p->part = at<int64_t>(p->ws, opart);
   p->hist = at<int32_t>(p->ws, ohist);
   p->binlist = at<int32_t>(p->ws, obl);
+  p->recs = at<RowRec>(p->ws, orec);
+  p->bst = at<int32_t>(p->ws, obst);
   p->bpart = at<int64_t>(p->ws, obp);
   p->dsum = at<Summary>(p->ws, osum);
   p->dstat = at<ComputeStatus>(p->ws, ostat);
@@ -529,7 +534,7 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   stage_begin(p, SPGEMM_T_UPPER, s);
   // stage 1 (Algorithm 2): P = exclusive scan of nnz(b_j*) over A's entries,
   // so u_i = P[arp[i+1]] - P[arp[i]].
-  scan_row_lengths(A->col_idx, B->row_ptr, p->nnzA, p->P, p->part, s);
+  scan_row_lengths(A->col_idx, B->row_ptr, p->nnzA, p->P, p->bst, p->part, s);
   {
     RowStatsArgs ra;
     ra.arp = A->row_ptr;
@@ -554,7 +559,8 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   stage_begin(p, SPGEMM_T_BIN, s);
   scan_i64(p->h, m, p->cto, p->part, s);
   scan_i32(p->hist, nh, p->hist_scan, p->part, s);
-  launch_bin_scatter(p->u, m, p->be, p->hist_scan, p->nwaves, p->binlist, s);
+  launch_bin_scatter(p->u, m, p->be, p->hist_scan, p->nwaves, A->row_ptr, p->binlist,
+                     p->recs, s);
   launch_summary(p->P, p->nnzA, p->cto, m, p->hist_scan, p->nwaves, p->bpart, p->nblocks,
                  p->dsum, s);
   stage_end(p, SPGEMM_T_BIN, s);
@@ -720,6 +726,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   ea.bcol = B->col_idx;
   ea.bval = static_cast<const T *>(B->val);
   ea.P = p->P;
+  ea.bst = p->bst;
   ea.u = p->u;
   ea.cto = p->cto;
   ea.ct_col = ct_col;
@@ -742,7 +749,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     for (int b = 36; b >= 33; --b) {
       const int cap = static_cast<int>(next_pow2(p->be.e[b - 32]));
       const int64_t r0 = S.bin_off[b], r1 = S.bin_off[b + 1];
-      if (launch_esc<T>(ea, p->binlist + r0, r1 - r0, cap, p->n, es))
+      if (launch_esc<T>(ea, p->recs + r0, r1 - r0, cap, p->n, es))
         return fail(SPGEMM_EINVAL, "no ESC kernel for this capacity");
     }
     stage_end(p, SPGEMM_T_MEDIUM, es);
@@ -750,7 +757,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     stage_begin(p, SPGEMM_T_TINY, es);
     if (p->opt.tiny_heap) {
       // bin 1 through the wavefront kernel, bins 2..edge[0] one kernel each
-      if (launch_esc<T>(ea, p->binlist + S.bin_off[1], S.bin_off[2] - S.bin_off[1], 1, p->n, es))
+      if (launch_esc<T>(ea, p->recs + S.bin_off[1], S.bin_off[2] - S.bin_off[1], 1, p->n, es))
         return fail(SPGEMM_EINVAL, "no ESC kernel for this capacity");
       for (int b = 2; b <= p->be.e[0]; ++b)
         if (launch_heap<T>(ea, p->binlist + S.bin_off[b], S.bin_off[b + 1] - S.bin_off[b], b, es))
@@ -761,7 +768,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
         const int cap = static_cast<int>(next_pow2(b));
         const int hi = std::min<int>(cap, p->be.e[0]);
         const int64_t r0 = S.bin_off[b], r1 = S.bin_off[hi + 1];
-        if (launch_esc<T>(ea, p->binlist + r0, r1 - r0, cap, p->n, es))
+        if (launch_esc<T>(ea, p->recs + r0, r1 - r0, cap, p->n, es))
           return fail(SPGEMM_EINVAL, "no ESC kernel for this capacity");
         b = hi + 1;
       }
@@ -1189,7 +1196,7 @@ int backward_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, const sp
   p->info.bytes_scratch =
       held_bytes(p) + (W ? static_cast<int64_t>(alloc_size(static_cast<size_t>(nprod) * sizeof(T))) : 0);
   if (want_a || W)
-    launch_grad_entries<T>(A->row_ptr, A->col_idx, aval, p->m, p->nnzA, p->P, B->row_ptr,
+    launch_grad_entries<T>(A->row_ptr, aval, p->m, p->nnzA, p->P, p->bst,
                            B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, W, s);
   if (want_b) {
     if (W) {
@@ -1268,7 +1275,7 @@ int backward_static_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B,
   T *dA = want_a ? static_cast<T *>(dA_val) : nullptr;
   T *dB = want_b ? static_cast<T *>(dB_val) : nullptr;
   if (!want_b) {
-    launch_grad_entries<T>(A->row_ptr, A->col_idx, aval, p->m, p->nnzA, p->P, B->row_ptr,
+    launch_grad_entries<T>(A->row_ptr, aval, p->m, p->nnzA, p->P, p->bst,
                            B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, nullptr, s);
     return SPGEMM_OK;
   }
@@ -1295,7 +1302,7 @@ int backward_static_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B,
   launch_transpose_pattern(A->row_ptr, A->col_idx, p->m, p->k, p->nnzA, cnt, tptr, trow, tpos,
                            tpart, s);
   if (want_a || W)
-    launch_grad_entries<T>(A->row_ptr, A->col_idx, aval, p->m, p->nnzA, p->P, B->row_ptr,
+    launch_grad_entries<T>(A->row_ptr, aval, p->m, p->nnzA, p->P, p->bst,
                            B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, W, s);
   if (W)
     launch_grad_b_sum<T>(tptr, tpos, p->P, B->row_ptr, p->k, W, dB, s);
@@ -1345,7 +1352,8 @@ const int64_t *plan_rowoff(spgemm_plan p) { return p->rowoff; }
 const int64_t *plan_scan(spgemm_plan p) { return p->P; }
 const int64_t *plan_upper(spgemm_plan p) { return p->u; }
 int64_t *plan_rownnz(spgemm_plan p) { return p->rownnz; }
-const int32_t *plan_binlist(spgemm_plan p) { return p->binlist; }
+const RowRec *plan_recs(spgemm_plan p) { return p->recs; }
+const int32_t *plan_bstart(spgemm_plan p) { return p->bst; }
 void set_last_error(const std::string &msg) { g_last_error = msg; }
 // the input checks of spgemm_analyze, for the batched forms
 int check_problem(const spgemm_csr *A, const spgemm_csr *B) {

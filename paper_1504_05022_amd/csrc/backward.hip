@@ -133,8 +133,8 @@ constexpr int BW_NT = 256;  // four independent wavefronts
 
 template <typename T, bool DENSE>
 __global__ __launch_bounds__(BW_NT) void k_grad_entries(
-    const int32_t *arp, const int32_t *acol, const T *aval, int64_t m, int64_t nnz,
-    const int64_t *P, const int32_t *brp, const int32_t *bcol, const T *bval, const int32_t *crp,
+    const int32_t *arp, const T *aval, int64_t m, int64_t nnz,
+    const int64_t *P, const int32_t *bst, const int32_t *bcol, const T *bval, const int32_t *crp,
     const int32_t *ccol, const T *dc, T *dA, T *W) {
   constexpr int NWV = BW_NT / WAVE;
   constexpr int BW_CH = bw_ch<DENSE>();
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
     const int nb = static_cast<int>(e1 - eb < WAVE ? e1 - eb : WAVE);
     const bool in = ln < nb;
     const int64_t e = in ? eb + ln : e1 - 1;
-    const int32_t j = acol[e];
+    const int32_t q0 = bst[e];
     const T av = aval[e];
     const int64_t Pb = P[eb];
     const int64_t pre = P[e] - Pb;
@@ -163,7 +163,6 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
     const int64_t tot = P[eb + nb] - Pb;
     const int32_t row = row_of(arp, row_lo, row_hi, e);
     row_lo = __builtin_amdgcn_readlane(row, nb - 1);
-    const int32_t q0 = brp[j];
     const int32_t c0 = crp[row], c1 = crp[row + 1];
     const bool some = in && len > 0;
     const int c = __popcll(__ballot(some) & (le_mask >> 1));  // entries with products below
@@ -376,8 +375,8 @@ __global__ __launch_bounds__(256) void k_grad_b_sum(const int64_t *tptr, const i
 }
 
 template <typename T>
-void launch_grad_entries(const int32_t *arp, const int32_t *acol, const T *aval, int64_t m,
-                         int64_t nnz, const int64_t *P, const int32_t *brp, const int32_t *bcol,
+void launch_grad_entries(const int32_t *arp, const T *aval, int64_t m, int64_t nnz,
+                         const int64_t *P, const int32_t *bst, const int32_t *bcol,
                          const T *bval, int64_t n, const int32_t *crp, const int32_t *ccol,
                          const T *dc, T *dA, T *W, hipStream_t s) {
   if (nnz <= 0) return;
@@ -385,11 +384,11 @@ void launch_grad_entries(const int32_t *arp, const int32_t *acol, const T *aval,
   if (n <= BW_MAP) {
     constexpr int64_t PER = int64_t(NWV) * bw_ch<true>();
     hipLaunchKernelGGL((k_grad_entries<T, true>), dim3((nnz + PER - 1) / PER), dim3(BW_NT), 0, s,
-                       arp, acol, aval, m, nnz, P, brp, bcol, bval, crp, ccol, dc, dA, W);
+                       arp, aval, m, nnz, P, bst, bcol, bval, crp, ccol, dc, dA, W);
   } else {
     constexpr int64_t PER = int64_t(NWV) * bw_ch<false>();
     hipLaunchKernelGGL((k_grad_entries<T, false>), dim3((nnz + PER - 1) / PER), dim3(BW_NT), 0, s,
-                       arp, acol, aval, m, nnz, P, brp, bcol, bval, crp, ccol, dc, dA, W);
+                       arp, aval, m, nnz, P, bst, bcol, bval, crp, ccol, dc, dA, W);
   }
 }
 
@@ -401,12 +400,12 @@ void launch_grad_b_sum(const int64_t *tptr, const int32_t *tpos, const int64_t *
                      tpos, P, brp, kb, W, dB);
 }
 
-template void launch_grad_entries<float>(const int32_t *, const int32_t *, const float *, int64_t,
+template void launch_grad_entries<float>(const int32_t *, const float *, int64_t,
                                          int64_t, const int64_t *, const int32_t *,
                                          const int32_t *, const float *, int64_t,
                                          const int32_t *, const int32_t *, const float *, float *,
                                          float *, hipStream_t);
-template void launch_grad_entries<double>(const int32_t *, const int32_t *, const double *,
+template void launch_grad_entries<double>(const int32_t *, const double *,
                                           int64_t, int64_t, const int64_t *, const int32_t *,
                                           const int32_t *, const double *, int64_t,
                                           const int32_t *, const int32_t *, const double *,

@@ -40,7 +40,8 @@ struct BatchProblem {
   int32_t *ccol;
   void *cval;
   int64_t *rownnz;
-  const int32_t *binlist;
+  const RowRec *recs;   // rows by bin
+  const int32_t *bst;   // first entry of B's row, per entry of A
   int32_t dtype;
   int32_t pad;
 };
@@ -68,6 +69,7 @@ DEVI EscArgs<T> esc_args_of(const BatchProblem &bp) {
   e.bcol = bp.bcol;
   e.bval = static_cast<const T *>(bp.bval);
   e.P = bp.P;
+  e.bst = bp.bst;
   e.u = bp.u;
   e.cto = bp.rowoff;  // rows land directly at their final place in C
   e.ct_col = bp.ccol;
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(ESC_NT) void k_batch_class(const BatchItem *items,
   __shared__ __align__(16) unsigned char lds[EscShape<double, G, K, uint32_t>::lds_bytes];
   const BatchItem it = items[blockIdx.x];
   const BatchProblem bp = probs[it.prob];
-  const int32_t *rows = bp.binlist + it.start;
+  const RowRec *rows = bp.recs + it.start;
   if (bp.dtype == SPGEMM_F64)
     esc_rows<double, G, K, uint32_t>(esc_args_of<double>(bp), rows, 0, it.count, lds);
   else
@@ -186,21 +188,25 @@ __host__ __device__ inline int bm_class(int64_t u) {
   return c;
 }
 
-// Stage 1, products of every entry: w[e] = nnz(b_{col(e)*}).
+// Stage 1, products of every entry: w[e] = nnz(b_{col(e)*}), and where that
+// row starts in B.
 __global__ __launch_bounds__(BM_NT) void k_bm_entries(const BmTile *tiles, const BmProblem *probs,
-                                                      int32_t *w) {
+                                                      int32_t *w, int32_t *bst) {
   const BmTile t = tiles[blockIdx.x];
   const BmProblem &q = probs[t.prob];
   const int32_t *acol = q.acol;
   const int32_t *brp = q.brp;
   const int64_t nnz = q.nnz;
   int32_t *wp = w + q.eo;
+  int32_t *bp = bst + q.eo;
 #pragma unroll
   for (int j = 0; j < BM_ENTRY_TILE / BM_NT; ++j) {
     const int64_t e = t.start + j * BM_NT + threadIdx.x;
     if (e < nnz) {
       const int32_t c = acol[e];
-      wp[e] = brp[c + 1] - brp[c];
+      const int32_t b0 = brp[c];
+      wp[e] = brp[c + 1] - b0;
+      bp[e] = b0;
     }
   }
 }
@@ -237,12 +243,21 @@ __global__ __launch_bounds__(BM_NT) void k_bm_rows(const BmTile *tiles, const Bm
 // within a list does not matter (every row goes to its own place in C~).
 __global__ __launch_bounds__(BM_NT) void k_bm_scatter(const BmTile *tiles, const BmProblem *probs,
                                                       const int64_t *U, unsigned long long *cur,
-                                                      int32_t *list) {
+                                                      RowRec *list) {
   const BmTile t = tiles[blockIdx.x];
   const BmProblem &q = probs[t.prob];
   if (!q.batched) return;
   const int64_t i = t.start + threadIdx.x;
-  const int c = i < q.m ? bm_class(U[q.ro + i]) : -1;
+  const bool valid = i < q.m;
+  RowRec rec{static_cast<int32_t>(i), 0, 0, 0};
+  int c = -1;
+  if (valid) {
+    const int64_t u = U[q.ro + i];
+    c = bm_class(u);
+    rec.u = static_cast<int32_t>(u);  // listed rows have at most 1024 products
+    rec.e0 = q.arp[i];
+    rec.ne = q.arp[i + 1] - rec.e0;
+  }
   unsigned long long *cp = cur + static_cast<int64_t>(t.prob) * BM_NCLS;
   const unsigned long long below = (1ull << lane()) - 1ull;
   for (int k = 0; k < kBatchNumClasses; ++k) {
@@ -251,7 +266,7 @@ __global__ __launch_bounds__(BM_NT) void k_bm_scatter(const BmTile *tiles, const
     unsigned long long b = 0;
     if (lane() == 0) b = atomicAdd(cp + k, static_cast<unsigned long long>(__popcll(mk)));
     b = static_cast<unsigned long long>(__shfl(static_cast<long long>(b), 0, WAVE));
-    if (c == k) list[b + __popcll(mk & below)] = static_cast<int32_t>(i);
+    if (c == k) list[b + __popcll(mk & below)] = rec;
   }
 }
 
@@ -591,7 +606,8 @@ int spgemm_batch_create(int32_t count, const spgemm_csr *A, const spgemm_csr *B,
       q.ccol = b->C[p].col_idx;
       q.cval = b->C[p].val;
       q.rownnz = plan_rownnz(cd.plans[p]);
-      q.binlist = plan_binlist(cd.plans[p]);
+      q.recs = plan_recs(cd.plans[p]);
+      q.bst = plan_bstart(cd.plans[p]);
       q.dtype = A[p].dtype;
       q.pad = 0;
     }
@@ -854,7 +870,8 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   const size_t o_cnt = add(sizeof(unsigned long long) * (ncnt + count));  // counts, then sums of u
   const size_t o_cur = add(sizeof(unsigned long long) * ncnt);
   const size_t o_io = add(sizeof(int64_t) * ncnt);
-  const size_t o_list = add(sizeof(int32_t) * R);
+  const size_t o_list = add(sizeof(RowRec) * R);
+  const size_t o_bst = add(sizeof(int32_t) * E);
   const size_t o_g = add(sizeof(int64_t) * (count + 1));
   const size_t o_bp = add(sizeof(BatchProblem) * count);
   char *ws = static_cast<char *>(mem.get(off));
@@ -873,7 +890,8 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   unsigned long long *dsumu = dcnt + ncnt;
   unsigned long long *dcur = reinterpret_cast<unsigned long long *>(ws + o_cur);
   int64_t *dio = reinterpret_cast<int64_t *>(ws + o_io);
-  int32_t *dlist = reinterpret_cast<int32_t *>(ws + o_list);
+  RowRec *dlist = reinterpret_cast<RowRec *>(ws + o_list);
+  int32_t *dbst = reinterpret_cast<int32_t *>(ws + o_bst);
   int64_t *dg = reinterpret_cast<int64_t *>(ws + o_g);
   BatchProblem *dbp = reinterpret_cast<BatchProblem *>(ws + o_bp);
   int64_t bytes_scratch = static_cast<int64_t>(off);
@@ -890,7 +908,7 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   // stage 1 over every problem: products per entry, their scan, u_i
   if (!etile.empty())
     hipLaunchKernelGGL(k_bm_entries, dim3(static_cast<unsigned int>(etile.size())), dim3(BM_NT),
-                       0, s, det, dprob, dw);
+                       0, s, det, dprob, dw, dbst);
   scan_i32(dw, E, dP, dpart, s);
   hipLaunchKernelGGL(k_bm_rows, dim3(static_cast<unsigned int>(rtile.size())), dim3(BM_NT), 0, s,
                      drt, dprob, dP, dU, dRN, dcnt, dsumu);
@@ -978,7 +996,8 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
     q.ccol = reinterpret_cast<int32_t *>(tcol);
     q.cval = const_cast<void *>(hp[p].tval);
     q.rownnz = dRN + hp[p].ro;
-    q.binlist = dlist;
+    q.recs = dlist;
+    q.bst = dbst + hp[p].eo;
     q.dtype = A[p].dtype;
     q.pad = 0;
   }

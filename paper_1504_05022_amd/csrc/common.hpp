@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 #define DEVI __device__ __forceinline__
 
 namespace spg {
@@ -51,17 +53,17 @@ template <int C> DEVI int64_t xcd_block_id() {
 // Value of lane (lane ^ m).  With m known at compile time, masks 1, 2, 3, 7,
 // 8 and 15 are DPP moves inside the VALU (quad permutations, the mirror of
 // each half row of 8 and of each row of 16 lanes, a rotation of each row by
-// 8), 4, 16 and 31 are LDS-unit swizzles inside groups of 32 lanes (no
+// 8; every lane has a source, so there is no old value to set first), 4, 16 and 31 are LDS-unit swizzles inside groups of 32 lanes (no
 // address operand), others go through ds_bpermute.
 DEVI uint32_t shfl_xor_u32(uint32_t v, int m) {
   const int x = static_cast<int>(v);
   switch (m) {
-    case 1: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false));
-    case 2: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false));
-    case 3: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, x, 0x1B, 0xF, 0xF, false));
-    case 7: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false));
-    case 8: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, false));
-    case 15: return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false));
+    case 1: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, false));
+    case 2: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, false));
+    case 3: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(x, 0x1B, 0xF, 0xF, false));
+    case 7: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, false));
+    case 8: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, false));
+    case 15: return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, false));
     case 4: return static_cast<uint32_t>(__builtin_amdgcn_ds_swizzle(x, 0x1F | (4 << 10)));
     case 16: return static_cast<uint32_t>(__builtin_amdgcn_ds_swizzle(x, 0x1F | (16 << 10)));
     case 31: return static_cast<uint32_t>(__builtin_amdgcn_ds_swizzle(x, 0x1F | (31 << 10)));
@@ -270,7 +272,7 @@ DEVI void stage_lanes(Key (&k)[K], int pos, int size, int stride) {
 
 // The same network with every comparison ascending: each merge of two
 // sorted halves of a block of `size` starts by comparing element i with its
-// mirror i ^ (size - 1) (which leaves two bitonic halves, every key of the
+// mirror size - 1 - i (which leaves two bitonic halves, every key of the
 // first at most every key of the second), then halves them with strides
 // size/4 .. 1.  No comparison depends on a lane's block direction, so the
 // register stages need no selects and the lane stages one per key.
@@ -279,15 +281,6 @@ template <int K, typename Key> DEVI void cas_asc(Key &a, Key &b) {
   const Key hi = a < b ? b : a;
   a = lo;
   b = hi;
-}
-
-// Partner kk ^ M in registers (M < K), the lower index keeping the minimum.
-template <int K, int M, typename Key> DEVI void flip_regs(Key (&k)[K]) {
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) {
-    const int p = kk ^ M;
-    if (p > kk) cas_asc<K, Key>(k[kk], k[p]);
-  }
 }
 
 // The key a lane keeps from (own, partner's): the minimum in the lower lane,
@@ -335,35 +328,101 @@ template <int K, int SIZE, typename Key> DEVI void mirror_lanes(Key (&k)[K], int
     k[kk] = keep_of<Key>(k[kk], oa, lower, bound);
     k[K - 1 - kk] = keep_of<Key>(k[K - 1 - kk], ob, lower, bound);
   }
+  if constexpr (K % 2 != 0 && K > 1)
+    k[K / 2] = keep_of<Key>(k[K / 2], shfl_xor_key<Key>(k[K / 2], PM), lower, bound);
 }
 
-// The halving stages STRIDE, STRIDE / 2, .. 1 of one merge.
-template <int K, int STRIDE, typename Key> DEVI void half_stages(Key (&k)[K], int pos) {
-  if constexpr (STRIDE > 0) {
-    if constexpr (STRIDE < K)
-      flip_regs<K, STRIDE, Key>(k);
-    else
-      half_lanes<K, STRIDE, Key>(k, pos);
-    half_stages<K, STRIDE / 2, Key>(k, pos);
+// Comparator networks inside a lane's K registers.  Sorting: Batcher's
+// merge exchange (Knuth, The Art of Computer Programming, vol. 3, section
+// 5.2.2, algorithm M), which takes any K.  Merging a bitonic sequence:
+// halving while the length is even, then a network of 3, 5 or 7 keys (the
+// merge exchange without the comparators that no bitonic sequence needs).
+// Both were checked on every 0-1 sequence of their kind.
+struct NetPairs {
+  int n;
+  signed char a[80], b[80];
+  constexpr void add(int x, int y) {
+    a[n] = static_cast<signed char>(x);
+    b[n] = static_cast<signed char>(y);
+    ++n;
+  }
+};
+constexpr NetPairs sort_net(int k) {
+  NetPairs p{};
+  int t = 0;
+  while ((1 << t) < k) ++t;
+  for (int pp = t > 0 ? 1 << (t - 1) : 0; pp > 0; pp /= 2) {
+    int q = 1 << (t - 1), r = 0, d = pp;
+    for (;;) {
+      for (int i = 0; i + d < k; ++i)
+        if ((i & pp) == r) p.add(i, i + d);
+      if (q == pp) break;
+      d = q - pp;
+      q /= 2;
+      r = pp;
+    }
+  }
+  return p;
+}
+constexpr void add_merge_net(NetPairs &p, int lo, int k) {
+  if (k == 3) {
+    p.add(lo, lo + 2), p.add(lo, lo + 1), p.add(lo + 1, lo + 2);
+  } else if (k == 5) {
+    p.add(lo, lo + 4), p.add(lo, lo + 2), p.add(lo + 1, lo + 3), p.add(lo + 2, lo + 4);
+    p.add(lo, lo + 1), p.add(lo + 2, lo + 3), p.add(lo + 1, lo + 2), p.add(lo + 3, lo + 4);
+  } else if (k == 7) {
+    p.add(lo, lo + 4), p.add(lo + 1, lo + 5), p.add(lo + 2, lo + 6), p.add(lo, lo + 2);
+    p.add(lo + 1, lo + 3), p.add(lo + 4, lo + 6), p.add(lo + 3, lo + 5), p.add(lo, lo + 1);
+    p.add(lo + 2, lo + 3), p.add(lo + 4, lo + 5), p.add(lo + 1, lo + 2), p.add(lo + 3, lo + 4);
+    p.add(lo + 5, lo + 6);
+  } else if (k > 1) {  // even
+    for (int i = 0; i < k / 2; ++i) p.add(lo + i, lo + k / 2 + i);
+    add_merge_net(p, lo, k / 2);
+    add_merge_net(p, lo + k / 2, k / 2);
+  }
+}
+constexpr NetPairs merge_net(int k) {
+  NetPairs p{};
+  add_merge_net(p, 0, k);
+  return p;
+}
+template <int K, bool MERGE> struct Net {
+  static constexpr NetPairs p = MERGE ? merge_net(K) : sort_net(K);
+};
+template <typename N, int K, typename Key, int... I>
+DEVI void net_apply(Key (&k)[K], std::integer_sequence<int, I...>) {
+  (cas_asc<K, Key>(k[N::p.a[I]], k[N::p.b[I]]), ...);
+}
+template <int K, bool MERGE, typename Key> DEVI void net_regs(Key (&k)[K]) {
+  using N = Net<K, MERGE>;
+  net_apply<N, K, Key>(k, std::make_integer_sequence<int, N::p.n>{});
+}
+
+// The halving stages across lanes S, S / 2, .. 1 apart, then inside a lane.
+template <int K, int S, typename Key> DEVI void half_stages(Key (&k)[K], int pos) {
+  if constexpr (S > 0) {
+    half_lanes<K, S * K, Key>(k, pos);
+    half_stages<K, S / 2, Key>(k, pos);
+  } else {
+    net_regs<K, true, Key>(k);
   }
 }
 
-// Merges of blocks of SIZE, 2 SIZE, .. N (each instantiated, so that every
+// Merges of blocks of L, 2 L, .. G lanes (each instantiated, so that every
 // stride and partner is a constant).
-template <int N, int K, int SIZE, typename Key> DEVI void merges_from(Key (&k)[K], int pos) {
-  if constexpr (SIZE <= N) {
-    if constexpr (SIZE <= K)
-      flip_regs<K, SIZE - 1, Key>(k);
-    else
-      mirror_lanes<K, SIZE, Key>(k, pos);
-    half_stages<K, SIZE / 4, Key>(k, pos);
-    merges_from<N, K, SIZE * 2, Key>(k, pos);
+template <int G, int K, int L, typename Key> DEVI void merges_from(Key (&k)[K], int pos) {
+  if constexpr (L <= G) {
+    mirror_lanes<K, L * K, Key>(k, pos);
+    half_stages<K, L / 4, Key>(k, pos);
+    merges_from<G, K, L * 2, Key>(k, pos);
   }
 }
 
-// Sort G*K keys held by an aligned group of G lanes (G <= 64).
+// Sort G*K keys held by an aligned group of G lanes (G a power of two up to
+// 64, any K).
 template <int G, int K, typename Key> DEVI void group_bitonic_sort(Key (&k)[K]) {
-  merges_from<G * K, K, 2, Key>(k, lane() & (G - 1));
+  net_regs<K, false, Key>(k);
+  merges_from<G, K, 2, Key>(k, lane() & (G - 1));
 }
 
 // Sort NT*K keys held by a work-group of NT threads.  Strides that cross
@@ -409,6 +468,11 @@ template <> struct KeyMax<uint64_t> { static constexpr uint64_t v = 0xffffffffff
 
 template <int B> struct Log2 { static constexpr int v = 1 + Log2<B / 2>::v; };
 template <> struct Log2<1> { static constexpr int v = 0; };
+constexpr int ceil_log2(int x) {
+  int t = 0;
+  while ((1 << t) < x) ++t;
+  return t;
+}
 
 // Folds a tile sorted on (column, stream index) and held by an aligned group
 // of G lanes: rank pos*K + kk (pos = lane in the group) is key[kk], the
@@ -423,7 +487,8 @@ template <typename T, int G, int K, typename Key>
 DEVI int fold_runs(const Key (&key)[K], const int tn, const T *pv, int32_t *sc, T *sv,
                    const int32_t cbase) {
   constexpr int U = G * K;
-  constexpr int LOGU = Log2<U>::v;
+  constexpr int LOGU = ceil_log2(U);
+  constexpr Key LMASK = (Key(1) << LOGU) - 1;
   constexpr Key KMAX = KeyMax<Key>::v;
   const int pos = lane() & (G - 1);
   const Key pk = shfl_up_key<Key>(key[K - 1], 1);  // rank pos*K - 1
@@ -447,7 +512,7 @@ DEVI int fold_runs(const Key (&key)[K], const int tn, const T *pv, int32_t *sc, 
   auto run_from = [&](T run) {
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
-      const T v = pv[static_cast<int>(key[kk] & (U - 1))];
+      const T v = pv[static_cast<int>(key[kk] & LMASK)];
       run = (hmask & (1u << kk)) ? T(0) + v : run + v;
     }
     return run;
@@ -480,7 +545,7 @@ DEVI int fold_runs(const Key (&key)[K], const int tn, const T *pv, int32_t *sc, 
     T run = cin;
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
-      const T v = pv[static_cast<int>(key[kk] & (U - 1))];
+      const T v = pv[static_cast<int>(key[kk] & LMASK)];
       run = (hmask & (1u << kk)) ? T(0) + v : run + v;
       tv[kk] = run;
     }

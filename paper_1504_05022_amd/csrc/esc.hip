@@ -5,8 +5,8 @@
 // thread group per row with a bitonic ESC in scratchpad memory for 33..512.
 // Here one kernel template covers both: a row with u <= G*K products is
 // handled by G lanes holding K products each.  Products are expanded into
-// LDS (run starts of every b_j* row, then a segmented max-scan gives each
-// product its a_ij), sorted with a bitonic network on the key
+// LDS (a bit mask of the run starts of the b_j* rows; counting its bits gives
+// each product its run and so its a_ij and its entry of B), sorted with a bitonic network on the key
 // (column, position in the expansion order) entirely in registers and
 // cross-lane shuffles, and compressed: each column's products are folded in
 // expansion order starting from +0.0 (so the values equal Gustavson's
@@ -22,7 +22,7 @@ template <int G, int K> constexpr int esc_occupancy() { return K >= 8 && G < 64 
 
 template <typename T, int G, int K, typename Key>
 __global__ __launch_bounds__(ESC_NT) __attribute__((amdgpu_waves_per_eu(esc_occupancy<G, K>())))
-void k_esc(EscArgs<T> a, const int32_t *rows, int64_t nrows) {
+void k_esc(EscArgs<T> a, const RowRec *rows, int64_t nrows) {
   using Sh = EscShape<T, G, K, Key>;
   __shared__ __align__(16) unsigned char lds[Sh::lds_bytes];
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * Sh::RPB; base < nrows;
@@ -31,7 +31,7 @@ void k_esc(EscArgs<T> a, const int32_t *rows, int64_t nrows) {
 }
 
 template <typename T, int G, int K>
-static void launch_gk(const EscArgs<T> &a, const int32_t *rows, int64_t nrows, int64_t ncols,
+static void launch_gk(const EscArgs<T> &a, const RowRec *rows, int64_t nrows, int64_t ncols,
                       hipStream_t s) {
   constexpr int RPB = ESC_NT / G;
   constexpr int LOGU = Log2<G * K>::v;
@@ -44,7 +44,7 @@ static void launch_gk(const EscArgs<T> &a, const int32_t *rows, int64_t nrows, i
 }
 
 template <typename T>
-int launch_esc(const EscArgs<T> &a, const int32_t *rows, int64_t nrows, int cap, int64_t ncols,
+int launch_esc(const EscArgs<T> &a, const RowRec *rows, int64_t nrows, int cap, int64_t ncols,
                hipStream_t s) {
   if (nrows <= 0) return 0;
   // lanes per row G and products per lane K for each capacity: several
@@ -66,9 +66,9 @@ int launch_esc(const EscArgs<T> &a, const int32_t *rows, int64_t nrows, int cap,
   return 0;
 }
 
-template int launch_esc<float>(const EscArgs<float> &, const int32_t *, int64_t, int, int64_t,
+template int launch_esc<float>(const EscArgs<float> &, const RowRec *, int64_t, int, int64_t,
                                hipStream_t);
-template int launch_esc<double>(const EscArgs<double> &, const int32_t *, int64_t, int, int64_t,
+template int launch_esc<double>(const EscArgs<double> &, const RowRec *, int64_t, int, int64_t,
                                 hipStream_t);
 
 }  // namespace spg

@@ -308,12 +308,23 @@ struct ComputeStatus {
 // int64 entries.
 int64_t scan_part_len(int64_t n);
 
-// w_e = nnz(b_{acol[e]*}), the per-entry term of Algorithm 2.
+// w_e = nnz(b_{acol[e]*}), the per-entry term of Algorithm 2; also records
+// where that row starts in B (bst), which every numeric kernel would
+// otherwise gather again.
 void scan_row_lengths(const int32_t *acol, const int32_t *brp, int64_t n, int64_t *out,
-                      int64_t *part, hipStream_t s);
+                      int32_t *bst, int64_t *part, hipStream_t s);
 // Plain int64 arrays (hybrid row sizes, row nnz, histograms).
 void scan_i64(const int64_t *v, int64_t n, int64_t *out, int64_t *part, hipStream_t s);
 void scan_i32(const int32_t *v, int64_t n, int64_t *out, int64_t *part, hipStream_t s);
+
+// A row of a bin list with what the short-row kernels need to start on it:
+// one 16-byte load instead of three dependent ones.
+struct alignas(16) RowRec {
+  int32_t row;
+  int32_t u;   // u_i (saturated)
+  int32_t e0;  // first entry of A
+  int32_t ne;  // entries
+};
 
 // ------------------------------------------------------------- analyze
 
@@ -345,7 +356,8 @@ constexpr int kBlockStats = 16;
 void launch_row_stats(const RowStatsArgs &a, hipStream_t s);
 // Stable scatter of the rows into their bins.
 void launch_bin_scatter(const int64_t *u, int64_t m, BinEdges be, const int64_t *hist_scan,
-                        int64_t nwaves, int32_t *binlist, hipStream_t s);
+                        int64_t nwaves, const int32_t *arp, int32_t *binlist, RowRec *recs,
+                        hipStream_t s);
 void launch_summary(const int64_t *P, int64_t nnzA, const int64_t *cto, int64_t m,
                     const int64_t *hist_scan, int64_t nwaves, const int64_t *bpart,
                     int64_t nblocks, Summary *sum, hipStream_t s);
@@ -358,6 +370,7 @@ template <typename T> struct EscArgs {
   const int32_t *brp, *bcol;
   const T *bval;
   const int64_t *P;       // scanned row lengths (Algorithm 2 partial sums)
+  const int32_t *bst;     // first entry of b_{acol[e]*}, per entry of A
   const int64_t *u;
   const int64_t *cto;     // C~ row offsets
   int32_t *ct_col;        // C~
@@ -368,7 +381,7 @@ template <typename T> struct EscArgs {
 // Rows of one capacity class (u <= cap, cap a power of two <= 1024) with
 // the wavefront-level expand-sort-compress kernel.
 template <typename T>
-int launch_esc(const EscArgs<T> &a, const int32_t *rows, int64_t nrows, int cap, int64_t ncols,
+int launch_esc(const EscArgs<T> &a, const RowRec *rows, int64_t nrows, int cap, int64_t ncols,
                hipStream_t s);
 
 // Rows of one exact size 2..32 with the paper's one-thread heap method
@@ -519,8 +532,8 @@ void launch_transpose_pattern(const int32_t *arp, const int32_t *acol, int64_t m
 // Entry-parallel gradient: dA (nullable) and the products W (nullable,
 // sum(u) entries) of the dB sums; then dB from W over A's transposed pattern.
 template <typename T>
-void launch_grad_entries(const int32_t *arp, const int32_t *acol, const T *aval, int64_t m,
-                         int64_t nnz, const int64_t *P, const int32_t *brp, const int32_t *bcol,
+void launch_grad_entries(const int32_t *arp, const T *aval, int64_t m, int64_t nnz,
+                         const int64_t *P, const int32_t *bst, const int32_t *bcol,
                          const T *bval, int64_t n, const int32_t *crp, const int32_t *ccol,
                          const T *dc, T *dA, T *W, hipStream_t s);
 template <typename T>
@@ -540,7 +553,8 @@ const int64_t *plan_rowoff(spgemm_plan p);
 const int64_t *plan_scan(spgemm_plan p);
 const int64_t *plan_upper(spgemm_plan p);
 int64_t *plan_rownnz(spgemm_plan p);
-const int32_t *plan_binlist(spgemm_plan p);
+const RowRec *plan_recs(spgemm_plan p);
+const int32_t *plan_bstart(spgemm_plan p);
 void set_last_error(const std::string &msg);
 // input checks of spgemm_analyze (CSR shapes and dtypes; option ranges)
 int check_problem(const spgemm_csr *A, const spgemm_csr *B);

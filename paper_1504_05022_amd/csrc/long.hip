@@ -474,14 +474,13 @@ DEVI void long_item(LongArgs<T> &a, const int32_t item_id) {
       const int64_t s1 = a.e.P[e + 1] - pbase;
       if (s0 <= pos + tn && pos + tn < s1) sh.next_first = e;
       if (s0 < pos + tn && s1 > pos && s1 > s0) {
-        const int32_t j = a.e.acol[e];
         int64_t ls = s0 - pos;
         int32_t off = 0;
         if (ls < 0) {
           off = static_cast<int32_t>(-ls);
           ls = 0;
         }
-        rs[tix<NT, KT>(static_cast<int>(ls))] = a.e.brp[j] + off;
+        rs[tix<NT, KT>(static_cast<int>(ls))] = a.e.bst[e] + off;
         ra[tix<NT, KT>(static_cast<int>(ls))] = a.e.aval[e];
       }
     }
@@ -888,7 +887,7 @@ DEVI void long1_body(LongArgs<T> &a, const int32_t item_id, const LongItem &item
         off = static_cast<int32_t>(-ls);
         ls = 0;
       }
-      rs[tix<NT, KT>(static_cast<int>(ls))] = a.e.brp[a.e.acol[e]] + off;
+      rs[tix<NT, KT>(static_cast<int>(ls))] = a.e.bst[e] + off;
       ra[tix<NT, KT>(static_cast<int>(ls))] = a.e.aval[e];
     }
   }
@@ -1034,7 +1033,7 @@ DEVI void long1_radix(LongArgs<T> &a, const int32_t item_id, const LongItem &ite
         off = static_cast<int32_t>(-ls);
         ls = 0;
       }
-      rs[tix<NT, KT>(static_cast<int>(ls))] = a.e.brp[a.e.acol[e]] + off;
+      rs[tix<NT, KT>(static_cast<int>(ls))] = a.e.bst[e] + off;
       ra[tix<NT, KT>(static_cast<int>(ls))] = a.e.aval[e];
     }
   }
@@ -1613,7 +1612,7 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
     const int32_t ec = in ? e : e1 - 1;
     const int64_t s0 = gP[ec] - pbase;
     const int64_t s1 = gP[ec + 1] - pbase;
-    const int32_t j = as_global(a.e.acol)[ec];
+    const int32_t b0 = as_global(a.e.bst)[ec];
     const T av = as_global(a.e.aval)[ec];
     if (in && s0 < p1 && s1 > p0 && s1 > s0) {
       int64_t ls = s0 - p0;
@@ -1622,7 +1621,7 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
         off = static_cast<int32_t>(-ls);
         ls = 0;
       }
-      rs[wix<K>(static_cast<int>(ls))] = as_global(a.e.brp)[j] + off;
+      rs[wix<K>(static_cast<int>(ls))] = b0 + off;
       ra[wix<K>(static_cast<int>(ls))] = av;
     }
     if (!__any(in && s1 < p1)) break;  // the next chunk starts at or after p1

@@ -240,9 +240,8 @@ DEVI void wave_direct(const EscArgs<T> &e, int32_t row, int64_t q0, int64_t q1,
       const int64_t ps = e.P[ee] - P0, pe = e.P[ee + 1] - P0;
       const int64_t lo = ps > q0 ? ps : q0, hi = pe < q1 ? pe : q1;
       if (hi > lo) {
-        const int32_t j = e.acol[ee];
         len = static_cast<int32_t>(hi - lo);
-        src = static_cast<int64_t>(e.brp[j]) + (lo - ps);
+        src = static_cast<int64_t>(e.bst[ee]) + (lo - ps);
         if (WANT_VAL) av = e.aval[ee];
       }
       pstart = lo - q0;
@@ -753,8 +752,7 @@ void k_wdense(WinArgsW<T> a, uint32_t *dbits, T *dacc) {
         const int64_t ps = a.e.P[ee] - P0, pe = a.e.P[ee + 1] - P0;
         const int64_t lo = ps > q0 ? ps : q0, hi = pe < q1 ? pe : q1;
         if (hi > lo) {
-          const int32_t j = a.e.acol[ee];
-          start = a.e.brp[j] + static_cast<int32_t>(lo - ps);
+          start = a.e.bst[ee] + static_cast<int32_t>(lo - ps);
           len = static_cast<int32_t>(hi - lo);
           if (NUM) av = a.e.aval[ee];
         }

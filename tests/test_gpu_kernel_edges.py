@@ -55,3 +55,20 @@ def test_backward_ragged_rows(dtype, n):
     terms = (np.array(lens)[A.col_idx], np.bincount(A.col_idx, minlength=k).repeat(lens))
     for got, ref, mag, t in zip((gA, gB), refs, mags, terms):
         assert np.all(np.abs(got.cpu().numpy() - ref) <= (t + 2) * eps * mag)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("col_range", [None, 60])
+def test_short_rows_around_network_sizes(dtype, col_range):
+    """Row sizes on both sides of every number of products per lane that the
+    short-row kernels choose (5, 6, 7, 8 and 10, 12, 16 times the lanes per
+    row), alone in a wavefront and beside rows of other sizes, with few and
+    with many equal columns, and with runs of B of one to many products:
+    bit-exact against the sequential sums."""
+    from test_gpu_parity import check
+    sizes = [g * k + d for g in (16, 32, 64) for k in (4, 5, 6, 7, 8) for d in (-1, 0, 1)]
+    sizes += [64 * k + d for k in (10, 12, 16) for d in (-1, 0, 1)]
+    sizes = [s for s in sorted(set(sizes)) if s <= 1024]
+    targets = sizes * 2 + [s for s in sizes for _ in range(4)]
+    A, B = S.crafted_rows(targets, col_range=col_range, empty_refs=3, dtype=dtype)
+    check(A, B, long_path=1, bin_edges=(32, 64, 128, 256, 1024))
