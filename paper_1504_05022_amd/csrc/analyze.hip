@@ -1,8 +1,10 @@
 // Stages 1-2 of the SpGEMM framework (Section 3.1): per-row upper bounds
 // (Algorithm 2) through a device prefix scan, binning (Algorithm 3) as a
-// per-wavefront histogram, a scan and a stable scatter, and the hybrid sizes
+// per-work-group histogram, a scan and a scatter, and the hybrid sizes
 // of the temporary matrix C~.  Also the reduce-then-scan primitive used by
 // every stage.
+#include <cstddef>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -24,14 +26,16 @@ struct __attribute__((packed, aligned(4))) RowBounds {
 // it writes: gathering the bounds twice was L2-request bound (3.2M entries:
 // 20 + 21 us; with the kept lengths 22 + 10).
 DEVI int64_t scan_tile_base(int64_t e) { return e / SCAN_TILE * SCAN_TILE; }
-struct RowLenFn {
+// (KEEP false: a scan of one tile, which needs no lengths kept.)
+template <bool KEEP> struct RowLenFn {
   const int32_t *acol;
   const int32_t *brp;
   int32_t *bst;
   int64_t *out;
   DEVI void keep(int64_t e, const RowBounds &r) const {
-    const int64_t base = scan_tile_base(e);
     bst[e] = r.begin;
+    if (!KEEP) return;
+    const int64_t base = scan_tile_base(e);
     reinterpret_cast<int32_t *>(out + base)[e - base] = r.end - r.begin;
   }
   DEVI int64_t operator()(int64_t e) const {
@@ -80,7 +84,9 @@ DEVI void scan_tile_load(const F &f, int64_t n, int64_t base, int64_t (&v)[SCAN_
 
 // Row lengths of a whole tile: all columns, then all row bounds, then the
 // stores (which the compiler may not move loads across).
-DEVI void scan_tile_load(const RowLenFn &f, int64_t n, int64_t base, int64_t (&v)[SCAN_IPT]) {
+template <bool KEEP>
+DEVI void scan_tile_load(const RowLenFn<KEEP> &f, int64_t n, int64_t base,
+                         int64_t (&v)[SCAN_IPT]) {
   if (base + SCAN_TILE <= n) {
     int32_t c[SCAN_IPT];
     RowBounds r[SCAN_IPT];
@@ -143,9 +149,12 @@ DEVI int scan_lds_ix(int i) { return i + i / SCAN_IPT; }
 // SELF: `part` holds the raw tile sums and every work-group adds up those
 // of the tiles before it (fine for a few thousand tiles; saves the launch of
 // phase 2); otherwise `part` is phase 2's exclusive scan.
-template <typename F, bool SELF>
+struct NoEnd {
+  DEVI void operator()(int64_t) const {}
+};
+template <typename F, bool SELF, typename End>
 __global__ __launch_bounds__(SCAN_NT) void k_scan_down(F f, int64_t n, const int64_t *part,
-                                                       int64_t nb, int64_t *out) {
+                                                       int64_t nb, int64_t *out, End end) {
   __shared__ int64_t sm[SCAN_NT / WAVE + 1];
   __shared__ int64_t tile[SCAN_TILE + SCAN_TILE / SCAN_IPT];
   const int t = threadIdx.x;
@@ -183,50 +192,63 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan_down(F f, int64_t n, const int
     const int64_t e = base + i;
     if (e < n) out[e] = tile[scan_lds_ix(i)];
   }
+  // `end` gets the total from one thread
   if constexpr (SELF) {
-    if (blockIdx.x == nb - 1 && t == 0) out[n] = offset + tot;
+    if (blockIdx.x == nb - 1 && t == 0) {
+      out[n] = offset + tot;
+      end(offset + tot);
+    }
   } else {
-    if (blockIdx.x == 0 && t == 0) out[n] = part[nb];
+    if (blockIdx.x == 0 && t == 0) {
+      out[n] = part[nb];
+      end(part[nb]);
+    }
   }
 }
 
 // tiles up to which a work-group of phase 3 sums the earlier tile sums itself
 constexpr int64_t SCAN_SELF_MAX_TILES = 4096;
 
-template <typename F, typename G>
-static void scan_with(F f, G down, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
+// Scans f; phase 1 sums `f`, phase 3 reads `down`, and a scan of one tile is
+// one launch over `one` (no earlier tiles to sum).
+template <typename F, typename G, typename H, typename End>
+static void scan_with(F f, G down, H one, End end, int64_t n, int64_t *out, int64_t *part,
+                      hipStream_t s) {
   const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
-  if (nb == 0) {
-    // out[0] = 0
-    hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(SCAN_NT), 0, s, part, int64_t(0));
-    hipLaunchKernelGGL((k_scan_down<G, false>), dim3(1), dim3(SCAN_NT), 0, s, down, n, part,
-                       int64_t(0), out);
+  if (nb <= 1) {
+    hipLaunchKernelGGL((k_scan_down<H, true, End>), dim3(1), dim3(SCAN_NT), 0, s, one, n, part,
+                       int64_t(1), out, end);
     return;
   }
   hipLaunchKernelGGL((k_scan_reduce<F>), dim3(nb), dim3(SCAN_NT), 0, s, f, n, part);
   if (nb <= SCAN_SELF_MAX_TILES) {
-    hipLaunchKernelGGL((k_scan_down<G, true>), dim3(nb), dim3(SCAN_NT), 0, s, down, n, part, nb,
-                       out);
+    hipLaunchKernelGGL((k_scan_down<G, true, End>), dim3(nb), dim3(SCAN_NT), 0, s, down, n, part,
+                       nb, out, end);
     return;
   }
   hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(SCAN_NT), 0, s, part, nb);
-  hipLaunchKernelGGL((k_scan_down<G, false>), dim3(nb), dim3(SCAN_NT), 0, s, down, n, part, nb,
-                     out);
+  hipLaunchKernelGGL((k_scan_down<G, false, End>), dim3(nb), dim3(SCAN_NT), 0, s, down, n, part,
+                     nb, out, end);
+}
+template <typename F>
+static void scan_plain(F f, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
+  scan_with(f, f, f, NoEnd{}, n, out, part, s);
 }
 
 void scan_row_lengths(const int32_t *acol, const int32_t *brp, int64_t n, int64_t *out,
                       int32_t *bst, int64_t *part, hipStream_t s) {
-  scan_with(RowLenFn{acol, brp, bst, out}, TileLenFn{out}, n, out, part, s);
+  scan_with(RowLenFn<true>{acol, brp, bst, out}, TileLenFn{out},
+            RowLenFn<false>{acol, brp, bst, out}, NoEnd{}, n, out, part, s);
 }
 void scan_i64(const int64_t *v, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
-  scan_with(I64Fn{v}, I64Fn{v}, n, out, part, s);
+  scan_plain(I64Fn{v}, n, out, part, s);
 }
 void scan_i32(const int32_t *v, int64_t n, int64_t *out, int64_t *part, hipStream_t s) {
-  scan_with(I32Fn{v}, I32Fn{v}, n, out, part, s);
+  scan_plain(I32Fn{v}, n, out, part, s);
 }
 void scan_piece_counts(const Piece *pieces, int64_t n, int64_t *out, int64_t *part,
                        hipStream_t s) {
-  scan_with(PieceFn{pieces}, PieceFn{pieces}, n, out, part, s);
+  scan_plain(PieceFn{pieces}, n, out, part, s);
 }
 
 // ------------------------------------------------------------ validation
@@ -267,85 +289,63 @@ void launch_validate(const int32_t *rp, const int32_t *ci, int64_t rows, int64_t
 
 // --------------------------------------------------------------- binning
 
-// For each distinct bin present in the wavefront: its lane mask.  Calls
-// `fn(bin, mask)` once per distinct bin (wave-uniform loop).
-template <typename Fn> DEVI void for_each_bin_in_wave(bool valid, int bin, Fn fn) {
-  uint64_t todo = __ballot(valid);
-  while (todo) {
-    const int leader = __ffsll(static_cast<long long>(todo)) - 1;
-    const int b = __shfl(bin, leader, WAVE);
-    const uint64_t mask = __ballot(valid && bin == b);
-    fn(b, mask);
-    todo &= ~mask;
+// A work-group takes RPT * 256 consecutive rows.  The bin histogram of every
+// work-group (k_row_stats), one exclusive scan per bin over the work-groups
+// (k_bin_scan) and a scatter (k_bin_scatter) give every bin its rows, in
+// work-group order; inside a work-group the order of a bin's rows is that of
+// the LDS counter and has no meaning.  Small products do all of it in one
+// work-group and one launch (k_rows_small): their launches cost more than
+// the work (four launches of about 4 us each and the gaps between them for
+// 2000 rows, against one of 8).
+constexpr int BIN_NT = 256;
+
+// What row i adds to the long-row planning sums (v: see kBlockStats).
+DEVI void long_sums(int64_t ui, int bin, const RowStatsArgs &a, int64_t (&v)[kBlockStats]) {
+  v[0] = v[0] > ui ? v[0] : ui;
+  if (bin != LONG_BIN) return;
+  const int64_t rmax = ui < a.ncols ? ui : a.ncols;
+  int64_t segp;
+  int32_t nseg, shift, npiece;
+  long_row_plan(ui, a.ncols, a.lp, segp, nseg, shift, npiece);
+  v[1] += ui;
+  v[2] += rmax;
+  v[3] += nseg;
+  v[4] += npiece;
+  if (nseg > 1) {
+    v[5] += ui;
+    v[6] += static_cast<int64_t>(nseg) * (npiece + 1);
+    v[8] += rmax;
+  } else if (ui <= kOneShot) {
+    v[5] += rmax;  // one-tile row: its result has a place of its own
+  } else if (rmax > a.long_slot) {
+    int64_t cap = a.long_slot;
+    while (cap < rmax) cap *= 2;
+    v[7] += cap;
   }
+  const int64_t segr = segp < a.ncols ? segp : a.ncols;
+  if (segr > a.l1cap - kLongTile) v[9] += segr * nseg;
+  const WinPlan wp = win_plan(ui, a.ncols, a.vbytes);
+  v[10] += wp.nitem;
+  v[11] += wp.nseg;
+  v[12] += wp.table;
+  v[13] += wp.partial;
+  v[14] += wp.dslots;
+  v[15] += wp.mode == WIN_NONE ? 1 : 0;
 }
 
-// Stage 1 result per row and the bin histogram of every wavefront.
-// hist layout: hist[bin * nwaves + wave] so that one exclusive scan yields,
-// for every (bin, wave), the start of that wave's rows in the bin list.
-// Also per-block sums that size the long-row work (reduced by k_summary).
-__global__ __launch_bounds__(256) void k_row_stats(RowStatsArgs a) {
-  __shared__ int32_t cnt[256 / WAVE][NBINS];
-  __shared__ int64_t red[256 / WAVE][kBlockStats];
+// Work-group totals of the planning sums; the result of sum k is returned to
+// thread k (< kBlockStats), others get 0.  Only the maximum is reduced where
+// no thread has a long row.  Contains barriers.
+template <int NT> DEVI int64_t block_stats(const int64_t (&v)[kBlockStats], bool any_long,
+                                           int64_t (&red)[NT / WAVE][kBlockStats]) {
   const int w = threadIdx.x / WAVE;
-  for (int b = lane(); b < NBINS; b += WAVE) cnt[w][b] = 0;
-  __syncthreads();
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const bool valid = i < a.m;
-  int64_t ui = 0;
-  int bin = 0;
-  if (valid) {
-    ui = a.P[a.arp[i + 1]] - a.P[a.arp[i]];
-    bin = bin_of(ui, a.be);
-    a.u[i] = ui;
-    a.h[i] = bin == LONG_BIN ? static_cast<int64_t>(a.long_slot) : ui;
-    if (ui == 0) a.rownnz[i] = 0;
-  }
-  for_each_bin_in_wave(valid, bin, [&](int b, uint64_t mask) {
-    if (lane() == 0) cnt[w][b] = __popcll(mask);
-  });
-  __syncthreads();
-  const int64_t gw = static_cast<int64_t>(blockIdx.x) * (256 / WAVE) + w;
-  if (gw < a.nwaves) {
-    for (int b = lane(); b < NBINS; b += WAVE) a.hist[b * a.nwaves + gw] = cnt[w][b];
-  }
-  // long-row planning sums
-  int64_t v[kBlockStats];
-#pragma unroll
-  for (int k = 0; k < kBlockStats; ++k) v[k] = 0;
-  v[0] = ui;
-  if (bin == LONG_BIN) {
-    const int64_t rmax = ui < a.ncols ? ui : a.ncols;
-    int64_t segp;
-    int32_t nseg, shift, npiece;
-    long_row_plan(ui, a.ncols, a.lp, segp, nseg, shift, npiece);
-    v[1] = ui;
-    v[2] = rmax;
-    v[3] = nseg;
-    v[4] = npiece;
-    if (nseg > 1) {
-      v[5] = ui;
-      v[6] = static_cast<int64_t>(nseg) * (npiece + 1);
-      v[8] = rmax;
-    } else if (ui <= kOneShot) {
-      v[5] = rmax;  // one-tile row: its result has a place of its own
-    } else if (rmax > a.long_slot) {
-      int64_t cap = a.long_slot;
-      while (cap < rmax) cap *= 2;
-      v[7] = cap;
-    }
-    const int64_t segr = segp < a.ncols ? segp : a.ncols;
-    if (segr > a.l1cap - kLongTile) v[9] = segr * nseg;
-    const WinPlan wp = win_plan(ui, a.ncols, a.vbytes);
-    v[10] = wp.nitem;
-    v[11] = wp.nseg;
-    v[12] = wp.table;
-    v[13] = wp.partial;
-    v[14] = wp.dslots;
-    v[15] = wp.mode == WIN_NONE ? 1 : 0;
-  }
+  const bool wl = __any(any_long);
 #pragma unroll
   for (int k = 0; k < kBlockStats; ++k) {
+    if (k > 0 && !wl) {
+      if (lane() == 0) red[w][k] = 0;
+      continue;
+    }
     int64_t x = v[k];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -355,117 +355,264 @@ __global__ __launch_bounds__(256) void k_row_stats(RowStatsArgs a) {
     if (lane() == 0) red[w][k] = x;
   }
   __syncthreads();
+  int64_t x = 0;
   if (threadIdx.x < kBlockStats) {
     const int k = threadIdx.x;
-    int64_t x = red[0][k];
-    for (int q = 1; q < 256 / WAVE; ++q) x = k == 0 ? (x > red[q][k] ? x : red[q][k]) : x + red[q][k];
-    a.bpart[static_cast<int64_t>(blockIdx.x) * kBlockStats + k] = x;
+    for (int q = 0; q < NT / WAVE; ++q)
+      x = k == 0 ? (x > red[q][k] ? x : red[q][k]) : x + red[q][k];
   }
+  return x;
 }
 
-void launch_row_stats(const RowStatsArgs &a, hipStream_t s) {
-  const int64_t nb = (a.m + 255) / 256;
-  if (nb == 0) return;
-  hipLaunchKernelGGL(k_row_stats, dim3(nb), dim3(256), 0, s, a);
-}
-
-// Stable scatter: rows keep ascending order inside each bin.
-__global__ __launch_bounds__(256) void k_bin_scatter(const int64_t *u, int64_t m, BinEdges be,
-                                                     const int64_t *hist_scan, int64_t nwaves,
-                                                     const int32_t *arp, int32_t *binlist,
-                                                     RowRec *recs) {
-  const int w = threadIdx.x / WAVE;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const bool valid = i < m;
-  const int64_t ui = valid ? u[i] : 0;
-  const int bin = valid ? bin_of(ui, be) : 0;
-  RowRec rec{static_cast<int32_t>(i), static_cast<int32_t>(ui < INT32_MAX ? ui : INT32_MAX), 0, 0};
-  if (valid) {
-    rec.e0 = arp[i];
-    rec.ne = arp[i + 1] - rec.e0;
+// The summary's words from the work-group's totals: bin_off[0..NBINS],
+// stats[0..], sum_u and sum_h; to the host's slot if there is one, else to
+// `sum`.  One wavefront writes it, so that its token follows its words.
+DEVI void write_summary(const int64_t *bin_off, const int64_t *stats, int64_t sum_u, int64_t sum_h,
+                        Summary *sum, HostSlot *slot, uint64_t token) {
+  constexpr int N = sizeof(Summary) / 8;
+  static_assert(sizeof(Summary) % 8 == 0 && N <= HostSlot::kWords && N <= WAVE,
+                "the summary must fit a slot");
+  static_assert(offsetof(Summary, sum_u) == 0 && offsetof(Summary, sum_h) == 8 &&
+                    offsetof(Summary, max_u) == 16 && offsetof(Summary, bin_off) == 24 &&
+                    offsetof(Summary, sum_u_long) == 24 + 8 * (NBINS + 1) &&
+                    offsetof(Summary, err) == 24 + 8 * (NBINS + 1) + 8 * (kBlockStats - 1),
+                "word order");
+  const int k = threadIdx.x;
+  if (k >= WAVE) return;
+  int64_t x = 0;  // the last word: no error
+  if (k == 0) x = sum_u;
+  else if (k == 1) x = sum_h;
+  else if (k == 2) x = stats[0];
+  else if (k < 3 + NBINS + 1) x = bin_off[k - 3];
+  else if (k < 3 + NBINS + 1 + kBlockStats - 1) x = stats[k - (3 + NBINS + 1) + 1];
+  if (!slot) {
+    if (k < N) reinterpret_cast<int64_t *>(sum)[k] = x;
+    return;
   }
-  const int64_t gw = static_cast<int64_t>(blockIdx.x) * (256 / WAVE) + w;
-  const uint64_t lt = (lane() == 0) ? 0ull : (~0ull >> (WAVE - lane()));
-  for_each_bin_in_wave(valid, bin, [&](int b, uint64_t mask) {
-    if (valid && bin == b) {
-      const int64_t pos = hist_scan[b * nwaves + gw] + __popcll(mask & lt);
-      binlist[pos] = static_cast<int32_t>(i);
-      recs[pos] = rec;
-    }
-  });
+  if (k < N)
+    __hip_atomic_store(&slot->word[k], static_cast<uint64_t>(x), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  if (k == 0)
+    __hip_atomic_store(&slot->token, token, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-void launch_bin_scatter(const int64_t *u, int64_t m, BinEdges be, const int64_t *hist_scan,
-                        int64_t nwaves, const int32_t *arp, int32_t *binlist, RowRec *recs,
-                        hipStream_t s) {
-  const int64_t nb = (m + 255) / 256;
-  if (nb == 0) return;
-  hipLaunchKernelGGL(k_bin_scatter, dim3(nb), dim3(256), 0, s, u, m, be, hist_scan, nwaves,
-                     arp, binlist, recs);
+DEVI int64_t tilde_size(int64_t ui, int bin, const RowStatsArgs &a) {
+  return bin == LONG_BIN ? static_cast<int64_t>(a.long_slot) : ui;
 }
 
-__global__ __launch_bounds__(256) void k_summary(const int64_t *P, int64_t nnzA,
-                                                 const int64_t *cto, int64_t m,
-                                                 const int64_t *hist_scan, int64_t nwaves,
-                                                 const int64_t *bpart, int64_t nblocks,
-                                                 Summary *sum) {
-  __shared__ int64_t red[256 / WAVE][kBlockStats];
+// Exclusive prefix of the bin totals cnt[0..NBINS) by the first wavefront
+// into off[0..NBINS]; the caller synchronizes.
+DEVI void bin_offsets(const int64_t *cnt, int64_t *off) {
+  if (threadIdx.x >= WAVE) return;
+  const int64_t c = lane() < NBINS ? cnt[lane()] : 0;
+  const int64_t inc = group_incl_sum<WAVE>(c);
+  if (lane() < NBINS) off[lane()] = inc - c;
+  if (lane() == NBINS - 1) off[NBINS] = inc;
+}
+
+// Stage 1 result per row, and per work-group its bin histogram, its part of
+// nnz(C~) and the planning sums (all laid out by kind, then work-group).
+template <int RPT>
+__global__ __launch_bounds__(BIN_NT) void k_row_stats(RowStatsArgs a) {
+  __shared__ int32_t cnt[NBINS];
+  __shared__ int64_t red[BIN_NT / WAVE][kBlockStats];
+  __shared__ int64_t sm[BIN_NT / WAVE + 1];
   const int t = threadIdx.x;
-  if (t == 0) {
-    sum->sum_u = P[nnzA];
-    sum->sum_h = cto[m];
-  }
-  if (t <= NBINS) sum->bin_off[t] = (t < NBINS) ? hist_scan[t * nwaves] : hist_scan[NBINS * nwaves];
-  int64_t v[kBlockStats];
-#pragma unroll
-  for (int k = 0; k < kBlockStats; ++k) v[k] = 0;
-  for (int64_t b = t; b < nblocks; b += 256) {
-#pragma unroll
-    for (int k = 0; k < kBlockStats; ++k) {
-      const int64_t x = bpart[b * kBlockStats + k];
-      v[k] = k == 0 ? (v[k] > x ? v[k] : x) : v[k] + x;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < kBlockStats; ++k) {
-    int64_t x = v[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const int64_t y = __shfl_xor(x, o, WAVE);
-      x = k == 0 ? (x > y ? x : y) : x + y;
-    }
-    if (lane() == 0) red[t / WAVE][k] = x;
-  }
+  if (t < NBINS) cnt[t] = 0;
   __syncthreads();
-  if (t < kBlockStats) {
-    int64_t x = red[0][t];
-    for (int q = 1; q < 256 / WAVE; ++q) x = t == 0 ? (x > red[q][t] ? x : red[q][t]) : x + red[q][t];
-    switch (t) {
-      case 0: sum->max_u = static_cast<unsigned long long>(x); break;
-      case 1: sum->sum_u_long = x; break;
-      case 2: sum->sum_r_long = x; break;
-      case 3: sum->n_items = x; break;
-      case 4: sum->n_pieces = x; break;
-      case 5: sum->sum_u_multi = x; break;
-      case 6: sum->n_split = x; break;
-      case 7: sum->pool_single = x; break;
-      case 8: sum->sum_r_multi = x; break;
-      case 9: sum->spill_bound = x; break;
-      case 10: sum->w_items = x; break;
-      case 11: sum->w_segs = x; break;
-      case 12: sum->w_table = x; break;
-      case 13: sum->w_partial = x; break;
-      case 14: sum->w_dslots = x; break;
-      case 15: sum->w_none = x; break;
+  int64_t v[kBlockStats] = {};
+  int64_t h = 0;
+  bool any_long = false;
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    const int64_t i = (static_cast<int64_t>(blockIdx.x) * RPT + r) * BIN_NT + t;
+    if (i >= a.m) continue;
+    const int64_t ui = a.P[a.arp[i + 1]] - a.P[a.arp[i]];
+    const int bin = bin_of(ui, a.be);
+    a.u[i] = ui;
+    if (ui == 0) a.rownnz[i] = 0;
+    h += tilde_size(ui, bin, a);
+    any_long |= bin == LONG_BIN;
+    atomicAdd(&cnt[bin], 1);
+    long_sums(ui, bin, a, v);
+  }
+  int64_t hs;
+  block_excl_sum<BIN_NT>(h, sm, hs);
+  const int64_t st = block_stats<BIN_NT>(v, any_long, red);  // (its barrier orders cnt too)
+  const int64_t nb = gridDim.x, b = blockIdx.x;
+  if (t < NBINS) a.hist[t * nb + b] = cnt[t];
+  if (t == 0) a.hpart[b] = hs;
+  if (t < kBlockStats) a.bpart[t * nb + b] = st;
+}
+
+// One work-group per bin (exclusive scan of its counts over the row
+// work-groups, total to tot[bin]), one for nnz(C~), one per planning sum.
+__global__ __launch_bounds__(BIN_NT) void k_bin_scan(int32_t *hist, int64_t *hpart,
+                                                     const int64_t *bpart, int64_t nb,
+                                                     int64_t *tot) {
+  __shared__ int64_t sm[BIN_NT / WAVE + 1];
+  const int c = blockIdx.x;
+  const int t = threadIdx.x;
+  int64_t carry = 0;
+  for (int64_t b0 = 0; b0 < nb; b0 += BIN_NT) {
+    const int64_t b = b0 + t;
+    int64_t x = 0, all;
+    if (c < NBINS)
+      x = b < nb ? hist[c * nb + b] : 0;
+    else if (c == NBINS)
+      x = b < nb ? hpart[b] : 0;
+    else
+      x = b < nb ? bpart[(c - NBINS - 1) * nb + b] : 0;
+    if (c == NBINS + 1) {  // the largest u
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const int64_t y = __shfl_xor(x, o, WAVE);
+        x = x > y ? x : y;
+      }
+      if (lane() == 0) sm[t / WAVE] = x;
+      __syncthreads();
+      for (int w = 0; w < BIN_NT / WAVE; ++w) carry = carry > sm[w] ? carry : sm[w];
+      __syncthreads();
+      continue;
     }
+    const int64_t ex = carry + block_excl_sum<BIN_NT>(x, sm, all);
+    if (c < NBINS) {
+      if (b < nb) hist[c * nb + b] = static_cast<int32_t>(ex);
+    } else if (c == NBINS) {
+      if (b < nb) hpart[b] = ex;
+    }
+    carry += all;
+  }
+  if (t == 0) tot[c] = carry;
+}
+
+// Rows into their bins, C~ offsets; the first work-group writes the summary.
+template <int RPT>
+__global__ __launch_bounds__(BIN_NT) void k_bin_scatter(RowStatsArgs a) {
+  __shared__ int64_t off[NBINS + 1];
+  __shared__ int32_t cnt[NBINS];
+  __shared__ int64_t sm[BIN_NT / WAVE + 1];
+  const int t = threadIdx.x;
+  const int64_t nb = gridDim.x, b = blockIdx.x;
+  bin_offsets(a.tot, off);
+  if (t < NBINS) cnt[t] = a.hist[t * nb + b];
+  int64_t ho = a.hpart[b];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    const int64_t i = (b * RPT + r) * BIN_NT + t;
+    const bool valid = i < a.m;
+    const int64_t ui = valid ? a.u[i] : 0;
+    const int bin = bin_of(ui, a.be);
+    int64_t all;
+    const int64_t ex = block_excl_sum<BIN_NT>(valid ? tilde_size(ui, bin, a) : 0, sm, all);
+    if (valid) {
+      a.cto[i] = ho + ex;
+      const int32_t e0 = a.arp[i];
+      const RowRec rec{static_cast<int32_t>(i),
+                       static_cast<int32_t>(ui < INT32_MAX ? ui : INT32_MAX), e0,
+                       a.arp[i + 1] - e0};
+      const int64_t pos = off[bin] + atomicAdd(&cnt[bin], 1);
+      a.binlist[pos] = rec.row;
+      a.recs[pos] = rec;
+    }
+    ho += all;
+  }
+  if (b == 0) {
+    const int64_t sum_h = a.tot[NBINS];
+    if (t == 0) a.cto[a.m] = sum_h;
+    write_summary(off, a.tot + NBINS + 1, a.P[a.nnz], sum_h, a.sum, a.slot, a.token);
   }
 }
 
-void launch_summary(const int64_t *P, int64_t nnzA, const int64_t *cto, int64_t m,
-                    const int64_t *hist_scan, int64_t nwaves, const int64_t *bpart,
-                    int64_t nblocks, Summary *sum, hipStream_t s) {
-  hipLaunchKernelGGL(k_summary, dim3(1), dim3(256), 0, s, P, nnzA, cto, m, hist_scan, nwaves,
-                     bpart, nblocks, sum);
+// Everything after stage 1's scan for up to ROWS_SMALL rows.
+constexpr int SMALL_NT = 1024;
+constexpr int SMALL_RPT = 4;
+constexpr int64_t ROWS_SMALL = SMALL_NT * SMALL_RPT;
+
+__global__ __launch_bounds__(SMALL_NT) void k_rows_small(RowStatsArgs a) {
+  __shared__ int64_t off[NBINS + 1], tot[NBINS], stats[kBlockStats];
+  __shared__ int32_t cnt[NBINS], cur[NBINS];
+  __shared__ int64_t red[SMALL_NT / WAVE][kBlockStats];
+  __shared__ int64_t sm[SMALL_NT / WAVE + 1];
+  const int t = threadIdx.x;
+  if (t < NBINS) cnt[t] = cur[t] = 0;
+  __syncthreads();
+  int64_t v[kBlockStats] = {};
+  bool any_long = false;
+  int32_t e0[SMALL_RPT], ne[SMALL_RPT];
+  int64_t u[SMALL_RPT];
+  int bin[SMALL_RPT];
+#pragma unroll
+  for (int r = 0; r < SMALL_RPT; ++r) {
+    const int64_t i = r * SMALL_NT + t;
+    u[r] = 0;
+    bin[r] = -1;
+    if (i >= a.m) continue;
+    e0[r] = a.arp[i];
+    ne[r] = a.arp[i + 1] - e0[r];
+    u[r] = a.P[e0[r] + ne[r]] - a.P[e0[r]];
+    bin[r] = bin_of(u[r], a.be);
+    a.u[i] = u[r];
+    if (u[r] == 0) a.rownnz[i] = 0;
+    any_long |= bin[r] == LONG_BIN;
+    atomicAdd(&cnt[bin[r]], 1);
+    long_sums(u[r], bin[r], a, v);
+  }
+  const int64_t st = block_stats<SMALL_NT>(v, any_long, red);  // (its barrier orders cnt too)
+  if (t < kBlockStats) stats[t] = st;
+  if (t < NBINS) tot[t] = cnt[t];
+  __syncthreads();
+  bin_offsets(tot, off);
+  __syncthreads();
+  int64_t ho = 0;
+#pragma unroll
+  for (int r = 0; r < SMALL_RPT; ++r) {
+    const int64_t i = r * SMALL_NT + t;
+    int64_t all;
+    if (r * SMALL_NT >= a.m) break;  // uniform
+    const int64_t ex =
+        block_excl_sum<SMALL_NT>(bin[r] >= 0 ? tilde_size(u[r], bin[r], a) : 0, sm, all);
+    if (bin[r] >= 0) {
+      a.cto[i] = ho + ex;
+      const RowRec rec{static_cast<int32_t>(i),
+                       static_cast<int32_t>(u[r] < INT32_MAX ? u[r] : INT32_MAX), e0[r], ne[r]};
+      const int64_t pos = off[bin[r]] + atomicAdd(&cur[bin[r]], 1);
+      a.binlist[pos] = rec.row;
+      a.recs[pos] = rec;
+    }
+    ho += all;
+  }
+  if (t == 0) a.cto[a.m] = ho;
+  write_summary(off, stats, a.P[a.nnz], ho, a.sum, a.slot, a.token);
+}
+
+// rows per thread of the binning kernels: enough that a bin's scan over the
+// work-groups stays short (1024 of them at 262144 rows; four rows per thread
+// beyond)
+int64_t bin_blocks(int64_t m) {
+  const int rpt = m > 262144 ? 4 : 1;
+  const int64_t nb = (m + BIN_NT * rpt - 1) / (BIN_NT * rpt);
+  return nb > 0 ? nb : 1;
+}
+
+void launch_binning(const RowStatsArgs &a, hipStream_t s) {
+  if (a.m <= ROWS_SMALL) {
+    hipLaunchKernelGGL(k_rows_small, dim3(1), dim3(SMALL_NT), 0, s, a);
+    return;
+  }
+  const int64_t nb = bin_blocks(a.m);
+  if (a.m > 262144)
+    hipLaunchKernelGGL(k_row_stats<4>, dim3(nb), dim3(BIN_NT), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_row_stats<1>, dim3(nb), dim3(BIN_NT), 0, s, a);
+  hipLaunchKernelGGL(k_bin_scan, dim3(NBINS + 1 + kBlockStats), dim3(BIN_NT), 0, s, a.hist,
+                     a.hpart, a.bpart, nb, a.tot);
+  if (a.m > 262144)
+    hipLaunchKernelGGL(k_bin_scatter<4>, dim3(nb), dim3(BIN_NT), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_bin_scatter<1>, dim3(nb), dim3(BIN_NT), 0, s, a);
 }
 
 __global__ void k_fill_i64(int64_t *p, int64_t n, int64_t v) {
@@ -501,16 +648,44 @@ void launch_set_pool(Pool *dst, Pool value, hipStream_t s) {
   hipLaunchKernelGGL(k_set_pool, dim3(1), dim3(1), 0, s, dst, value);
 }
 
-__global__ void k_status(const int64_t *rowoff, int64_t m, const Pool *pool, ComputeStatus *st) {
-  st->nnz_c = rowoff[m];
-  st->fail_count = pool->fail_count;
-  st->fail2 = pool->fail2;
-  st->pool_used = pool->used;
-}
+// The status of compute, by one thread: to the host's slot if there is one
+// (the words, then the token that announces them), else to `st`.
+struct StatusEnd {
+  const Pool *pool;
+  ComputeStatus *st;
+  HostSlot *slot;
+  uint64_t token;
+  DEVI void operator()(int64_t nnz) const {
+    ComputeStatus v;
+    v.nnz_c = nnz;
+    v.fail_count = pool->fail_count;
+    v.fail2 = pool->fail2;
+    v.pool_used = pool->used;
+    if (!slot) {
+      *st = v;
+      return;
+    }
+    constexpr int N = sizeof(ComputeStatus) / 8;
+    uint64_t w[N];
+    __builtin_memcpy(w, &v, sizeof(v));
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      __hip_atomic_store(&slot->word[k], w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&slot->token, token, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+};
+
+__global__ void k_status(const int64_t *rowoff, int64_t m, StatusEnd end) { end(rowoff[m]); }
 
 void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, ComputeStatus *st,
-                   hipStream_t s) {
-  hipLaunchKernelGGL(k_status, dim3(1), dim3(1), 0, s, rowoff, m, pool, st);
+                   HostSlot *slot, uint64_t token, hipStream_t s) {
+  hipLaunchKernelGGL(k_status, dim3(1), dim3(1), 0, s, rowoff, m, StatusEnd{pool, st, slot, token});
+}
+
+void scan_rows_status(const int64_t *v, int64_t n, int64_t *out, int64_t *part, const Pool *pool,
+                      ComputeStatus *st, HostSlot *slot, uint64_t token, hipStream_t s) {
+  const I64Fn f{v};
+  scan_with(f, f, f, StatusEnd{pool, st, slot, token}, n, out, part, s);
 }
 
 }  // namespace spg

@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -146,6 +147,56 @@ void *pinned_staging() {
   return buf;
 }
 
+// Records that kernels write straight into pinned host memory, two slots per
+// thread (the summary of analyze, the status of compute): the host waits for
+// the token of its request instead of for a copy command and the stream.
+struct HostSlots {
+  HostSlot slot[2];
+  uint64_t next;  // last token given out
+};
+
+HostSlots *host_slots() {
+  thread_local HostSlots *hs = nullptr;
+  if (!hs) {
+    void *p = nullptr;
+    if (hipHostMalloc(&p, sizeof(HostSlots), hipHostMallocMapped | hipHostMallocPortable |
+                                                 hipHostMallocCoherent) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    std::memset(p, 0, sizeof(HostSlots));
+    hs = static_cast<HostSlots *>(p);
+  }
+  return hs;
+}
+
+// A slot (nullptr if there is none: the kernels then write to device memory,
+// read back by read_small) and the token that will announce its record.
+HostSlot *take_slot(int which, uint64_t *token) {
+  HostSlots *hs = host_slots();
+  if (!hs) return nullptr;
+  *token = ++hs->next;
+  return &hs->slot[which];
+}
+
+// Waits for the record; a wait beyond a few milliseconds is left to the
+// runtime, which also reports errors of the stream.
+hipError_t wait_slot(HostSlot *slot, uint64_t token, void *dst, size_t bytes, hipStream_t s) {
+  const auto arrived = [&] { return __atomic_load_n(&slot->token, __ATOMIC_ACQUIRE) == token; };
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int spin = 0; !arrived(); ++spin) {
+    __builtin_ia32_pause();
+    if ((spin & 255) == 255 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(5)) {
+      const hipError_t e = hipStreamSynchronize(s);
+      if (e != hipSuccess) return e;
+      if (!arrived()) return hipErrorUnknown;
+      break;
+    }
+  }
+  std::memcpy(dst, slot->word, bytes);
+  return hipSuccess;
+}
+
 // Device -> host copy of a small record through the pinned staging area;
 // synchronizes the stream.
 hipError_t read_small(void *dst, const void *src, size_t bytes, hipStream_t s) {
@@ -176,18 +227,15 @@ struct spgemm_plan_s {
   // analyze scratch (one allocation)
   void *ws = nullptr;
   size_t ws_bytes = 0;
-  int64_t *P = nullptr, *u = nullptr, *h = nullptr, *cto = nullptr, *rownnz = nullptr,
-          *rowoff = nullptr, *hist_scan = nullptr, *part = nullptr;
-  int32_t *hist = nullptr, *binlist = nullptr, *bst = nullptr;
+  int64_t *P = nullptr, *u = nullptr, *cto = nullptr, *rownnz = nullptr, *rowoff = nullptr,
+          *part = nullptr;
+  int32_t *binlist = nullptr, *bst = nullptr;
   RowRec *recs = nullptr;
-  int64_t *bpart = nullptr;
-  int64_t nblocks = 0;
   LongParams lp{};
   int l1cap = 0;
   Summary *dsum = nullptr;
   ComputeStatus *dstat = nullptr;
   Pool *dpool = nullptr;
-  int64_t nwaves = 0;
 
   // host mirrors
   Summary *hsum = nullptr;
@@ -445,8 +493,6 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   p->stream = s;
 
   const int64_t m = p->m;
-  p->nwaves = (m + 63) / 64;  // one histogram column per 64-row wavefront
-  p->nblocks = (m + 255) / 256;
   p->l1cap = o.l1_cap ? o.l1_cap : long_l1cap_default(dtype_bytes(p->dtype));
   // defaults: a row of up to kWaveTile products is one item; longer rows are
   // cut into segments of kWaveTile / 2 (one wavefront each, at twice the
@@ -457,22 +503,22 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   p->lp.cb = kWaveTile / 4;
   p->lp.minw_shift = 4;
   p->lp.maxw_shift = 30;
-  const int64_t nh = static_cast<int64_t>(NBINS) * p->nwaves;
-  int64_t partn = scan_part_len(std::max<int64_t>({p->nnzA, m, nh, 1}));
+  const int64_t nblocks = bin_blocks(m);
+  int64_t partn = scan_part_len(std::max<int64_t>({p->nnzA, m, 1}));
   Layout L;
   const size_t oP = L.add<int64_t>(p->nnzA + 1);
   const size_t ou = L.add<int64_t>(m);
-  const size_t oh = L.add<int64_t>(m);
   const size_t octo = L.add<int64_t>(m + 1);
   const size_t onnz = L.add<int64_t>(m);
   const size_t ooff = L.add<int64_t>(m + 1);
-  const size_t ohs = L.add<int64_t>(nh + 1);
   const size_t opart = L.add<int64_t>(partn);
-  const size_t ohist = L.add<int32_t>(nh);
+  const size_t ohist = L.add<int32_t>(NBINS * nblocks);
+  const size_t ohp = L.add<int64_t>(nblocks);
   const size_t obl = L.add<int32_t>(m);
   const size_t orec = L.add<RowRec>(m);
   const size_t obst = L.add<int32_t>(p->nnzA);
-  const size_t obp = L.add<int64_t>(p->nblocks * kBlockStats);
+  const size_t obp = L.add<int64_t>(nblocks * kBlockStats);
+  const size_t otot = L.add<int64_t>(NBINS + 1 + kBlockStats);
   const size_t osum = L.add<Summary>(1);
   const size_t ostat = L.add<ComputeStatus>(1);
   const size_t opool = L.add<Pool>(1);
@@ -484,17 +530,13 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   }
   p->P = at<int64_t>(p->ws, oP);
   p->u = at<int64_t>(p->ws, ou);
-  p->h = at<int64_t>(p->ws, oh);
   p->cto = at<int64_t>(p->ws, octo);
   p->rownnz = at<int64_t>(p->ws, onnz);
   p->rowoff = at<int64_t>(p->ws, ooff);
-  p->hist_scan = at<int64_t>(p->ws, ohs);
   p->part = at<int64_t>(p->ws, opart);
-  p->hist = at<int32_t>(p->ws, ohist);
   p->binlist = at<int32_t>(p->ws, obl);
   p->recs = at<RowRec>(p->ws, orec);
   p->bst = at<int32_t>(p->ws, obst);
-  p->bpart = at<int64_t>(p->ws, obp);
   p->dsum = at<Summary>(p->ws, osum);
   p->dstat = at<ComputeStatus>(p->ws, ostat);
   p->dpool = at<Pool>(p->ws, opool);
@@ -516,8 +558,8 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
     p->events = true;
   }
 
-  launch_zero(p->dsum, sizeof(Summary), s);
   if (o.validate) {
+    launch_zero(p->dsum, sizeof(Summary), s);
     // checked before any kernel indexes with the inputs
     launch_validate(A->row_ptr, A->col_idx, A->rows, A->cols, A->nnz, p->dsum, s);
     launch_validate(B->row_ptr, B->col_idx, B->rows, B->cols, B->nnz, p->dsum, s);
@@ -535,36 +577,40 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   // stage 1 (Algorithm 2): P = exclusive scan of nnz(b_j*) over A's entries,
   // so u_i = P[arp[i+1]] - P[arp[i]].
   scan_row_lengths(A->col_idx, B->row_ptr, p->nnzA, p->P, p->bst, p->part, s);
+  stage_end(p, SPGEMM_T_UPPER, s);
+  // stage 2 (Algorithm 3): u_i, bin lists, C~ offsets, summary
+  uint64_t token = 0;
+  HostSlot *slot = take_slot(0, &token);
+  stage_begin(p, SPGEMM_T_BIN, s);
   {
     RowStatsArgs ra;
     ra.arp = A->row_ptr;
     ra.P = p->P;
     ra.m = m;
     ra.ncols = p->n;
+    ra.nnz = p->nnzA;
     ra.be = p->be;
     ra.long_slot = o.long_slot;
     ra.l1cap = p->l1cap;
     ra.vbytes = dtype_bytes(p->dtype);
     ra.lp = p->lp;
     ra.u = p->u;
-    ra.h = p->h;
-    ra.hist = p->hist;
-    ra.nwaves = p->nwaves;
+    ra.cto = p->cto;
     ra.rownnz = p->rownnz;
-    ra.bpart = p->bpart;
-    launch_row_stats(ra, s);
+    ra.binlist = p->binlist;
+    ra.recs = p->recs;
+    ra.hist = at<int32_t>(p->ws, ohist);
+    ra.hpart = at<int64_t>(p->ws, ohp);
+    ra.bpart = at<int64_t>(p->ws, obp);
+    ra.tot = at<int64_t>(p->ws, otot);
+    ra.sum = p->dsum;
+    ra.slot = slot;
+    ra.token = token;
+    launch_binning(ra, s);
   }
-  stage_end(p, SPGEMM_T_UPPER, s);
-  // stage 2 (Algorithm 3): C~ offsets and the stable bin lists
-  stage_begin(p, SPGEMM_T_BIN, s);
-  scan_i64(p->h, m, p->cto, p->part, s);
-  scan_i32(p->hist, nh, p->hist_scan, p->part, s);
-  launch_bin_scatter(p->u, m, p->be, p->hist_scan, p->nwaves, A->row_ptr, p->binlist,
-                     p->recs, s);
-  launch_summary(p->P, p->nnzA, p->cto, m, p->hist_scan, p->nwaves, p->bpart, p->nblocks,
-                 p->dsum, s);
   stage_end(p, SPGEMM_T_BIN, s);
-  hipError_t e = read_small(p->hsum, p->dsum, sizeof(Summary), s);
+  hipError_t e = slot ? wait_slot(slot, token, p->hsum, sizeof(Summary), s)
+                      : read_small(p->hsum, p->dsum, sizeof(Summary), s);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) {
     destroy_plan(p);
@@ -593,7 +639,8 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   I.long_items = S.n_items;
   I.bytes_scratch = held_bytes(p);
   for (int st : {SPGEMM_T_UPPER, SPGEMM_T_BIN})
-    if (timed(p, st)) (void)hipEventElapsedTime(&I.stage_ms[st], p->ev[2 * st], p->ev[2 * st + 1]);
+    if (timed(p, st) && hipEventSynchronize(p->ev[2 * st + 1]) == hipSuccess)
+      (void)hipEventElapsedTime(&I.stage_ms[st], p->ev[2 * st], p->ev[2 * st + 1]);
   if (info) *info = I;
   *plan = p;
   return SPGEMM_OK;
@@ -737,23 +784,47 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   // on the caller's stream: forked here, once C~ exists (the second stream
   // waits for what the caller's stream holds now, not for the long-row
   // kernels queued next), queued after the first long-row kernels so that
-  // the host gets those going first, joined before the row sizes are scanned
-  const hipStream_t es = fork_aux(p, s) ? p->aux : s;
+  // the host gets those going first, joined before the row sizes are scanned.
+  // Without long rows there is nothing to run beside: the fork and the join
+  // would only cost their events (about 10 us a call)
+  const hipStream_t es = nlong > 0 && fork_aux(p, s) ? p->aux : s;
   bool short_done = false;
   auto launch_short_rows = [&]() -> int {
     if (short_done) return SPGEMM_OK;
     short_done = true;
-    // ---- bin group 4: the four range bins, the largest first: its kernel
-    // runs long enough for the host to queue the short ones behind it
+    // one launch per power-of-two capacity; a capacity with few rows joins
+    // the next larger one up to eight times its size (its rows then sort
+    // with idle lanes, which is cheaper than a launch of its own)
+    constexpr int64_t kFewRows = 2048;
+    struct Launch {
+      int64_t r0, r1;
+      int cap;
+    };
+    auto launch_bins = [&](std::vector<Launch> &v) -> int {
+      for (size_t i = 0; i + 1 < v.size(); ++i) {
+        if (v[i].r0 == v[i].r1) continue;
+        size_t j = i + 1;  // the next capacity with rows
+        while (j < v.size() && v[j].r0 == v[j].r1) ++j;
+        if (j == v.size() || v[j].cap > 8 * v[i].cap || v[i].r1 - v[i].r0 > kFewRows) continue;
+        v[j].r0 = v[i].r0;  // bins are stored in order
+        v[i].r1 = v[i].r0;
+      }
+      // the largest first: its kernel runs long enough for the host to queue
+      // the short ones behind it
+      for (size_t i = v.size(); i-- > 0;)
+        if (launch_esc<T>(ea, p->recs + v[i].r0, v[i].r1 - v[i].r0, v[i].cap, p->n, es))
+          return fail(SPGEMM_EINVAL, "no ESC kernel for this capacity");
+      return SPGEMM_OK;
+    };
+    // ---- bin group 4: the four range bins
     stage_begin(p, SPGEMM_T_MEDIUM, es);
-    for (int b = 36; b >= 33; --b) {
-      const int cap = static_cast<int>(next_pow2(p->be.e[b - 32]));
-      const int64_t r0 = S.bin_off[b], r1 = S.bin_off[b + 1];
-      if (launch_esc<T>(ea, p->recs + r0, r1 - r0, cap, p->n, es))
-        return fail(SPGEMM_EINVAL, "no ESC kernel for this capacity");
-    }
+    std::vector<Launch> v;
+    int lrc;
+    for (int b = 33; b <= 36; ++b)
+      v.push_back({S.bin_off[b], S.bin_off[b + 1], static_cast<int>(next_pow2(p->be.e[b - 32]))});
+    if ((lrc = launch_bins(v)) != SPGEMM_OK) return lrc;
     stage_end(p, SPGEMM_T_MEDIUM, es);
-    // ---- stage 3, bin groups 2-3: one launch per power-of-two capacity
+    // ---- stage 3, bin groups 2-3
     stage_begin(p, SPGEMM_T_TINY, es);
     if (p->opt.tiny_heap) {
       // bin 1 through the wavefront kernel, bins 2..edge[0] one kernel each
@@ -763,15 +834,14 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
         if (launch_heap<T>(ea, p->binlist + S.bin_off[b], S.bin_off[b + 1] - S.bin_off[b], b, es))
           return fail(SPGEMM_EINVAL, "no heap kernel for this size");
     } else {
-      int b = 1;
-      while (b <= p->be.e[0]) {
+      v.clear();
+      for (int b = 1; b <= p->be.e[0];) {
         const int cap = static_cast<int>(next_pow2(b));
         const int hi = std::min<int>(cap, p->be.e[0]);
-        const int64_t r0 = S.bin_off[b], r1 = S.bin_off[hi + 1];
-        if (launch_esc<T>(ea, p->recs + r0, r1 - r0, cap, p->n, es))
-          return fail(SPGEMM_EINVAL, "no ESC kernel for this capacity");
+        v.push_back({S.bin_off[b], S.bin_off[hi + 1], cap});
         b = hi + 1;
       }
+      if ((lrc = launch_bins(v)) != SPGEMM_OK) return lrc;
     }
     stage_end(p, SPGEMM_T_TINY, es);
     return SPGEMM_OK;
@@ -825,11 +895,23 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     launch_set_pool(p->dpool, *p->hpool, s);
     return SPGEMM_OK;
   };
-  auto read_status = [&]() -> int {
-    launch_status(p->rowoff, m, p->dpool, p->dstat, s);
-    HIP_TRY(read_small(p->hstat, p->dstat, sizeof(ComputeStatus), s));
+  uint64_t token = 0;
+  HostSlot *slot = nullptr;
+  auto wait_status = [&]() -> int {
+    HIP_TRY(slot ? wait_slot(slot, token, p->hstat, sizeof(ComputeStatus), s)
+                 : read_small(p->hstat, p->dstat, sizeof(ComputeStatus), s));
     HIP_TRY(hipGetLastError());
     return SPGEMM_OK;
+  };
+  auto read_status = [&]() -> int {
+    slot = take_slot(1, &token);
+    launch_status(p->rowoff, m, p->dpool, p->dstat, slot, token, s);
+    return wait_status();
+  };
+  // row pointers of C, and the status with their total
+  auto scan_rows = [&]() {
+    slot = take_slot(1, &token);
+    scan_rows_status(p->rownnz, m, p->rowoff, p->part, p->dpool, p->dstat, slot, token, s);
   };
   auto finish_long = [&]() {
     // long-row sizes from their pieces
@@ -918,7 +1000,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   if ((rc = launch_short_rows()) != SPGEMM_OK) return rc;  // no long rows
   if (es != s) join_aux(p, s);
   stage_begin(p, SPGEMM_T_SCAN, s);
-  scan_i64(p->rownnz, m, p->rowoff, p->part, s);
+  scan_rows();
   stage_end(p, SPGEMM_T_SCAN, s);
   // C's row pointers have a known size: allocated while the GPU is busy,
   // released again if anything below fails
@@ -933,7 +1015,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     unsigned int *f2 = fail2_a, *f2_other = fail2_b;
     unsigned int *fl = fail_a, *fl_other = fail_b;
     for (;;) {
-      if ((rc = read_status()) != SPGEMM_OK) return rc;
+      if ((rc = wait_status()) != SPGEMM_OK) return rc;
       const unsigned int nf1 = legacy ? p->hstat->fail_count : 0u;
       const unsigned int nf2 = legacy ? p->hstat->fail2 : 0u;
       if (nf1 == 0 && nf2 == 0) break;
@@ -967,7 +1049,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
         la.work = nullptr;
       }
       finish_long();
-      scan_i64(p->rownnz, m, p->rowoff, p->part, s);
+      scan_rows();
     }
   }
   const int64_t nnz = p->hstat->nnz_c;

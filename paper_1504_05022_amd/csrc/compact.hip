@@ -11,16 +11,18 @@
 namespace spg {
 
 // Row pointers of C, and the short rows (u <= long_min) copied from C~:
-// CP_ROWS consecutive rows per wavefront.
-template <typename T>
+// R consecutive rows per wavefront, fewer where m is small, so that the copy
+// still fills the chip (2000 rows of 100 entries: 63 wavefronts of 32 rows
+// took 21.5 us, 1000 of 2 take 6).
+template <typename T, int R>
 __global__ __launch_bounds__(CP_NT) void k_compact_rows(CompactArgs<T> a, int64_t m) {
-  __shared__ CopyTable<CP_ROWS> tabs[CP_NT / WAVE];
+  __shared__ CopyTable<R> tabs[CP_NT / WAVE];
   const int64_t w = (static_cast<int64_t>(blockIdx.x) * CP_NT + threadIdx.x) / WAVE;
-  const int64_t r0 = w * CP_ROWS;
+  const int64_t r0 = w * R;
   if (r0 >= m) return;  // uniform across the wavefront
   const int64_t r = r0 + lane();
   int64_t n = 0, src = 0, o = 0;
-  if (lane() < CP_ROWS && r < m) {
+  if (lane() < R && r < m) {
     o = a.rowoff[r];
     const int64_t o1 = a.rowoff[r + 1];
     a.c_rp[r] = static_cast<int32_t>(o);
@@ -30,8 +32,8 @@ __global__ __launch_bounds__(CP_NT) void k_compact_rows(CompactArgs<T> a, int64_
       src = a.cto[r];
     }
   }
-  wave_stream_copy<T, CP_ROWS>(n, a.ct_col + src, a.ct_val + src, o, a.c_col, a.c_val,
-                               tabs[threadIdx.x / WAVE]);
+  wave_stream_copy<T, R>(n, a.ct_col + src, a.ct_val + src, o, a.c_col, a.c_val,
+                         tabs[threadIdx.x / WAVE]);
 }
 
 // Long rows, piece by piece: one wavefront per piece (pieces hold a few
@@ -77,9 +79,16 @@ __global__ __launch_bounds__(CP_NT) void k_compact_pieces(CompactArgs<T> a, int6
 template <typename T>
 void launch_compact(const CompactArgs<T> &a, int64_t m, int64_t npieces, hipStream_t s) {
   if (m <= 0) return;
-  const int64_t rwaves = (m + CP_ROWS - 1) / CP_ROWS;
-  hipLaunchKernelGGL((k_compact_rows<T>), dim3((rwaves * WAVE + CP_NT - 1) / CP_NT), dim3(CP_NT),
-                     0, s, a, m);
+  const auto grid = [&](int64_t r) {
+    return dim3(static_cast<unsigned int>(((m + r - 1) / r * WAVE + CP_NT - 1) / CP_NT));
+  };
+  // four wavefronts per SIMD or more
+  if (m >= 4096 * CP_ROWS)
+    hipLaunchKernelGGL((k_compact_rows<T, CP_ROWS>), grid(CP_ROWS), dim3(CP_NT), 0, s, a, m);
+  else if (m >= 4096 * 8)
+    hipLaunchKernelGGL((k_compact_rows<T, 8>), grid(8), dim3(CP_NT), 0, s, a, m);
+  else
+    hipLaunchKernelGGL((k_compact_rows<T, 2>), grid(2), dim3(CP_NT), 0, s, a, m);
   if (npieces > 0)
     hipLaunchKernelGGL((k_compact_pieces<T>), dim3((npieces * WAVE + CP_NT - 1) / CP_NT),
                        dim3(CP_NT), 0, s, a, npieces);

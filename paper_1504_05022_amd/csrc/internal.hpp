@@ -331,36 +331,46 @@ struct alignas(16) RowRec {
 void launch_validate(const int32_t *rp, const int32_t *ci, int64_t rows, int64_t cols,
                      int64_t nnz, Summary *sum, hipStream_t s);
 
-// Stage 1 per row: u_i from the scanned row lengths, C~ row sizes, bin
-// histograms per wavefront; zeroes nnz of empty rows.
+// A slot of pinned host memory that a kernel fills: the words of a record,
+// then (released at system scope) the token the host waits for.  Saves the
+// copy command and the wait for it to end.
+struct HostSlot {
+  static constexpr int kWords = 62;
+  uint64_t word[kWords];
+  uint64_t token;
+  uint64_t pad;
+};
+
+// Stages 1 (after the scan of the row lengths) and 2: u_i, the bin lists, C~
+// offsets and the summary (to `slot` with `token`, or to `sum` if there is no
+// slot); zeroes nnz of empty rows.
 struct RowStatsArgs {
   const int32_t *arp;
   const int64_t *P;
-  int64_t m, ncols;
+  int64_t m, ncols, nnz;
   BinEdges be;
   int32_t long_slot;
   int32_t l1cap;
   int32_t vbytes;  // value size (window plan)
   LongParams lp;
-  int64_t *u, *h;
+  int64_t *u, *cto, *rownnz;
+  int32_t *binlist;
+  RowRec *recs;
+  // per-work-group partial results: NBINS, 1 and kBlockStats per work-group;
+  // tot: their totals
   int32_t *hist;
-  int64_t nwaves;
-  int64_t *rownnz;
-  int64_t *bpart;  // per-block partial sums, kBlockStats per block
+  int64_t *hpart, *bpart, *tot;
+  Summary *sum;
+  HostSlot *slot;
+  uint64_t token;
 };
-// per block: max u, sum u (long), sum min(u,n) (long), items, pieces,
+// max u, sum u (long), sum min(u,n) (long), items, pieces,
 // sum u (multi), split entries, pool (single), sum min(u,n) (multi), spill,
 // then the window plan: items, segments, table entries, partial entries,
 // dense partial rows, rows without a window plan
 constexpr int kBlockStats = 16;
-void launch_row_stats(const RowStatsArgs &a, hipStream_t s);
-// Stable scatter of the rows into their bins.
-void launch_bin_scatter(const int64_t *u, int64_t m, BinEdges be, const int64_t *hist_scan,
-                        int64_t nwaves, const int32_t *arp, int32_t *binlist, RowRec *recs,
-                        hipStream_t s);
-void launch_summary(const int64_t *P, int64_t nnzA, const int64_t *cto, int64_t m,
-                    const int64_t *hist_scan, int64_t nwaves, const int64_t *bpart,
-                    int64_t nblocks, Summary *sum, hipStream_t s);
+int64_t bin_blocks(int64_t m);
+void launch_binning(const RowStatsArgs &a, hipStream_t s);
 
 // ------------------------------------------------------------- compute
 
@@ -545,8 +555,12 @@ void launch_grad_b(const int64_t *tptr, const int32_t *trow, const int32_t *tpos
                    const int32_t *ccol, const T *dc, T *dB, hipStream_t s);
 void launch_zero(void *p, size_t bytes, hipStream_t s);
 void launch_set_pool(Pool *dst, Pool value, hipStream_t s);
+// Status of compute: to `slot` with `token`, or to `st` if there is no slot.
 void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, ComputeStatus *st,
-                   hipStream_t s);
+                   HostSlot *slot, uint64_t token, hipStream_t s);
+// The scan of the row sizes, with the status at its end.
+void scan_rows_status(const int64_t *v, int64_t n, int64_t *out, int64_t *part, const Pool *pool,
+                      ComputeStatus *st, HostSlot *slot, uint64_t token, hipStream_t s);
 
 // Access to a plan's device arrays (defined with the plan in api.hip).
 const int64_t *plan_rowoff(spgemm_plan p);

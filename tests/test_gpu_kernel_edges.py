@@ -72,3 +72,17 @@ def test_short_rows_around_network_sizes(dtype, col_range):
     targets = sizes * 2 + [s for s in sizes for _ in range(4)]
     A, B = S.crafted_rows(targets, col_range=col_range, empty_refs=3, dtype=dtype)
     check(A, B, long_path=1, bin_edges=(32, 64, 128, 256, 1024))
+
+
+@pytest.mark.parametrize("m", [0, 1, 4096, 4097, 32768, 131071, 131072, 262144, 262145])
+def test_row_counts_around_binning_and_copy_sizes(m):
+    """Row counts at the limits of the one-work-group binning, of its rows per
+    thread and of the copy's rows per wavefront; empty rows, rows of one to a
+    few hundred products and a long row among them."""
+    from test_gpu_parity import check
+    rng = np.random.default_rng(m)
+    B = _ragged(rng, 64, [0, 1, 2, 40] * 16, 5000, np.float64)
+    lens = np.arange(m) % 5
+    lens[-3:] = min(m, 60)
+    A = _ragged(rng, m, lens, 64, np.float64)
+    check(A, B)
