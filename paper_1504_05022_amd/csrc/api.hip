@@ -254,8 +254,8 @@ struct spgemm_plan_s {
   // backward scratch: A's transposed pattern, built on first use
   void *bws = nullptr;
   size_t bws_bytes = 0;
-  int32_t *tcnt = nullptr, *trow = nullptr, *tpos = nullptr;
-  int64_t *tptr = nullptr, *tpart = nullptr;
+  int32_t *trow = nullptr, *tpos = nullptr;
+  int64_t *tptr = nullptr;
 
   // second stream for the short-row kernels (from a per-device pool) and
   // the events that fork it from and join it to the caller's stream
@@ -1230,26 +1230,54 @@ extern "C" int spgemm_multiply(const spgemm_csr *A, const spgemm_csr *B,
 
 namespace {
 
-// A's transposed pattern (rows of every column, ascending), built once per plan.
-int ensure_transpose(spgemm_plan p, const spgemm_csr *A, hipStream_t s) {
+// A's transposed pattern (entries of every column, ascending), built once per
+// plan; *temp: temporary space the call held beside the plan's.
+int ensure_transpose(spgemm_plan p, const spgemm_csr *A, size_t *temp, hipStream_t s) {
+  *temp = 0;
   if (p->bws) return SPGEMM_OK;
+  // by partition where its temporary space can be had, else in place
+  TransposeParts tp;
+  bool parts = transpose_parts(p->k, p->nnzA, tp);
+  Layout T;
+  size_t oe = 0, otab = 0, ooff = 0, oprt = 0;
+  void *t = nullptr;
+  if (parts) {
+    const int64_t nt = tp.groups * tp.tiles;
+    oe = T.add<unsigned char>(p->nnzA * static_cast<int64_t>(kTransposeEntryBytes));
+    otab = T.add<int32_t>(nt);
+    ooff = T.add<int64_t>(nt + 1);
+    oprt = T.add<int64_t>(scan_part_len(nt));
+    t = p->al.get(T.bytes(), s);
+    parts = t != nullptr;
+  }
   Layout L;
-  const size_t oc = L.add<int32_t>(p->k);
   const size_t ot = L.add<int64_t>(p->k + 1);
-  const size_t orr = L.add<int32_t>(p->nnzA);
   const size_t op = L.add<int32_t>(p->nnzA);
-  const size_t opa = L.add<int64_t>(scan_part_len(std::max<int64_t>(p->k, 1)));
-  p->bws = p->al.get(L.bytes(), s);
-  if (!p->bws) return fail(SPGEMM_ENOMEM, "backward scratch allocation failed");
+  const size_t oc = parts ? 0 : L.add<int32_t>(p->k);
+  const size_t orr = parts ? 0 : L.add<int32_t>(p->nnzA);
+  const size_t opa = parts ? 0 : L.add<int64_t>(scan_part_len(std::max<int64_t>(p->k, 1)));
+  void *bws = p->al.get(L.bytes(), s);
+  if (!bws) {
+    p->al.put(t, s);
+    return fail(SPGEMM_ENOMEM, "backward scratch allocation failed");
+  }
+  int64_t *tptr = at<int64_t>(bws, ot);
+  int32_t *tpos = at<int32_t>(bws, op);
+  if (parts) {
+    *temp = alloc_size(T.bytes());
+    launch_transpose_parts(tp, A->col_idx, p->k, p->nnzA, at<unsigned char>(t, oe),
+                           at<int32_t>(t, otab), at<int64_t>(t, ooff), at<int64_t>(t, oprt), tptr,
+                           tpos, s);
+    p->al.put(t, s);
+  } else {
+    p->trow = at<int32_t>(bws, orr);
+    launch_transpose_pattern(A->row_ptr, A->col_idx, p->m, p->k, p->nnzA, at<int32_t>(bws, oc),
+                             tptr, p->trow, tpos, at<int64_t>(bws, opa), s);
+  }
+  p->bws = bws;
   p->bws_bytes = L.bytes();
-  p->tcnt = at<int32_t>(p->bws, oc);
-  p->tptr = at<int64_t>(p->bws, ot);
-  p->trow = at<int32_t>(p->bws, orr);
-  p->tpos = at<int32_t>(p->bws, op);
-  p->tpart = at<int64_t>(p->bws, opa);
-  p->info.bytes_scratch = held_bytes(p);
-  launch_transpose_pattern(A->row_ptr, A->col_idx, p->m, p->k, p->nnzA, p->tcnt, p->tptr,
-                           p->trow, p->tpos, p->tpart, s);
+  p->tptr = tptr;
+  p->tpos = tpos;
   return SPGEMM_OK;
 }
 
@@ -1269,14 +1297,27 @@ int backward_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, const sp
   T *dA = want_a ? static_cast<T *>(dA_val) : nullptr;
   T *dB = want_b ? static_cast<T *>(dB_val) : nullptr;
   int rc;
-  if (want_b && (rc = ensure_transpose(p, A, s)) != SPGEMM_OK) return rc;
+  size_t temp = 0;
+  if (want_b && (rc = ensure_transpose(p, A, &temp, s)) != SPGEMM_OK) return rc;
   const int64_t nprod = p->info.nnz_hat;
   T *W = nullptr;
   if (want_b && nprod > 0 && nprod * static_cast<int64_t>(sizeof(T)) <= kMaxStagedProducts)
     W = static_cast<T *>(p->al.get(static_cast<size_t>(nprod) * sizeof(T), s));
-  // the call's peak: what the plan holds plus the staged products
-  p->info.bytes_scratch =
-      held_bytes(p) + (W ? static_cast<int64_t>(alloc_size(static_cast<size_t>(nprod) * sizeof(T))) : 0);
+  // rows of the transposed pattern: only without staged products
+  int32_t *trow = p->trow;
+  void *rows = nullptr;
+  if (want_b && !W && !trow) {
+    rows = p->al.get(static_cast<size_t>(p->nnzA) * 4, s);
+    if (!rows) return fail(SPGEMM_ENOMEM, "backward scratch allocation failed");
+    trow = static_cast<int32_t *>(rows);
+    launch_transpose_rows(A->row_ptr, p->m, p->tpos, p->nnzA, trow, s);
+  }
+  // the call's peak: what the plan holds plus the larger of the pattern's
+  // temporary space and the staged products
+  size_t extra = temp;
+  if (W) extra = std::max(extra, alloc_size(static_cast<size_t>(nprod) * sizeof(T)));
+  if (rows) extra = std::max(extra, alloc_size(static_cast<size_t>(p->nnzA) * 4));
+  p->info.bytes_scratch = held_bytes(p) + static_cast<int64_t>(extra);
   if (want_a || W)
     launch_grad_entries<T>(A->row_ptr, aval, p->m, p->nnzA, p->P, p->bst,
                            B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, W, s);
@@ -1285,8 +1326,9 @@ int backward_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, const sp
       launch_grad_b_sum<T>(p->tptr, p->tpos, p->P, B->row_ptr, p->k, W, dB, s);
       p->al.put(W, s);
     } else {
-      launch_grad_b<T>(p->tptr, p->trow, p->tpos, aval, B->row_ptr, B->col_idx, p->k,
-                       C->row_ptr, C->col_idx, dc, dB, s);
+      launch_grad_b<T>(p->tptr, trow, p->tpos, aval, B->row_ptr, B->col_idx, p->k, C->row_ptr,
+                       C->col_idx, dc, dB, s);
+      p->al.put(rows, s);
     }
   }
   return SPGEMM_OK;

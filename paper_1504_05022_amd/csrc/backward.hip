@@ -504,6 +504,204 @@ void launch_transpose_pattern(const int32_t *arp, const int32_t *acol, int64_t m
     hipLaunchKernelGGL(k_col_sort, dim3((k + 255) / 256), dim3(256), 0, s, tptr, k, trow, tpos);
 }
 
+// ------------------------------------------------ transposed pattern by parts
+//
+// Stable and without global atomics, for plans, which can afford the space:
+// A's entries are partitioned by groups of W columns (tiles of TP_TILE
+// entries, one count per tile and group, one scan), then every group is
+// partitioned by column by one work-group.  Both steps keep the order of the
+// entries, so a column's positions ascend, and with them its rows, without
+// a sort.  A wavefront places 64 entries at a time: entries of one bucket find
+// each other by one ballot per key bit, and a counter per wavefront and
+// bucket gives their place.
+//
+// 6M entries in 300000 columns: counting 204, slot atomics and scatter 292,
+// per-column insertion sorts 294 us before; now 165 us in all (73 to partition,
+// 73 to order the groups).
+constexpr int TP_NT = 256;
+constexpr int TP_NW = TP_NT / WAVE;
+constexpr int TP_WAVE_ENTRIES = 2048;
+constexpr int TP_TILE = TP_NW * TP_WAVE_ENTRIES;
+constexpr int TP_GROUPS = 1024;     // column groups at most (16 KB of counters)
+constexpr int TP_WIDTH_LOG = 11;    // columns per group at most (32 KB of counters)
+constexpr int TP_GROUP_ENTRIES = 8192;  // entries per group aimed at
+
+struct TpEntry {
+  int32_t e, col;
+};
+
+// Place of this lane's entry (bucket b < 2^bits; ok: there is one) after the
+// entries of its bucket before it; advances the bucket's counter.
+DEVI int32_t tp_place(bool ok, uint32_t b, int bits, int32_t *cur) {
+  uint64_t same = __ballot(ok);
+  for (int k = 0; k < bits; ++k) {
+    const bool bit = (b >> k) & 1u;
+    const uint64_t m = __ballot(ok && bit);
+    same &= bit ? m : ~m;
+  }
+  const uint64_t below = same & ((1ull << lane()) - 1ull);
+  int32_t at = 0;
+  if (ok) at = cur[b] + __popcll(below);
+  wave_sync();
+  if (ok && (same >> lane()) == 1ull) cur[b] = at + 1;  // the bucket's last lane
+  wave_sync();
+  return at;
+}
+
+// Entries of every column group in every tile: table[group * tiles + tile].
+__global__ __launch_bounds__(TP_NT) void k_tp_count(const int32_t *acol, int64_t nnz, int wlog,
+                                                    int groups, int32_t *table) {
+  __shared__ int32_t cnt[TP_GROUPS];
+  for (int g = threadIdx.x; g < groups; g += TP_NT) cnt[g] = 0;
+  __syncthreads();
+  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * TP_TILE;
+  int32_t c[TP_TILE / TP_NT];
+#pragma unroll
+  for (int j = 0; j < TP_TILE / TP_NT; ++j) {
+    const int64_t e = e0 + j * TP_NT + threadIdx.x;
+    c[j] = acol[e < nnz ? e : nnz - 1];
+  }
+#pragma unroll
+  for (int j = 0; j < TP_TILE / TP_NT; ++j)
+    if (e0 + j * TP_NT + threadIdx.x < nnz) atomicAdd(&cnt[c[j] >> wlog], 1);
+  __syncthreads();
+  for (int g = threadIdx.x; g < groups; g += TP_NT)
+    table[static_cast<int64_t>(g) * gridDim.x + blockIdx.x] = cnt[g];
+}
+
+// Entries to their column groups, in order (off: scanned table).
+__global__ __launch_bounds__(TP_NT) void k_tp_part(const int32_t *acol, int64_t nnz, int wlog,
+                                                   int groups, int gbits, const int64_t *off,
+                                                   TpEntry *out) {
+  __shared__ int32_t cur[TP_NW][TP_GROUPS];
+  const int w = threadIdx.x / WAVE;
+  for (int g = threadIdx.x; g < TP_NW * TP_GROUPS; g += TP_NT) (&cur[0][0])[g] = 0;
+  __syncthreads();
+  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * TP_TILE + w * TP_WAVE_ENTRIES;
+  constexpr int ROWS = TP_WAVE_ENTRIES / WAVE;
+  int32_t c[ROWS];
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j) {
+    const int64_t e = e0 + j * WAVE + lane();
+    c[j] = acol[e < nnz ? e : nnz - 1];
+  }
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j)
+    if (e0 + j * WAVE + lane() < nnz) atomicAdd(&cur[w][c[j] >> wlog], 1);
+  __syncthreads();
+  for (int g = threadIdx.x; g < groups; g += TP_NT) {
+    int32_t at = static_cast<int32_t>(off[static_cast<int64_t>(g) * gridDim.x + blockIdx.x]);
+#pragma unroll
+    for (int q = 0; q < TP_NW; ++q) {
+      const int32_t n = cur[q][g];
+      cur[q][g] = at;
+      at += n;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j) {
+    const int64_t e = e0 + j * WAVE + lane();
+    const bool ok = e < nnz;
+    const int32_t at = tp_place(ok, static_cast<uint32_t>(c[j]) >> wlog, gbits, cur[w]);
+    if (ok) out[at] = TpEntry{static_cast<int32_t>(e), c[j]};
+  }
+}
+
+// One work-group per column group: its columns' pointers, and its entries by
+// column, in order.
+__global__ __launch_bounds__(TP_NT) void k_tp_columns(const TpEntry *in, const int64_t *off,
+                                                      int64_t tiles, int64_t k, int wlog,
+                                                      int64_t *tptr, int32_t *tpos) {
+  extern __shared__ int32_t cur[];  // [TP_NW][width]
+  __shared__ int64_t sm[TP_NT / WAVE + 1];
+  const int width = 1 << wlog;
+  const int w = threadIdx.x / WAVE;
+  const int64_t g = blockIdx.x;
+  const int64_t s0 = off[g * tiles], s1 = off[(g + 1) * tiles];
+  for (int x = threadIdx.x; x < TP_NW * width; x += TP_NT) cur[x] = 0;
+  __syncthreads();
+  // a quarter of the group per wavefront
+  const int64_t per = (s1 - s0 + TP_NW * WAVE - 1) / (TP_NW * WAVE) * WAVE;
+  const int64_t w0 = s0 + w * per < s1 ? s0 + w * per : s1;
+  const int64_t w1 = w0 + per < s1 ? w0 + per : s1;
+  int32_t *mine = cur + w * width;
+  for (int64_t x = w0 + lane(); x < w1; x += WAVE) atomicAdd(&mine[in[x].col & (width - 1)], 1);
+  __syncthreads();
+  int64_t base = s0;
+  for (int c0 = 0; c0 < width; c0 += TP_NT) {
+    const int c = c0 + threadIdx.x;
+    int64_t n = 0, tot;
+    if (c < width)
+      for (int q = 0; q < TP_NW; ++q) n += cur[q * width + c];
+    const int64_t at = base + block_excl_sum<TP_NT>(n, sm, tot);
+    if (c < width) {
+      int32_t run = static_cast<int32_t>(at);
+      for (int q = 0; q < TP_NW; ++q) {
+        const int32_t x = cur[q * width + c];
+        cur[q * width + c] = run;
+        run += x;
+      }
+      if ((g << wlog) + c < k) tptr[(g << wlog) + c] = at;
+    }
+    base += tot;
+  }
+  if (threadIdx.x == 0 && ((g + 1) << wlog) >= k) tptr[k] = s1;
+  __syncthreads();
+  // the next round's entry is loaded while the current one is placed
+  TpEntry next{0, 0};
+  if (w0 + lane() < w1) next = in[w0 + lane()];
+  for (int64_t x0 = w0; x0 < w1; x0 += WAVE) {
+    const TpEntry en = next;
+    const int64_t xn = x0 + WAVE + lane();
+    if (xn < w1) next = in[xn];
+    const bool ok = x0 + lane() < w1;
+    const int32_t at = tp_place(ok, static_cast<uint32_t>(en.col) & (width - 1), wlog, mine);
+    if (ok) tpos[at] = en.e;
+  }
+}
+
+// Row of every position of the transposed pattern.
+__global__ void k_tp_rows(const int32_t *arp, int64_t m, const int32_t *tpos, int64_t nnz,
+                          int32_t *trow) {
+  const int64_t d = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (d < nnz) trow[d] = row_of(arp, 0, static_cast<int32_t>(m), tpos[d]);
+}
+
+bool transpose_parts(int64_t k, int64_t nnz, TransposeParts &tp) {
+  if (k <= 0 || nnz <= 0) return false;
+  tp.wlog = 0;
+  while (tp.wlog < TP_WIDTH_LOG && (int64_t(2) << tp.wlog) <= k * TP_GROUP_ENTRIES / nnz) ++tp.wlog;
+  auto groups = [&] { return (k + (int64_t(1) << tp.wlog) - 1) >> tp.wlog; };
+  while (tp.wlog < TP_WIDTH_LOG && groups() > TP_GROUPS) ++tp.wlog;
+  if (groups() > TP_GROUPS) return false;  // beyond 2M columns
+  tp.groups = groups();
+  tp.tiles = (nnz + TP_TILE - 1) / TP_TILE;
+  return true;
+}
+
+void launch_transpose_parts(const TransposeParts &tp, const int32_t *acol, int64_t k, int64_t nnz,
+                            void *entries, int32_t *table, int64_t *off, int64_t *part,
+                            int64_t *tptr, int32_t *tpos, hipStream_t s) {
+  TpEntry *en = static_cast<TpEntry *>(entries);
+  const int groups = static_cast<int>(tp.groups);
+  hipLaunchKernelGGL(k_tp_count, dim3(tp.tiles), dim3(TP_NT), 0, s, acol, nnz, tp.wlog, groups,
+                     table);
+  scan_i32(table, tp.groups * tp.tiles, off, part, s);
+  hipLaunchKernelGGL(k_tp_part, dim3(tp.tiles), dim3(TP_NT), 0, s, acol, nnz, tp.wlog, groups,
+                     ceil_log2(groups), off, en);
+  hipLaunchKernelGGL(k_tp_columns, dim3(tp.groups), dim3(TP_NT),
+                     (sizeof(int32_t) * TP_NW) << tp.wlog, s, en, off, tp.tiles, k, tp.wlog, tptr,
+                     tpos);
+}
+
+void launch_transpose_rows(const int32_t *arp, int64_t m, const int32_t *tpos, int64_t nnz,
+                           int32_t *trow, hipStream_t s) {
+  if (nnz > 0)
+    hipLaunchKernelGGL(k_tp_rows, dim3((nnz + 255) / 256), dim3(256), 0, s, arp, m, tpos, nnz,
+                       trow);
+}
+
 template <typename T>
 void launch_grad_b(const int64_t *tptr, const int32_t *trow, const int32_t *tpos, const T *aval,
                    const int32_t *brp, const int32_t *bcol, int64_t kb, const int32_t *crp,

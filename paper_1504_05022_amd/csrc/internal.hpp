@@ -539,7 +539,24 @@ void launch_fill_i64(int64_t *p, int64_t n, int64_t v, hipStream_t s);
 void launch_transpose_pattern(const int32_t *arp, const int32_t *acol, int64_t m, int64_t k,
                               int64_t nnz, int32_t *cnt, int64_t *tptr, int32_t *trow,
                               int32_t *tpos, int64_t *part, hipStream_t s);
-// Entry-parallel gradient: dA (nullable) and the products W (nullable,
+// The same pattern by stable partition, for callers with 8 bytes per entry of
+// temporary space; false: more than 2M columns, use the form above.
+struct TransposeParts {
+  int wlog;        // log2 of the columns per group
+  int64_t groups;  // column groups
+  int64_t tiles;   // tiles of entries
+};
+constexpr size_t kTransposeEntryBytes = 8;
+bool transpose_parts(int64_t k, int64_t nnz, TransposeParts &tp);
+// entries: nnz * kTransposeEntryBytes; table: groups * tiles; off: one more;
+// part: scan_part_len(groups * tiles).  Positions only.
+void launch_transpose_parts(const TransposeParts &tp, const int32_t *acol, int64_t k, int64_t nnz,
+                            void *entries, int32_t *table, int64_t *off, int64_t *part,
+                            int64_t *tptr, int32_t *tpos, hipStream_t s);
+// Rows of the positions (only dB without staged products needs them).
+void launch_transpose_rows(const int32_t *arp, int64_t m, const int32_t *tpos, int64_t nnz,
+                           int32_t *trow, hipStream_t s);
+// Product-parallel gradient: dA (nullable) and the products W (nullable,
 // sum(u) entries) of the dB sums; then dB from W over A's transposed pattern.
 template <typename T>
 void launch_grad_entries(const int32_t *arp, const T *aval, int64_t m, int64_t nnz,

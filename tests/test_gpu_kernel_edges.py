@@ -86,3 +86,37 @@ def test_row_counts_around_binning_and_copy_sizes(m):
     lens[-3:] = min(m, 60)
     A = _ragged(rng, m, lens, 64, np.float64)
     check(A, B)
+
+
+@pytest.mark.parametrize("k", [1, 2, 1024, 1025, 4096])
+def test_db_over_transposed_pattern_parts(k):
+    """Columns of A from one to several groups of them, entries around tiles
+    of 8192 and wavefronts of 2048, a column in every row, empty columns:
+    dB, whose sums run in the order of A's rows, equals sequential sums."""
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, Plan
+    rng = np.random.default_rng(k)
+    for rows in (1, 2047, 8191, 8193, 20001):
+        lens = np.minimum(rng.integers(0, 4, rows), k)
+        A = _ragged(rng, rows, lens, k, np.float64)
+        # every row also holds column 0
+        entries = [np.unique(np.r_[0, A.col_idx[a:b]])
+                   for a, b in zip(A.row_ptr[:-1], A.row_ptr[1:])]
+        rp = np.r_[0, np.cumsum([x.size for x in entries])].astype(np.int32)
+        ci = np.concatenate(entries).astype(np.int32)
+        A = S.Csr(rows, k, rp, ci, rng.standard_normal(ci.size))
+        B = S.Csr(k, 3, np.arange(k + 1, dtype=np.int32), (np.arange(k) % 3).astype(np.int32),
+                  rng.standard_normal(k))
+        print("case: %d x %d, %d entries" % (rows, k, ci.size), flush=True)
+        dA, dB = CsrMatrix.from_host(A), CsrMatrix.from_host(B)
+        plan = Plan(dA, dB)
+        C = plan.compute()
+        dc = rng.standard_normal(C.nnz)
+        _, gB = plan.backward(C, torch.from_numpy(dc).cuda(), want_a=False)
+        _, _, crp, cci, _ = C.to_host()
+        dense = np.zeros((rows, 3))
+        dense[np.repeat(np.arange(rows), np.diff(crp)), cci] = dc
+        prod = A.val * dense[np.repeat(np.arange(rows), np.diff(rp)), ci % 3]
+        ref = np.zeros(k)
+        np.add.at(ref, ci, prod)  # in the order of the entries
+        assert np.array_equal(gB.cpu().numpy(), ref)
