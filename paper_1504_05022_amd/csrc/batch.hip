@@ -212,8 +212,10 @@ __global__ __launch_bounds__(BM_NT) void k_bm_entries(const BmTile *tiles, const
 }
 
 // Stage 1, rows: u_i from the entry scan P, rows of every capacity class
-// and the sum of u_i counted per problem (one atomic per wavefront and
-// class).  Rows without products get their final size, 0, here.
+// and the sum of u_i counted per problem (in LDS first: one atomic per
+// work-group and class; one per wavefront and class, all on a few addresses,
+// took 64 us for 310k rows).  Rows without products get their final size, 0,
+// here.
 __global__ __launch_bounds__(BM_NT) void k_bm_rows(const BmTile *tiles, const BmProblem *probs,
                                                    const int64_t *P, int64_t *U, int64_t *RN,
                                                    unsigned long long *cnt,
@@ -228,14 +230,22 @@ __global__ __launch_bounds__(BM_NT) void k_bm_rows(const BmTile *tiles, const Bm
     U[q.ro + i] = u;
     if (u == 0) RN[q.ro + i] = 0;
   }
+  __shared__ unsigned int cls[BM_NCLS];
+  __shared__ unsigned long long sum;
+  if (threadIdx.x < BM_NCLS) cls[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) sum = 0ull;
+  __syncthreads();
   const int c = valid ? bm_class(u) : -1;
-  unsigned long long *cp = cnt + static_cast<int64_t>(t.prob) * BM_NCLS;
-  for (int k = 0; k < BM_NCLS; ++k) {
-    const unsigned long long mk = __ballot(c == k);
-    if (mk != 0 && lane() == 0) atomicAdd(cp + k, static_cast<unsigned long long>(__popcll(mk)));
-  }
+  if (c >= 0) atomicAdd(&cls[c], 1u);
   const long long tot = group_last<WAVE>(group_incl_sum<WAVE>(static_cast<long long>(u)));
-  if (tot != 0 && lane() == 0) atomicAdd(sumu + t.prob, static_cast<unsigned long long>(tot));
+  if (tot != 0 && lane() == 0) atomicAdd(&sum, static_cast<unsigned long long>(tot));
+  __syncthreads();
+  unsigned long long *cp = cnt + static_cast<int64_t>(t.prob) * BM_NCLS;
+  if (threadIdx.x < BM_NCLS) {
+    const unsigned int n = cls[threadIdx.x];
+    if (n != 0u) atomicAdd(cp + threadIdx.x, static_cast<unsigned long long>(n));
+  }
+  if (threadIdx.x == 0 && sum != 0ull) atomicAdd(sumu + t.prob, sum);
 }
 
 // Stage 2: the rows of every batched problem into its class lists; cur
@@ -258,16 +268,22 @@ __global__ __launch_bounds__(BM_NT) void k_bm_scatter(const BmTile *tiles, const
     rec.e0 = q.arp[i];
     rec.ne = q.arp[i + 1] - rec.e0;
   }
+  // places in the work-group's part of every list, then one reservation per
+  // list and work-group
+  __shared__ unsigned int cls[kBatchNumClasses];
+  __shared__ unsigned long long first[kBatchNumClasses];
+  if (threadIdx.x < kBatchNumClasses) cls[threadIdx.x] = 0u;
+  __syncthreads();
+  unsigned int at = 0u;
+  if (c >= 0 && c < kBatchNumClasses) at = atomicAdd(&cls[c], 1u);
+  __syncthreads();
   unsigned long long *cp = cur + static_cast<int64_t>(t.prob) * BM_NCLS;
-  const unsigned long long below = (1ull << lane()) - 1ull;
-  for (int k = 0; k < kBatchNumClasses; ++k) {
-    const unsigned long long mk = __ballot(c == k);
-    if (mk == 0) continue;
-    unsigned long long b = 0;
-    if (lane() == 0) b = atomicAdd(cp + k, static_cast<unsigned long long>(__popcll(mk)));
-    b = static_cast<unsigned long long>(__shfl(static_cast<long long>(b), 0, WAVE));
-    if (c == k) list[b + __popcll(mk & below)] = rec;
+  if (threadIdx.x < kBatchNumClasses) {
+    const unsigned int n = cls[threadIdx.x];
+    if (n != 0u) first[threadIdx.x] = atomicAdd(cp + threadIdx.x, static_cast<unsigned long long>(n));
   }
+  __syncthreads();
+  if (c >= 0 && c < kBatchNumClasses) list[first[c] + at] = rec;
 }
 
 // Work items of list (problem, class) = blockIdx.x: rows [base + k * rpb,
