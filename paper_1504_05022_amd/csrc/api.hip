@@ -1138,7 +1138,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   ca.c_col = static_cast<int32_t *>(ccol);
   ca.c_val = static_cast<T *>(cval);
   if (m > 0)
-    launch_compact<T>(ca, m, npieces, s);
+    launch_compact<T>(ca, m, S.sum_u - S.sum_u_long, npieces, s);
   else
     launch_zero(crp, 4, s);
   stage_end(p, SPGEMM_T_COPY, s);

@@ -319,13 +319,16 @@ __global__ void k_bm_gather(const BmProblem *probs, int32_t count, const int64_t
   if (p == count) g[p] = RO[R];
 }
 
-template <typename T>
+// work-groups per row tile of a copy of R rows per wavefront
+constexpr int bm_copy_split(int r) { return BM_ROW_TILE / (CP_NT / WAVE * r); }
+
+template <typename T, int R>
 DEVI void bm_copy_rows(const BmProblem &q, const int32_t *tcol, const int64_t *CTO,
                        const int64_t *RO, const int64_t *RN, int64_t r0, int64_t end,
-                       CopyTable<CP_ROWS> &tb) {
+                       CopyTable<R> &tb) {
   const int64_t i = r0 + lane();
   int64_t n = 0, src = 0, o = 0;
-  if (lane() < CP_ROWS && i < end) {
+  if (lane() < R && i < end) {
     const int64_t base = RO[q.ro];
     o = RO[q.ro + i] - base;
     q.crp[i] = static_cast<int32_t>(o);
@@ -333,31 +336,34 @@ DEVI void bm_copy_rows(const BmProblem &q, const int32_t *tcol, const int64_t *C
     n = RN[q.ro + i];
     src = CTO[q.ro + i];
   }
-  wave_stream_copy<T, CP_ROWS>(n, tcol + src, static_cast<const T *>(q.tval) + src, o, q.ccol,
+  wave_stream_copy<T, R>(n, tcol + src, static_cast<const T *>(q.tval) + src, o, q.ccol,
                                static_cast<T *>(q.cval), tb);
 }
 
 // Stage 5 for every batched problem: row pointers of C_p and its rows
-// copied from C~, CP_ROWS rows per wavefront.
+// copied from C~, R rows per wavefront (copy_rows).
+template <int R>
 __global__ __launch_bounds__(CP_NT) void k_bm_compact(const BmTile *tiles, const BmProblem *probs,
                                                       const int32_t *tcol, const int64_t *CTO,
                                                       const int64_t *RO, const int64_t *RN) {
-  __shared__ CopyTable<CP_ROWS> tabs[CP_NT / WAVE];
-  const BmTile t = tiles[blockIdx.x];
+  constexpr int SPLIT = bm_copy_split(R);
+  __shared__ CopyTable<R> tabs[CP_NT / WAVE];
+  const BmTile t = tiles[blockIdx.x / SPLIT];
   const BmProblem &q = probs[t.prob];
   if (!q.batched) return;
+  const int part = blockIdx.x % SPLIT;
   if (q.m == 0) {
-    if (threadIdx.x == 0) q.crp[0] = 0;
+    if (part == 0 && threadIdx.x == 0) q.crp[0] = 0;
     return;
   }
   const int w = threadIdx.x / WAVE;
   const int64_t end = min(t.start + BM_ROW_TILE, q.m);
-  for (int64_t r0 = t.start + w * CP_ROWS; r0 < end; r0 += (CP_NT / WAVE) * CP_ROWS) {
-    if (q.dtype == SPGEMM_F64)
-      bm_copy_rows<double>(q, tcol, CTO, RO, RN, r0, end, tabs[w]);
-    else
-      bm_copy_rows<float>(q, tcol, CTO, RO, RN, r0, end, tabs[w]);
-  }
+  const int64_t r0 = t.start + (part * (CP_NT / WAVE) + w) * R;
+  if (r0 >= end) return;  // uniform across the wavefront
+  if (q.dtype == SPGEMM_F64)
+    bm_copy_rows<double, R>(q, tcol, CTO, RO, RN, r0, end, tabs[w]);
+  else
+    bm_copy_rows<float, R>(q, tcol, CTO, RO, RN, r0, end, tabs[w]);
 }
 
 }  // namespace spg
@@ -862,7 +868,7 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
     E += q.nnz;
     R += q.m;
   }
-  if (etile.size() >= (size_t(1) << 31) || rtile.size() >= (size_t(1) << 31))
+  if (etile.size() >= (size_t(1) << 31) || rtile.size() >= (size_t(1) << 31) / bm_copy_split(2))
     return bfail(SPGEMM_EOVERFLOW, "batch too large for one launch");
 
   // scratch of the analysis
@@ -1111,8 +1117,20 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   }
   if (!h2d(dprob, hp.data(), sizeof(BmProblem) * count))
     return bfail(SPGEMM_EHIP, "batch table upload failed");
-  hipLaunchKernelGGL(k_bm_compact, dim3(static_cast<unsigned int>(rtile.size())), dim3(CP_NT), 0,
-                     s, drt, dprob, reinterpret_cast<const int32_t *>(tcol), dCTO, dRO, dRN);
+  const auto copy = [&](auto r) {
+    constexpr int RR = decltype(r)::value;
+    hipLaunchKernelGGL(k_bm_compact<RR>,
+                       dim3(static_cast<unsigned int>(rtile.size() * bm_copy_split(RR))),
+                       dim3(CP_NT), 0, s, drt, dprob, reinterpret_cast<const int32_t *>(tcol), dCTO,
+                       dRO, dRN);
+  };
+  switch (copy_rows(R, ntilde)) {
+    case 32: copy(std::integral_constant<int, 32>{}); break;
+    case 16: copy(std::integral_constant<int, 16>{}); break;
+    case 8: copy(std::integral_constant<int, 8>{}); break;
+    case 4: copy(std::integral_constant<int, 4>{}); break;
+    default: copy(std::integral_constant<int, 2>{}); break;
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return bfail(SPGEMM_EHIP, std::string("batch multiply: ") + hipGetErrorString(e));
   mem.keep(ob);

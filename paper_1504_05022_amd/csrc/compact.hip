@@ -4,6 +4,8 @@
 // rows and streams all their entries at once, so the copy is coalesced and
 // no wavefront waits on one row's metadata; long rows are copied piece by
 // piece, one wavefront each.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 #include "stream_copy.hpp"
@@ -11,9 +13,7 @@
 namespace spg {
 
 // Row pointers of C, and the short rows (u <= long_min) copied from C~:
-// R consecutive rows per wavefront, fewer where m is small, so that the copy
-// still fills the chip (2000 rows of 100 entries: 63 wavefronts of 32 rows
-// took 21.5 us, 1000 of 2 take 6).
+// R consecutive rows per wavefront (copy_rows).
 template <typename T, int R>
 __global__ __launch_bounds__(CP_NT) void k_compact_rows(CompactArgs<T> a, int64_t m) {
   __shared__ CopyTable<R> tabs[CP_NT / WAVE];
@@ -77,24 +77,30 @@ __global__ __launch_bounds__(CP_NT) void k_compact_pieces(CompactArgs<T> a, int6
 }
 
 template <typename T>
-void launch_compact(const CompactArgs<T> &a, int64_t m, int64_t npieces, hipStream_t s) {
+void launch_compact(const CompactArgs<T> &a, int64_t m, int64_t products, int64_t npieces,
+                    hipStream_t s) {
   if (m <= 0) return;
-  const auto grid = [&](int64_t r) {
-    return dim3(static_cast<unsigned int>(((m + r - 1) / r * WAVE + CP_NT - 1) / CP_NT));
+  const auto rows = [&](auto r) {
+    constexpr int RR = decltype(r)::value;
+    const int64_t waves = (m + RR - 1) / RR;
+    hipLaunchKernelGGL((k_compact_rows<T, RR>), dim3((waves * WAVE + CP_NT - 1) / CP_NT),
+                       dim3(CP_NT), 0, s, a, m);
   };
-  // four wavefronts per SIMD or more
-  if (m >= 4096 * CP_ROWS)
-    hipLaunchKernelGGL((k_compact_rows<T, CP_ROWS>), grid(CP_ROWS), dim3(CP_NT), 0, s, a, m);
-  else if (m >= 4096 * 8)
-    hipLaunchKernelGGL((k_compact_rows<T, 8>), grid(8), dim3(CP_NT), 0, s, a, m);
-  else
-    hipLaunchKernelGGL((k_compact_rows<T, 2>), grid(2), dim3(CP_NT), 0, s, a, m);
+  switch (copy_rows(m, products)) {
+    case 32: rows(std::integral_constant<int, 32>{}); break;
+    case 16: rows(std::integral_constant<int, 16>{}); break;
+    case 8: rows(std::integral_constant<int, 8>{}); break;
+    case 4: rows(std::integral_constant<int, 4>{}); break;
+    default: rows(std::integral_constant<int, 2>{}); break;
+  }
   if (npieces > 0)
     hipLaunchKernelGGL((k_compact_pieces<T>), dim3((npieces * WAVE + CP_NT - 1) / CP_NT),
                        dim3(CP_NT), 0, s, a, npieces);
 }
 
-template void launch_compact<float>(const CompactArgs<float> &, int64_t, int64_t, hipStream_t);
-template void launch_compact<double>(const CompactArgs<double> &, int64_t, int64_t, hipStream_t);
+template void launch_compact<float>(const CompactArgs<float> &, int64_t, int64_t, int64_t,
+                                    hipStream_t);
+template void launch_compact<double>(const CompactArgs<double> &, int64_t, int64_t, int64_t,
+                                     hipStream_t);
 
 }  // namespace spg

@@ -529,8 +529,10 @@ template <typename T> struct CompactArgs {
   int32_t *c_col;
   T *c_val;
 };
+// products: of the short rows together
 template <typename T>
-void launch_compact(const CompactArgs<T> &a, int64_t m, int64_t npieces, hipStream_t s);
+void launch_compact(const CompactArgs<T> &a, int64_t m, int64_t products, int64_t npieces,
+                    hipStream_t s);
 
 void launch_fill_i64(int64_t *p, int64_t n, int64_t v, hipStream_t s);
 
