@@ -36,6 +36,7 @@
 // allocated before the numeric pass, which writes every item straight to
 // its place in C.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "internal.hpp"
@@ -623,9 +624,23 @@ __global__ __launch_bounds__(WAVE) void k_wpart(EscArgs<T> e, const WinRow *rows
 // numeric pass starts every column at a signalling-NaN pattern that no
 // arithmetic result has (results are quiet NaNs), replaced by +0.0 + p at
 // the column's first product, so the columns hit are those that lost it.
-// The loads of GE entries are issued together, one group ahead.
+// The loads of a group of slots are issued together, one group ahead.  A
+// slot holds one entry, or two of at most 32 products, or four of at most
+// 16: half and quarter wavefronts load their own b_j* rows, so that more of
+// them are in flight; numeric updates still go entry by entry, symbolic ones
+// (stores of 1) all at once.
+//
+// What bounds it: the latency of the B-row gathers at 7 to 9 wavefronts per
+// CU (their accumulators fill LDS), then the read-add-write chain.  Numeric /
+// symbolic pass of the long rows of a 300000^2 x 4096 product, 32 per row of
+// B, binary32: 626 / 209 us with one entry per slot, 546 / 174 now; of a
+// 90001^2 x 2000 one, 24 per row, binary64: 227 / 112 and 174 / 74.
 
-constexpr int GE = 16;
+// slots per group (16 and 8 measured 573 and 546 us binary32, 174 and 181
+// binary64: two wavefronts per SIMD with 255 registers are all LDS allows)
+template <typename T, bool NUM, int SUB> constexpr int dense_slots() {
+  return NUM && sizeof(T) == 4 && SUB < WAVE ? 8 : 16;
+}
 
 DEVI float readlane_val(float v, int t) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), t));
@@ -687,7 +702,6 @@ template <typename T, bool NUM>
 __global__ __launch_bounds__(WAVE * dense_nwv<NUM>())
 __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<NUM>())))
 void k_wdense(WinArgsW<T> a, uint32_t *dbits, T *dacc) {
-  constexpr int G = GE;  // entries per load group
   constexpr int NWV = dense_nwv<NUM>();
   __shared__ DenseLds<T, NUM> L;
   const int ln = lane();
@@ -758,47 +772,80 @@ void k_wdense(WinArgsW<T> a, uint32_t *dbits, T *dacc) {
         }
       }
       const int nb = (e_end - eb) < WAVE ? (e_end - eb) : WAVE;
-      // groups of G entries, double-buffered: the loads of the next group
-      // are in flight while the current one is added
-      struct Group {
-        int32_t st[G], ls[G], bc[G];
-        T as[G], bv[G];
-      };
-      auto load_group = [&](int t0, Group &g_) {
+      // groups of G slots of 64 / SUB entries (SUB lanes each), double-
+      // buffered: the loads of the next group are in flight while the
+      // current one is added
+      auto take = [&](auto sub_c) {
+        constexpr int SUB = decltype(sub_c)::value;
+        constexpr int EPS = WAVE / SUB;           // entries per slot
+        constexpr int G = dense_slots<T, NUM, SUB>();
+        const int sub = ln / SUB, x = ln & (SUB - 1);
+        struct Group {
+          int32_t st[SUB == WAVE ? G : 1], ls[G], bc[G];
+          T as[G], bv[G];
+        };
+        auto load_group = [&](int t0, Group &g_) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const int t = t0 + g < nb ? t0 + g : nb - 1;
-          g_.st[g] = __builtin_amdgcn_readlane(start, t);
-          g_.ls[g] = t0 + g < nb ? __builtin_amdgcn_readlane(len, t) : 0;
-          g_.as[g] = NUM ? readlane_val(av, t) : T(0);
-          // clamped, not branched around: the loads of a group stay in
-          // flight together (B has entries whenever the item has products)
-          const int32_t idx = ln < g_.ls[g] ? g_.st[g] + ln : 0;
-          g_.bc[g] = bcol[idx];
-          g_.bv[g] = NUM ? bval[idx] : T(0);
-        }
-      };
-      Group cur, nxt;
-      load_group(0, cur);
-      for (int t0 = 0; t0 < nb; t0 += G) {
-        if (t0 + G < nb) load_group(t0 + G, nxt);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          if (ln < cur.ls[g]) update(cur.bc[g], cur.as[g] * cur.bv[g]);
-          order_lds();
-          // b_j* rows longer than a wavefront: the rest of the row, in order
-          for (int x0 = WAVE; x0 < cur.ls[g]; x0 += WAVE) {
-            const int x = x0 + ln;
-            if (x < cur.ls[g]) {
-              const int32_t c = bcol[cur.st[g] + x];
-              const T v = NUM ? bval[cur.st[g] + x] : T(0);
-              update(c, cur.as[g] * v);
+          for (int g = 0; g < G; ++g) {
+            const int t = t0 + g * EPS + sub;
+            const int tc = t < nb ? t : nb - 1;
+            int32_t st;
+            if constexpr (SUB == WAVE) {
+              st = __builtin_amdgcn_readlane(start, tc);
+              g_.st[g] = st;
+              g_.ls[g] = t < nb ? __builtin_amdgcn_readlane(len, tc) : 0;
+              g_.as[g] = NUM ? readlane_val(av, tc) : T(0);
+            } else {
+              st = __shfl(start, tc, WAVE);
+              const int32_t l = __shfl(len, tc, WAVE);
+              g_.ls[g] = t < nb ? l : 0;
+              g_.as[g] = NUM ? __shfl(av, tc, WAVE) : T(0);
             }
-            order_lds();
+            // clamped, not branched around: the loads of a group stay in
+            // flight together (B has entries whenever the item has products)
+            const int32_t idx = x < g_.ls[g] ? st + x : 0;
+            g_.bc[g] = bcol[idx];
+            g_.bv[g] = NUM ? bval[idx] : T(0);
           }
+        };
+        Group cur, nxt;
+        load_group(0, cur);
+        for (int t0 = 0; t0 < nb; t0 += G * EPS) {
+          if (t0 + G * EPS < nb) load_group(t0 + G * EPS, nxt);
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            if constexpr (NUM) {
+              // entry after entry: two of them may share a column
+#pragma unroll
+              for (int q = 0; q < EPS; ++q) {
+                if (x < cur.ls[g] && sub == q) update(cur.bc[g], cur.as[g] * cur.bv[g]);
+                order_lds();
+              }
+            } else {
+              if (x < cur.ls[g]) update(cur.bc[g], T(0));  // in any order
+            }
+            if constexpr (SUB == WAVE) {
+              // b_j* rows longer than a wavefront: the rest of the row, in order
+              for (int x0 = WAVE; x0 < cur.ls[g]; x0 += WAVE) {
+                const int y = x0 + ln;
+                if (y < cur.ls[g]) {
+                  const int32_t c = bcol[cur.st[g] + y];
+                  const T v = NUM ? bval[cur.st[g] + y] : T(0);
+                  update(c, cur.as[g] * v);
+                }
+                order_lds();
+              }
+            }
+          }
+          cur = nxt;
         }
-        cur = nxt;
-      }
+      };
+      if (!__any(len > 16))
+        take(std::integral_constant<int, 16>{});
+      else if (!__any(len > 32))
+        take(std::integral_constant<int, 32>{});
+      else
+        take(std::integral_constant<int, 64>{});
       if (a.e.P[eb + nb] - P0 >= q1) break;
     }
     group_sync();

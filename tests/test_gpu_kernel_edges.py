@@ -120,3 +120,20 @@ def test_db_over_transposed_pattern_parts(k):
         ref = np.zeros(k)
         np.add.at(ref, ci, prod)  # in the order of the entries
         assert np.array_equal(gB.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("most", [16, 17, 32, 33, 64, 65, 200])
+def test_dense_windows_by_b_row_length(dtype, most):
+    """Long rows of a narrow product whose rows of B are all at most 16, at
+    most 32 or longer (alone, two and four to a wavefront), with equal columns
+    in neighbouring rows, empty rows and partly filled batches; one row above
+    the size that is cut into product ranges."""
+    from test_gpu_parity import check
+    rng = np.random.default_rng(most)
+    n = 256
+    lens = np.r_[most, rng.integers(0, most + 1, 199)]
+    B = _ragged(rng, 200, lens, n, dtype)
+    deg = [d for d in (5, 63, 64, 65, 127, 130, 199, 200) for _ in range(6)]
+    A = _ragged(rng, len(deg), deg, 200, dtype)
+    check(A, B, exact=bool(np.sum(lens) <= 16384))
