@@ -1113,6 +1113,11 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
       I.bytes_scratch = held_bytes(p);
     }
   }
+  // the copy of the short rows; beside the numeric window pass, which leaves
+  // bandwidth to spare (its wavefronts wait on gathers), it runs on the second
+  // stream where it is worth the events (1M products copy in about 10 us)
+  const bool beside = use_win && es != s && S.sum_u - S.sum_u_long >= (int64_t(1) << 20) &&
+                      fork_aux(p, s);
   if (use_win) {
     // numeric pass of the long rows, straight into C
     stage_begin(p, SPGEMM_T_COMBINE, s);
@@ -1123,7 +1128,8 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     stage_end(p, SPGEMM_T_COMBINE_WAVE, s);
     stage_end(p, SPGEMM_T_COMBINE, s);
   }
-  stage_begin(p, SPGEMM_T_COPY, s);
+  const hipStream_t cs = beside ? p->aux : s;
+  stage_begin(p, SPGEMM_T_COPY, cs);
   CompactArgs<T> ca;
   ca.u = p->u;
   ca.cto = p->cto;
@@ -1138,10 +1144,11 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   ca.c_col = static_cast<int32_t *>(ccol);
   ca.c_val = static_cast<T *>(cval);
   if (m > 0)
-    launch_compact<T>(ca, m, S.sum_u - S.sum_u_long, npieces, s);
+    launch_compact<T>(ca, m, S.sum_u - S.sum_u_long, npieces, cs);
   else
     launch_zero(crp, 4, s);
-  stage_end(p, SPGEMM_T_COPY, s);
+  stage_end(p, SPGEMM_T_COPY, cs);
+  if (beside) join_aux(p, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     p->al.put(ccol, s);

@@ -116,12 +116,28 @@ __global__ __launch_bounds__(256) void k_wplan_scan(int64_t *bsum, int64_t nblk)
   }
 }
 
-// Row records (one thread per long row).
+// Row records (one thread per long row), and the item of a direct dense row
+// that has one.  SELF: bsum holds the raw block sums and every work-group adds
+// up those of the blocks before it (few blocks; saves k_wplan_scan).
+template <bool SELF>
 __global__ __launch_bounds__(256) void k_wplan_write(const int32_t *lrows, int64_t nlong,
                                                      const int64_t *u, int64_t n, int vbytes,
-                                                     const int64_t *bsum, WinRow *rows) {
+                                                     const int64_t *bsum, const int32_t *arp,
+                                                     WinRow *rows, WinWork *items) {
   __shared__ int64_t sm[256 / WAVE + 1];
   const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  int64_t base[5];
+  if constexpr (SELF) {
+    int64_t ps[5] = {};
+    for (int64_t b = threadIdx.x; b < static_cast<int64_t>(blockIdx.x); b += 256)
+#pragma unroll
+      for (int q = 0; q < 5; ++q) ps[q] += bsum[b * 5 + q];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) (void)block_excl_sum<256, int64_t>(ps[q], sm, base[q]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) base[q] = bsum[static_cast<int64_t>(blockIdx.x) * 5 + q];
+  }
   WinPlan p{};
   p.mode = WIN_NONE;
   int64_t ui = 0;
@@ -137,7 +153,7 @@ __global__ __launch_bounds__(256) void k_wplan_write(const int32_t *lrows, int64
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
     int64_t tot;
-    off[q] = block_excl_sum<256, int64_t>(v[q], sm, tot) + bsum[static_cast<int64_t>(blockIdx.x) * 5 + q];
+    off[q] = block_excl_sum<256, int64_t>(v[q], sm, tot) + base[q];
   }
   if (k >= nlong) return;
   WinRow r;
@@ -154,6 +170,8 @@ __global__ __launch_bounds__(256) void k_wplan_write(const int32_t *lrows, int64
   r.pbase = off[3];
   r.dslot0 = off[4];
   rows[k] = r;
+  if (p.mode == WIN_DD && p.nitem == 1)
+    items[off[0]] = WinWork{static_cast<int32_t>(k), 0, arp[row], 0};
 }
 
 // First entry of A whose products reach product q0 of its row: the entry e
@@ -188,7 +206,8 @@ template <typename First> DEVI int64_t owner_row(int64_t nlong, int64_t t, First
 
 // One thread per work unit: items (WHAT 0; e0 set for the product ranges
 // of direct dense rows), segments (WHAT 1; e0 always) or dense partial rows
-// (WHAT 2; the owning long row in slot_row).
+// (WHAT 2; the owning long row in slot_row, and its item: they are the
+// product ranges of rows that have several).
 template <int WHAT>
 __global__ __launch_bounds__(256) void k_wplan_units(const WinRow *rows, int64_t nlong,
                                                      int64_t nunits, const int32_t *arp,
@@ -202,6 +221,9 @@ __global__ __launch_bounds__(256) void k_wplan_units(const WinRow *rows, int64_t
   const WinRow r = rows[k];
   if (WHAT == 2) {
     slot_row[t] = static_cast<int32_t>(k);
+    const int64_t q = t - r.dslot0;
+    work[r.item0 + q] = WinWork{static_cast<int32_t>(k), static_cast<int32_t>(q),
+                                entry_of(arp, P, r.row, q * kWinSplit), 0};
     return;
   }
   const int32_t q = static_cast<int32_t>(t - (WHAT == 0 ? r.item0 : r.seg0));
@@ -1022,24 +1044,41 @@ __global__ __launch_bounds__(WNT) void k_wsym_g(EscArgs<T> e, int64_t n, const W
 
 // Dense partial rows of a direct dense row: OR of their bitmaps (kept in
 // the first one) and the row's count (on its first item; the others 0).
-__global__ __launch_bounds__(WNT) void k_wsym_reduce(const WinRow *rows, const int32_t *slot_row,
-                                                     int64_t nslots, int64_t n, uint32_t *dbits,
-                                                     int64_t *cnt) {
-  __shared__ int64_t red[WNT / WAVE + 1];
+constexpr int SYM_NT = 1024;
+
+__global__ __launch_bounds__(SYM_NT) void k_wsym_reduce(const WinRow *rows,
+                                                        const int32_t *slot_row, int64_t nslots,
+                                                        int64_t n, uint32_t *dbits, int64_t *cnt) {
+  constexpr int MAXW = 4096 / 32;  // words of the widest dense window
+  __shared__ int64_t red[SYM_NT / WAVE + 1];
+  __shared__ uint32_t acc[MAXW];
   const int64_t sl = blockIdx.x;
   if (sl >= nslots) return;
   const WinRow wr = rows[slot_row[sl]];
   if (sl != wr.dslot0) return;  // one work-group per row
   const int nwords = static_cast<int>((n + 31) >> 5);
-  int64_t c = 0;
-  for (int q = threadIdx.x; q < nwords; q += WNT) {
+  if (nwords > MAXW) return;  // launched only for dense windows
+  if (threadIdx.x < MAXW) acc[threadIdx.x] = 0u;
+  __syncthreads();
+  // the ranges are dealt to groups of nwords threads (the longest row has
+  // hundreds: one group with one load in flight took 90 us for 586)
+  const int ng = SYM_NT / nwords;
+  const int g = threadIdx.x / nwords, q = threadIdx.x % nwords;
+  uint32_t *bits = dbits + wr.dslot0 * static_cast<int64_t>(nwords);
+  if (g < ng) {
     uint32_t x = 0;
-    for (int32_t k = 0; k < wr.nitem; ++k) x |= dbits[(wr.dslot0 + k) * static_cast<int64_t>(nwords) + q];
-    dbits[wr.dslot0 * static_cast<int64_t>(nwords) + q] = x;
-    c += __popc(x);
+#pragma unroll 8
+    for (int32_t k = g; k < wr.nitem; k += ng) x |= bits[k * static_cast<int64_t>(nwords) + q];
+    if (x != 0u) atomicOr(&acc[q], x);
+  }
+  __syncthreads();
+  int64_t c = 0;
+  if (threadIdx.x < nwords) {
+    bits[threadIdx.x] = acc[threadIdx.x];
+    c = __popc(acc[threadIdx.x]);
   }
   int64_t tot;
-  (void)block_excl_sum<WNT, int64_t>(c, red, tot);
+  (void)block_excl_sum<SYM_NT, int64_t>(c, red, tot);
   if (threadIdx.x == 0) {
     cnt[wr.item0] = tot;
     for (int32_t k = 1; k < wr.nitem; ++k) cnt[wr.item0 + k] = 0;
@@ -1335,7 +1374,7 @@ __global__ __launch_bounds__(WNT) void k_wnum_reduce(const WinRow *rows, const i
   if (!on) return;
   const T *src = dacc + wr.dslot0 * n + c;
   T v = src[0];
-#pragma unroll 8
+#pragma unroll 32
   for (int32_t k = 1; k < wr.nitem; ++k) v = v + src[static_cast<int64_t>(k) * n];
   const int64_t dst = rowoff[wr.row] + before + o;
   c_col[dst] = static_cast<int32_t>(c);
@@ -1353,10 +1392,18 @@ void win_plan_launch(const int32_t *lrows, int64_t nlong, const int64_t *u, int6
   if (nlong <= 0) return;
   const int64_t nb = (nlong + 255) / 256;
   hipLaunchKernelGGL(k_wplan_count, dim3(nb), dim3(256), 0, s, lrows, nlong, u, n, vbytes, bsum);
-  hipLaunchKernelGGL(k_wplan_scan, dim3(1), dim3(256), 0, s, bsum, nb);
-  hipLaunchKernelGGL(k_wplan_write, dim3(nb), dim3(256), 0, s, lrows, nlong, u, n, vbytes, bsum,
-                     rows);
-  if (nitems > 0)
+  if (nb <= 1024) {
+    hipLaunchKernelGGL(k_wplan_write<true>, dim3(nb), dim3(256), 0, s, lrows, nlong, u, n, vbytes,
+                       bsum, arp, rows, items);
+  } else {
+    hipLaunchKernelGGL(k_wplan_scan, dim3(1), dim3(256), 0, s, bsum, nb);
+    hipLaunchKernelGGL(k_wplan_write<false>, dim3(nb), dim3(256), 0, s, lrows, nlong, u, n, vbytes,
+                       bsum, arp, rows, items);
+  }
+  // a dense window: every row's items are written with its record or with
+  // its dense partial rows
+  const bool dense = n <= (int64_t(1) << win_dense_log(vbytes));
+  if (nitems > 0 && !dense)
     hipLaunchKernelGGL(k_wplan_units<0>, dim3((nitems + 255) / 256), dim3(256), 0, s, rows, nlong,
                        nitems, arp, P, items, static_cast<int32_t *>(nullptr));
   if (nsegs > 0)
@@ -1364,7 +1411,7 @@ void win_plan_launch(const int32_t *lrows, int64_t nlong, const int64_t *u, int6
                        nsegs, arp, P, segs, static_cast<int32_t *>(nullptr));
   if (nslots > 0)
     hipLaunchKernelGGL(k_wplan_units<2>, dim3((nslots + 255) / 256), dim3(256), 0, s, rows, nlong,
-                       nslots, arp, P, static_cast<WinWork *>(nullptr), slot_row);
+                       nslots, arp, P, items, slot_row);
 }
 
 template <typename T>
@@ -1385,7 +1432,6 @@ void win_symbolic(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinW
                   const int32_t *slot_row, int64_t nslots, uint32_t *list_ids,
                   uint32_t *list_count, uint32_t *dbits, int64_t *cnt, hipStream_t s) {
   if (nitems <= 0) return;
-  launch_zero(list_count, sizeof(uint32_t), s);
   WinArgsW<T> a{};
   a.e = e;
   a.n = n;
@@ -1401,10 +1447,11 @@ void win_symbolic(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinW
     hipLaunchKernelGGL((k_wdense<T, false>), dim3(nitems), dim3(WAVE), 0, s, a, dbits,
                        static_cast<T *>(nullptr));
     if (nslots > 0)
-      hipLaunchKernelGGL(k_wsym_reduce, dim3(nslots), dim3(WNT), 0, s, rows, slot_row, nslots, n,
-                         dbits, cnt);
+      hipLaunchKernelGGL(k_wsym_reduce, dim3(nslots), dim3(SYM_NT), 0, s, rows, slot_row, nslots,
+                         n, dbits, cnt);
     return;
   }
+  launch_zero(list_count, sizeof(uint32_t), s);
   hipLaunchKernelGGL((k_witem<T, false>), dim3(nitems), dim3(WAVE), 0, s, a);
   hipLaunchKernelGGL((k_wsym_g<T>), dim3(kListGrid), dim3(WNT), 0, s, e, n, rows, items, table,
                      pkey, WinList{list_ids, list_count}, cnt);
