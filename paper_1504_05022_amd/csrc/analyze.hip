@@ -651,16 +651,19 @@ void launch_set_pool(Pool *dst, Pool value, hipStream_t s) {
 // The status of compute, by one thread: to the host's slot if there is one
 // (the words, then the token that announces them), else to `st`.
 struct StatusEnd {
-  const Pool *pool;
+  const Pool *pool;          // nullptr: no merge method
+  const LongCounters *cnt;
   ComputeStatus *st;
   HostSlot *slot;
   uint64_t token;
   DEVI void operator()(int64_t nnz) const {
     ComputeStatus v;
     v.nnz_c = nnz;
-    v.fail_count = pool->fail_count;
-    v.fail2 = pool->fail2;
-    v.pool_used = pool->used;
+    v.fail_count = pool ? pool->fail_count : 0u;
+    v.fail2 = pool ? pool->fail2 : 0u;
+    v.pool_used = pool ? pool->used : 0ull;
+    v.left = cnt ? cnt->l3 : 0u;
+    v.pad = 0u;
     if (!slot) {
       *st = v;
       return;
@@ -677,15 +680,17 @@ struct StatusEnd {
 
 __global__ void k_status(const int64_t *rowoff, int64_t m, StatusEnd end) { end(rowoff[m]); }
 
-void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, ComputeStatus *st,
-                   HostSlot *slot, uint64_t token, hipStream_t s) {
-  hipLaunchKernelGGL(k_status, dim3(1), dim3(1), 0, s, rowoff, m, StatusEnd{pool, st, slot, token});
+void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, const LongCounters *cnt,
+                   ComputeStatus *st, HostSlot *slot, uint64_t token, hipStream_t s) {
+  hipLaunchKernelGGL(k_status, dim3(1), dim3(1), 0, s, rowoff, m,
+                     StatusEnd{pool, cnt, st, slot, token});
 }
 
 void scan_rows_status(const int64_t *v, int64_t n, int64_t *out, int64_t *part, const Pool *pool,
-                      ComputeStatus *st, HostSlot *slot, uint64_t token, hipStream_t s) {
+                      const LongCounters *cnt, ComputeStatus *st, HostSlot *slot, uint64_t token,
+                      hipStream_t s) {
   const I64Fn f{v};
-  scan_with(f, f, f, StatusEnd{pool, st, slot, token}, n, out, part, s);
+  scan_with(f, f, f, StatusEnd{pool, cnt, st, slot, token}, n, out, part, s);
 }
 
 }  // namespace spg

@@ -885,14 +885,15 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   la.rowoff = p->rowoff;
   la.pscan = pscan;
   const bool spill_expected = S.spill_bound > 0 || p->opt.pool_entries > 0;
-  auto new_pool = [&](int64_t entries, unsigned long long used) -> int {
+  // (set: tell the device; the first pool is set with the long-row table)
+  auto new_pool = [&](int64_t entries, unsigned long long used, bool set = true) -> int {
     void *chunk = p->al.get(pool_chunk_bytes(entries, sizeof(T)), s);
     if (!chunk) return fail(SPGEMM_ENOMEM, "long-row pool allocation failed");
     p->pool_chunks.push_back(chunk);
     p->pool_bytes += alloc_size(pool_chunk_bytes(entries, sizeof(T)));
     *p->hpool = pool_view(chunk, entries);
     p->hpool->used = used;
-    launch_set_pool(p->dpool, *p->hpool, s);
+    if (set) launch_set_pool(p->dpool, *p->hpool, s);
     return SPGEMM_OK;
   };
   uint64_t token = 0;
@@ -905,20 +906,23 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   };
   auto read_status = [&]() -> int {
     slot = take_slot(1, &token);
-    launch_status(p->rowoff, m, p->dpool, p->dstat, slot, token, s);
+    launch_status(p->rowoff, m, p->dpool, lcnt, p->dstat, slot, token, s);
     return wait_status();
   };
   // row pointers of C, and the status with their total
   auto scan_rows = [&]() {
     slot = take_slot(1, &token);
-    scan_rows_status(p->rownnz, m, p->rowoff, p->part, p->dpool, p->dstat, slot, token, s);
+    scan_rows_status(p->rownnz, m, p->rowoff, p->part, legacy ? p->dpool : nullptr,
+                     legacy ? lcnt : nullptr, p->dstat, slot, token, s);
+    // where every piece goes in its row: not needed before C is allocated
+    if (legacy) scan_piece_counts(pieces, npieces, pscan, ppart, s);
   };
   auto finish_long = [&]() {
     // long-row sizes from their pieces
-    scan_piece_counts(pieces, npieces, pscan, ppart, s);
-    launch_long_rownnz(lrows, nlong, pscan, p->rownnz, s);
+    launch_long_rownnz(lrows, nlong, pieces, p->rownnz, s);
   };
   int rc;
+  bool combine_rest = false;  // the kernels of large pieces are still to be launched
   if (use_win) {
     // window method: plan, partition, symbolic pass, long-row sizes
     stage_begin(p, SPGEMM_T_LONG, s);
@@ -940,10 +944,11 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     pool_entries = p->opt.pool_entries
                        ? p->opt.pool_entries
                        : S.pool_single + 3 * S.spill_bound + 65536;
-    if ((rc = new_pool(pool_entries, 0)) != SPGEMM_OK) return rc;
+    if ((rc = new_pool(pool_entries, 0, false)) != SPGEMM_OK) return rc;
     launch_long_table(p->binlist, S.bin_off[LONG_BIN], nlong, p->u, p->n, p->lp, lrows, nitems,
-                      items, states, partials, npieces, piece_lrow, A->row_ptr, p->P, lt_tmp, s);
-    launch_cstate_init(cstates, npieces, lcnt, s);
+                      items, states, partials, npieces, piece_lrow, cstates, lcnt, p->dpool,
+                      *p->hpool, A->row_ptr, p->P, lt_tmp, s);
+    const int64_t item_most = long_item_most(I.max_u, p->lp);
     // phase 1: every segment; one wavefront, else one work-group tile, else
     // the level-1 merge method
     stage_begin(p, SPGEMM_T_LONG, s);
@@ -951,9 +956,10 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     launch_long_wave<T>(la, nitems, s);
     stage_end(p, SPGEMM_T_LONG_WAVE, s);
     if ((rc = launch_short_rows()) != SPGEMM_OK) return rc;
-    launch_long_wave_large<T>(la, nitems, s);
-    launch_long_oneshot<T>(la, nitems, s);
-    if (launch_long<T>(la, nitems, p->l1cap, s))
+    // the kernels of larger items only where the plan can have them
+    if (item_most > kWaveTile / 2) launch_long_wave_large<T>(la, nitems, s);
+    if (item_most > kWaveTile) launch_long_oneshot<T>(la, nitems, s);
+    if (item_most > kOneShot && launch_long<T>(la, nitems, p->l1cap, s))
       return fail(SPGEMM_EINVAL, "no long-row kernel for this l1_cap");
     I.long_launches++;
     stage_end(p, SPGEMM_T_LONG, s);
@@ -989,9 +995,10 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
       launch_combine_wave<T>(la, npieces, s);
       stage_end(p, SPGEMM_T_COMBINE_WAVE, s);
       launch_combine_wave_large<T>(la, npieces, s);
-      launch_combine_oneshot<T>(la, npieces, s);
-      launch_combine<T>(la, npieces, s);
       stage_end(p, SPGEMM_T_COMBINE, s);
+      // pieces above a wavefront's tile are rare: the status says whether
+      // there are any, and only then the kernels for them are launched
+      combine_rest = true;
     }
     finish_long();
   }
@@ -1018,6 +1025,16 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
       if ((rc = wait_status()) != SPGEMM_OK) return rc;
       const unsigned int nf1 = legacy ? p->hstat->fail_count : 0u;
       const unsigned int nf2 = legacy ? p->hstat->fail2 : 0u;
+      if (combine_rest && nf1 == 0) {
+        combine_rest = false;
+        if (p->hstat->left > 0) {
+          launch_combine_oneshot<T>(la, npieces, s);
+          launch_combine<T>(la, npieces, s);
+          finish_long();
+          scan_rows();
+          continue;
+        }
+      }
       if (nf1 == 0 && nf2 == 0) break;
       if (++I.realloc_rounds > 64) return fail(SPGEMM_ENOMEM, "long-row pool keeps overflowing");
       pool_entries *= 2;
@@ -1032,6 +1049,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
         la.work = nullptr;
         la.fail_list = fl;
         launch_cstate_init(cstates, npieces, lcnt, s);
+        combine_rest = false;
         la.fail_list2 = f2;
         if (direct) {
           launch_piece_count<T>(la, npieces, s);

@@ -299,6 +299,8 @@ struct ComputeStatus {
   unsigned int fail_count;
   unsigned int fail2;
   unsigned long long pool_used;
+  unsigned int left;  // combine pieces too large for one wavefront
+  unsigned int pad;
 };
 
 // ----------------------------------------------------------------- scans
@@ -446,11 +448,22 @@ bool long_direct_ok(const LongParams &lp, int64_t ncols);
 template <typename T>
 void launch_piece_count(const LongArgs<T> &a, int64_t npieces, hipStream_t s);
 
-// Long-row table, work items and piece map (three launches).
+// Largest work item of the plan's long rows.
+inline int64_t long_item_most(int64_t max_u, const LongParams &lp) {
+  if (lp.segp < 0) return max_u;
+  const int64_t need = (max_u + lp.maxs - 1) / lp.maxs;
+  const int64_t seg = lp.segp > need ? lp.segp : need;
+  const int64_t most = lp.single > seg ? lp.single : seg;
+  return most < max_u ? most : max_u;
+}
+
+// Long-row table, work items, piece map, empty checkpoints of the pieces,
+// list counters and pool (three launches).
 void launch_long_table(const int32_t *binlist, int64_t off, int64_t nlong, const int64_t *u,
                        int64_t ncols, LongParams lp, LongRow *lrows, int64_t nitems,
                        LongItem *items, LongState *state, Seq *partials, int64_t npieces,
-                       int32_t *piece_lrow, const int32_t *arp, const int64_t *P, int64_t *tmp,
+                       int32_t *piece_lrow, LongState *cstate, LongCounters *cnt, Pool *pool,
+                       Pool value, const int32_t *arp, const int64_t *P, int64_t *tmp,
                        hipStream_t s);
 void launch_cstate_init(LongState *state, int64_t n, LongCounters *cnt, hipStream_t s);
 int combine_maxs();
@@ -480,9 +493,9 @@ void launch_combine_oneshot(const LongArgs<T> &a, int64_t npieces, hipStream_t s
 template <typename T>
 int launch_combine(const LongArgs<T> &a, int64_t npieces, hipStream_t s);
 int long_l1cap_default(int dtype_bytes);
-// Output sizes of the long rows from their pieces: piece scan -> rownnz.
-void launch_long_rownnz(const LongRow *lrows, int64_t nlong, const int64_t *pscan,
-                        int64_t *rownnz, hipStream_t s);
+// Output sizes of the long rows from their pieces.
+void launch_long_rownnz(const LongRow *lrows, int64_t nlong, const Piece *pieces, int64_t *rownnz,
+                        hipStream_t s);
 void scan_piece_counts(const Piece *pieces, int64_t n, int64_t *out, int64_t *part,
                        hipStream_t s);
 
@@ -574,12 +587,14 @@ void launch_grad_b(const int64_t *tptr, const int32_t *trow, const int32_t *tpos
                    const int32_t *ccol, const T *dc, T *dB, hipStream_t s);
 void launch_zero(void *p, size_t bytes, hipStream_t s);
 void launch_set_pool(Pool *dst, Pool value, hipStream_t s);
-// Status of compute: to `slot` with `token`, or to `st` if there is no slot.
-void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, ComputeStatus *st,
-                   HostSlot *slot, uint64_t token, hipStream_t s);
+// Status of compute (pool, cnt: nullptr without the merge method): to `slot`
+// with `token`, or to `st` if there is no slot.
+void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, const LongCounters *cnt,
+                   ComputeStatus *st, HostSlot *slot, uint64_t token, hipStream_t s);
 // The scan of the row sizes, with the status at its end.
 void scan_rows_status(const int64_t *v, int64_t n, int64_t *out, int64_t *part, const Pool *pool,
-                      ComputeStatus *st, HostSlot *slot, uint64_t token, hipStream_t s);
+                      const LongCounters *cnt, ComputeStatus *st, HostSlot *slot, uint64_t token,
+                      hipStream_t s);
 
 // Access to a plan's device arrays (defined with the plan in api.hip).
 const int64_t *plan_rowoff(spgemm_plan p);

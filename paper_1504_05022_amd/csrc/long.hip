@@ -2144,27 +2144,66 @@ __global__ __launch_bounds__(256) void k_lt_write(const int32_t *binlist, int64_
   lrows[t] = lr;
 }
 
-// Work items (one thread each): product range, first entry of A's row that
-// reaches it, an empty checkpoint and an empty partial.
-__global__ __launch_bounds__(256) void k_lt_items(const LongRow *lrows, int64_t nlong,
-                                                  int64_t nitems, const int32_t *arp,
-                                                  const int64_t *P, LongItem *items,
-                                                  LongState *state, Seq *partials) {
-  const int64_t x = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (x >= nitems) return;
-  int64_t lo = 0, hi = nlong;  // the row whose items include x
+// Checkpoint at the start of its work, with an empty global sequence.
+DEVI LongState long_state(int64_t pos) {
+  LongState st;
+  st.pos = pos;
+  st.gcnt = 0;
+  st.gcap = 0;
+  st.gcol = nullptr;
+  st.gval = nullptr;
+  st.scap = 0;
+  st.scol = nullptr;
+  st.sval = nullptr;
+  st.status = 0;
+  st.pad = 0;
+  return st;
+}
+
+// The long row that owns unit x of a list whose per-row starts are
+// first(row) (non-decreasing).
+template <typename First> DEVI int64_t lt_owner(int64_t nlong, int64_t x, First first) {
+  int64_t lo = 0, hi = nlong;
   while (hi - lo > 1) {
     const int64_t mid = (lo + hi) >> 1;
-    if (lrows[mid].item0 <= x)
+    if (first(mid) <= x)
       lo = mid;
     else
       hi = mid;
   }
+  return lo;
+}
+
+// One thread per work item (product range, first entry of A's row that
+// reaches it, an empty checkpoint and an empty partial), then one per output
+// piece (its row, an empty checkpoint); the first threads also clear the list
+// counters and set the pool.
+__global__ __launch_bounds__(256) void k_lt_units(const LongRow *lrows, int64_t nlong,
+                                                  int64_t nitems, int64_t npieces,
+                                                  const int32_t *arp, const int64_t *P,
+                                                  LongItem *items, LongState *state,
+                                                  Seq *partials, int32_t *piece_lrow,
+                                                  LongState *cstate, LongCounters *cnt, Pool *pool,
+                                                  Pool value) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (t == 0) {
+    *cnt = LongCounters{};
+    *pool = value;
+  }
+  if (t >= nitems) {
+    const int64_t x = t - nitems;
+    if (x >= npieces) return;
+    piece_lrow[x] =
+        static_cast<int32_t>(lt_owner(nlong, x, [&](int64_t r) { return lrows[r].piece0; }));
+    cstate[x] = long_state(0);
+    return;
+  }
+  const int64_t lo = lt_owner(nlong, t, [&](int64_t r) { return lrows[r].item0; });
   const LongRow lr = lrows[lo];
   LongItem it;
   it.row = lr.row;
   it.lrow = static_cast<int32_t>(lo);
-  it.p0 = (x - lr.item0) * lr.segp;
+  it.p0 = (t - lr.item0) * lr.segp;
   it.p1 = it.p0 + lr.segp < lr.u ? it.p0 + lr.segp : lr.u;
   {
     const int32_t e0 = arp[lr.row], e1 = arp[lr.row + 1];
@@ -2180,46 +2219,16 @@ __global__ __launch_bounds__(256) void k_lt_items(const LongRow *lrows, int64_t 
     it.e_first = a;
   }
   it.pad = 0;
-  items[x] = it;
-  LongState st;
-  st.pos = it.p0;
-  st.gcnt = 0;
-  st.gcap = 0;
-  st.gcol = nullptr;
-  st.gval = nullptr;
-  st.scap = 0;
-  st.scol = nullptr;
-  st.sval = nullptr;
-  st.status = 0;
-  st.pad = 0;
-  state[x] = st;
-  Seq q;
-  q.col = nullptr;
-  q.val = nullptr;
-  q.cnt = 0;
-  partials[x] = q;
-}
-
-// Row of every output piece (one thread each).
-__global__ __launch_bounds__(256) void k_lt_pieces(const LongRow *lrows, int64_t nlong,
-                                                   int64_t npieces, int32_t *piece_lrow) {
-  const int64_t x = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (x >= npieces) return;
-  int64_t lo = 0, hi = nlong;
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (lrows[mid].piece0 <= x)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  piece_lrow[x] = static_cast<int32_t>(lo);
+  items[t] = it;
+  state[t] = long_state(it.p0);
+  partials[t] = Seq{nullptr, nullptr, 0};
 }
 
 void launch_long_table(const int32_t *binlist, int64_t off, int64_t nlong, const int64_t *u,
                        int64_t ncols, LongParams lp, LongRow *lrows, int64_t nitems,
                        LongItem *items, LongState *state, Seq *partials, int64_t npieces,
-                       int32_t *piece_lrow, const int32_t *arp, const int64_t *P, int64_t *tmp,
+                       int32_t *piece_lrow, LongState *cstate, LongCounters *cnt, Pool *pool,
+                       Pool value, const int32_t *arp, const int64_t *P, int64_t *tmp,
                        hipStream_t s) {
   if (nlong <= 0) return;
   const int64_t nb = (nlong + 255) / 256;
@@ -2233,12 +2242,9 @@ void launch_long_table(const int32_t *binlist, int64_t off, int64_t nlong, const
     hipLaunchKernelGGL(k_lt_write<false>, dim3(nb), dim3(256), 0, s, binlist, off, nlong, u,
                        ncols, lp, tmp, lrows);
   }
-  if (nitems > 0)
-    hipLaunchKernelGGL(k_lt_items, dim3((nitems + 255) / 256), dim3(256), 0, s, lrows, nlong,
-                       nitems, arp, P, items, state, partials);
-  if (npieces > 0)
-    hipLaunchKernelGGL(k_lt_pieces, dim3((npieces + 255) / 256), dim3(256), 0, s, lrows, nlong,
-                       npieces, piece_lrow);
+  hipLaunchKernelGGL(k_lt_units, dim3((nitems + npieces + 256) / 256), dim3(256), 0, s, lrows,
+                     nlong, nitems, npieces, arp, P, items, state, partials, piece_lrow, cstate, cnt,
+                     pool, value);
 }
 
 // Checkpoints of the combine pieces: start of the stream, empty G; and the
@@ -2247,18 +2253,7 @@ __global__ void k_cstate_init(LongState *state, int64_t n, unsigned int *cnt, in
   const int64_t x = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (x < ncnt) cnt[x] = 0u;
   if (x >= n) return;
-  LongState s;
-  s.pos = 0;
-  s.gcnt = 0;
-  s.gcap = 0;
-  s.gcol = nullptr;
-  s.gval = nullptr;
-  s.scap = 0;
-  s.scol = nullptr;
-  s.sval = nullptr;
-  s.status = 0;
-  s.pad = 0;
-  state[x] = s;
+  state[x] = long_state(0);
 }
 
 void launch_cstate_init(LongState *state, int64_t n, LongCounters *cnt, hipStream_t s) {
@@ -2269,20 +2264,25 @@ void launch_cstate_init(LongState *state, int64_t n, LongCounters *cnt, hipStrea
                      reinterpret_cast<unsigned int *>(cnt), ncnt);
 }
 
-// rownnz of long rows = sum of their pieces (from the exclusive piece scan)
-__global__ void k_long_rownnz(const LongRow *lrows, int64_t nlong, const int64_t *pscan,
-                              int64_t *rownnz) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= nlong) return;
+// Sizes of the long rows: one wavefront adds up the pieces of each.  (Their
+// scan, which only the copy needs, is left for the time in which the host
+// allocates C.)
+__global__ __launch_bounds__(256) void k_long_rownnz(const LongRow *lrows, int64_t nlong,
+                                                     const Piece *pieces, int64_t *rownnz) {
+  const int64_t t = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / WAVE;
+  if (t >= nlong) return;  // uniform across the wavefront
   const LongRow lr = lrows[t];
-  rownnz[lr.row] = pscan[lr.piece0 + lr.npiece] - pscan[lr.piece0];
+  int64_t c = 0;
+  for (int32_t k = lane(); k < lr.npiece; k += WAVE) c += pieces[lr.piece0 + k].cnt;
+  c = group_last<WAVE>(group_incl_sum<WAVE>(c));
+  if (lane() == 0) rownnz[lr.row] = c;
 }
 
-void launch_long_rownnz(const LongRow *lrows, int64_t nlong, const int64_t *pscan,
-                        int64_t *rownnz, hipStream_t s) {
+void launch_long_rownnz(const LongRow *lrows, int64_t nlong, const Piece *pieces, int64_t *rownnz,
+                        hipStream_t s) {
   if (nlong <= 0) return;
-  hipLaunchKernelGGL(k_long_rownnz, dim3((nlong + 255) / 256), dim3(256), 0, s, lrows, nlong,
-                     pscan, rownnz);
+  hipLaunchKernelGGL(k_long_rownnz, dim3((nlong * WAVE + 255) / 256), dim3(256), 0, s, lrows,
+                     nlong, pieces, rownnz);
 }
 
 // ------------------------------------------------------------ launchers

@@ -137,3 +137,21 @@ def test_dense_windows_by_b_row_length(dtype, most):
     deg = [d for d in (5, 63, 64, 65, 127, 130, 199, 200) for _ in range(6)]
     A = _ragged(rng, len(deg), deg, 200, dtype)
     check(A, B, exact=bool(np.sum(lens) <= 16384))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("u", [(1025, 600), (3000, 1025, 4000), (40000, 4100, 520, 3000)])
+def test_long_rows_in_few_columns(dtype, u):
+    """Cut rows of C whose products share one range of columns: streams above
+    a wavefront's 1024 entries, up to and above a work-group's 4096, beside
+    rows that have none."""
+    from test_gpu_parity import check
+    rng = np.random.default_rng(len(u))
+    n, width = 20000, 20
+    deg = [x // width for x in u] + [3]
+    k = max(deg)
+    lens = [width] * k
+    B = _ragged(rng, k, lens, 48, dtype)
+    B = S.Csr(k, n, B.row_ptr, B.col_idx + 77, B.val)
+    A = _ragged(rng, len(deg), deg, k, dtype)
+    check(A, B)
