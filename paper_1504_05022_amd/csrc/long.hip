@@ -1568,10 +1568,6 @@ __global__ __launch_bounds__(NT) void k_combine1(LongArgs<T> a) {
 constexpr int WAVE_NT = 256;  // four independent wavefronts per work-group
 constexpr int WAVE_K = kWaveTile / WAVE;
 
-// Element l of a wavefront tile lives at (l mod K) * 64 + l / K (lanes touch
-// consecutive words).
-template <int K> DEVI int wix(int l) { return (l & (K - 1)) * WAVE + (l >> Log2<K>::v); }
-
 // Rank r of a sorted wavefront tile lives at r + r / 64: lane-blocked writes
 // (lane p, ranks p*K ..) and lane-striped reads (lane p, ranks k*64 + p)
 // are both free of LDS bank conflicts.  A tile needs U + U / 64 slots.
@@ -1582,11 +1578,30 @@ DEVI int wpad(int r) { return r + (r >> 6); }
 // and need every resident wavefront they can get.
 template <int K> constexpr int wave_occupancy() { return K <= 8 ? 6 : 3; }
 
-template <typename T, int K, typename Key>
-DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
-                    unsigned char *lds_a, T *lds_b) {
+// The product l of a tile belongs to the run (of products of one b_j* row, or
+// of stream entries of one segment) numbered by the run starts in 1 .. l: a
+// count of bits of the mask hd.  Two VALU instructions per product and no
+// barrier, where a max-scan over the tile and a hand-over of the resolved
+// index through LDS took about twenty and two.
+template <int K, typename F> DEVI void each_run(const uint32_t *hd, F f) {
+  int below = 0;
+#pragma unroll
+  for (int kk = 0; kk < K; ++kk) {
+    const uint32_t lo = hd[2 * kk], hi = hd[2 * kk + 1];
+    f(kk, below + static_cast<int>(
+                      __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))));
+    below += __popc(lo) + __popc(hi);
+  }
+}
+
+// The buffers are laid out for at least K products per lane; hd has 2 * KL
+// words.
+template <typename T, int K, int KL, typename Key>
+DEVI void wave_item_k(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
+                      unsigned char *lds_a, T *lds_b, uint32_t *hd) {
   constexpr int U = WAVE * K;
-  constexpr int LOGU = Log2<U>::v;
+  constexpr int LOGU = ceil_log2(U);
+  constexpr Key LMASK = (Key(1) << LOGU) - 1;
   constexpr Key KMAX = KeyMax<Key>::v;
   const int pos = lane();
   int32_t *rs = reinterpret_cast<int32_t *>(lds_a);
@@ -1600,12 +1615,13 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
   const int32_t e1 = a.e.arp[i + 1];
   const int64_t pbase = a.e.P[a.e.arp[i]];
 
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) rs[kk * WAVE + pos] = -1;
+  if (pos < 2 * KL) hd[pos] = 0u;
   wave_sync();
-  // run starts of the b_j* rows that overlap [p0, p1); the loads of a
-  // chunk of 64 entries are issued together (clamped, not branched on)
+  // runs of the b_j* rows that overlap [p0, p1): the B index of product l less
+  // l, and a_ij; the loads of a chunk of 64 entries are issued together
+  // (clamped, not branched on)
   const GLOBAL_AS int64_t *gP = as_global(a.e.P);
+  int nrun = 0;
   for (int32_t e0 = item.e_first; e0 < e1; e0 += WAVE) {
     const int32_t e = e0 + pos;
     const bool in = e < e1;
@@ -1614,54 +1630,17 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
     const int64_t s1 = gP[ec + 1] - pbase;
     const int32_t b0 = as_global(a.e.bst)[ec];
     const T av = as_global(a.e.aval)[ec];
-    if (in && s0 < p1 && s1 > p0 && s1 > s0) {
-      int64_t ls = s0 - p0;
-      int32_t off = 0;
-      if (ls < 0) {
-        off = static_cast<int32_t>(-ls);
-        ls = 0;
-      }
-      rs[wix<K>(static_cast<int>(ls))] = b0 + off;
-      ra[wix<K>(static_cast<int>(ls))] = av;
+    const bool some = in && s0 < p1 && s1 > p0 && s1 > s0;
+    const uint64_t mine = __ballot(some);
+    if (some) {
+      const int r = nrun + __popcll(mine & ((1ull << pos) - 1ull));
+      const int32_t q0 = static_cast<int32_t>(s0 - p0);  // negative: began before p0
+      rs[r] = b0 - q0;
+      ra[r] = av;
+      if (q0 > 0) atomicOr(&hd[(q0 - 1) >> 5], 1u << ((q0 - 1) & 31));
     }
+    nrun += __popcll(mine);
     if (!__any(in && s1 < p1)) break;  // the next chunk starts at or after p1
-  }
-  wave_sync();
-  int st[K];
-  int run = -1;
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) {
-    const int l = pos * K + kk;
-    const int f = (l < tn && rs[wix<K>(l)] >= 0) ? l : -1;
-    run = max(run, f);
-    st[kk] = run;
-  }
-  const int incl = group_incl_max<WAVE>(run);
-  int prev = wave_shr1(incl, -1);
-  if (pos == 0) prev = -1;
-  // B index and a_ij of every product, resolved in lane-blocked order and
-  // handed over through LDS so that consecutive lanes gather consecutive
-  // products (coalesced loads along each b_j* row)
-  int32_t gbx[K];
-  T gav[K];
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) {
-    const int l = pos * K + kk;
-    const int s0 = max(prev, st[kk]);
-    const bool ok = l < tn && s0 >= 0;
-    gbx[kk] = ok ? rs[wix<K>(s0)] + (l - s0) : 0;
-    gav[kk] = ok ? ra[wix<K>(s0)] : T(0);
-  }
-  int32_t *gb = rs;  // product l at gb[l] / ga[l]
-  T *ga = ra;
-  wave_sync();
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) {
-    const int l = pos * K + kk;
-    if (l < tn) {
-      gb[l] = gbx[kk];
-      ga[l] = gav[kk];
-    }
   }
   wave_sync();
   // every load of the tile is issued before any is used: positions past
@@ -1669,15 +1648,14 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
   // then ignored
   int32_t bc[K];
   T bv[K], av[K];
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) {
+  each_run<K>(hd, [&](int kk, int r) {
     const int l = kk * WAVE + pos;
-    const int32_t g = gb[l];
+    const int32_t g = rs[r] + l;
     const int32_t bidx = l < tn ? g : 0;
-    av[kk] = ga[l];
+    av[kk] = ra[r];
     bc[kk] = as_global(a.e.bcol)[bidx];
     bv[kk] = as_global(a.e.bval)[bidx];
-  }
+  });
   Key key[K];
   T prod[K];
 #pragma unroll
@@ -1687,7 +1665,7 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
     prod[kk] = ok ? av[kk] * bv[kk] : T(0);
     key[kk] = ok ? ((static_cast<Key>(bc[kk]) << LOGU) | static_cast<Key>(l)) : KMAX;
   }
-  wave_sync();  // pv takes the place of ga
+  wave_sync();  // pv takes the place of ra, the keys that of rs
 #pragma unroll
   for (int kk = 0; kk < K; ++kk) {
     const int l = kk * WAVE + pos;
@@ -1705,7 +1683,6 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
     if (l + 1 < tn && !(key[kk] < next)) ordered = false;
   }
   if (__all(ordered)) {
-    wave_sync();  // gb is dead
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) sk[wpad(kk * WAVE + pos)] = key[kk];
     wave_sync();
@@ -1740,7 +1717,7 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
       krs[kk] = r < tn ? kv : KMAX;
     }
 #pragma unroll
-    for (int kk = 0; kk < K; ++kk) vrs[kk] = pv[static_cast<int>(krs[kk] & (U - 1))];
+    for (int kk = 0; kk < K; ++kk) vrs[kk] = pv[static_cast<int>((kk * WAVE + pos < tn ? krs[kk] : Key(0)) & LMASK)];
     Key carry = 0;  // key of the rank before this pass's first
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
@@ -1799,6 +1776,19 @@ DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
   }
 }
 
+// A one-item row of the second pass that leaves a quarter or more of the tile
+// unused takes fewer products per lane (every step costs in proportion to K).
+template <typename T, int K, typename Key>
+DEVI void wave_item(LongArgs<T> &a, const int32_t item_id, const LongItem &item,
+                    unsigned char *lds_a, T *lds_b, uint32_t *hd) {
+  if constexpr (K == 16 && sizeof(Key) == 4) {
+    const int tn = static_cast<int>(item.p1 - item.p0);
+    if (tn <= WAVE * 10) return wave_item_k<T, 10, K, Key>(a, item_id, item, lds_a, lds_b, hd);
+    if (tn <= WAVE * 12) return wave_item_k<T, 12, K, Key>(a, item_id, item, lds_a, lds_b, hd);
+  }
+  wave_item_k<T, K, K, Key>(a, item_id, item, lds_a, lds_b, hd);
+}
+
 // Every item (in_list == nullptr), or the listed ones in a grid-stride
 // loop; items above 64 K products go to out_list.
 template <typename T, typename Key, int K>
@@ -1813,6 +1803,7 @@ void k_long_w(LongArgs<T> a, int64_t nitems,
   constexpr int KB = sizeof(Key) > 4 ? static_cast<int>(sizeof(Key)) : 4;
   __shared__ __align__(16) unsigned char s_a[NWV][(U + U / WAVE) * KB];
   __shared__ __align__(16) T s_b[NWV][U];
+  __shared__ uint32_t s_m[NWV][U / 32];
   // wave-uniform (so item and row records are read through the scalar cache)
   const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / WAVE));
   const int64_t id0 = xcd_block_id<16>() * NWV + w;
@@ -1826,71 +1817,36 @@ void k_long_w(LongArgs<T> a, int64_t nitems,
       if (lane() == 0) out_list[atomicAdd(out_cnt, 1u)] = static_cast<unsigned int>(id);
       continue;
     }
-    wave_item<T, K, Key>(a, id, item, s_a[w], s_b[w]);
+    wave_item<T, K, Key>(a, id, item, s_a[w], s_b[w], s_m[w]);
   }
 }
 
 // The gather, sort, fold and output of a piece whose stream (tn entries,
-// at most WAVE * K) the segment table of wave_piece describes: seg_at in
-// lds_a, tbase in lds_b.
+// at most WAVE * K) the segment table of wave_piece describes: per non-empty
+// segment the partial-buffer index of stream index 0 in lds_a, the mask of
+// their starts in hd.
 template <typename T, int K, typename Key>
 DEVI void piece_body(LongArgs<T> &a, const int32_t pid, const LongRow &lr, const int32_t lri,
                      const int32_t c0, const int tn, const int64_t E, const int64_t obase,
-                     unsigned char *lds_a, T *lds_b) {
+                     unsigned char *lds_a, T *lds_b, const uint32_t *hd) {
   constexpr int U = WAVE * K;
-  constexpr int LOGU = Log2<U>::v;
+  constexpr int LOGU = ceil_log2(U);
   constexpr Key KMAX = KeyMax<Key>::v;
   const int pos = lane();
-  const int32_t *seg_at = reinterpret_cast<const int32_t *>(lds_a);
-  const int32_t *tbase = reinterpret_cast<const int32_t *>(lds_b);
+  const int32_t *tb = reinterpret_cast<const int32_t *>(lds_a);
   const int32_t *pcol = a.pcol + lr.pbase;
   const T *pval = a.pval + lr.pbase;
-  // partial-buffer index of every stream entry: the segment is the last one
-  // starting at or before it (a max-scan in lane-blocked order), handed over
-  // through LDS so that the loads below read consecutive entries with
-  // consecutive lanes
-  int32_t gix[K];
-  {
-    int run = -1;
-    int sgk[K];
-#pragma unroll
-    for (int kk = 0; kk < K; ++kk) {
-      const int l = pos * K + kk;
-      const int v = seg_at[l];
-      run = max(run, l < tn ? v : -1);
-      sgk[kk] = run;
-    }
-    const int inc = group_incl_max<WAVE>(run);
-    int prev = wave_shr1(inc, -1);
-    if (pos == 0) prev = -1;
-#pragma unroll
-    for (int kk = 0; kk < K; ++kk) {
-      const int l = pos * K + kk;
-      const int sg = max(prev, sgk[kk]);
-      const int32_t tb = tbase[sg > 0 ? sg : 0];
-      gix[kk] = l < tn ? tb + l : 0;
-    }
-  }
-  int32_t *gi = reinterpret_cast<int32_t *>(lds_a);
-  wave_sync();  // the segment table is dead from here on
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) {
-    const int l = pos * K + kk;
-    if (l < tn) gi[l] = gix[kk];
-  }
-  wave_sync();
   // every load is issued before any is used (entries past the end reload
   // entry 0 and are ignored)
   int32_t cv[K];
   T vv[K];
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) {
+  each_run<K>(hd, [&](int kk, int r) {
     const int l = kk * WAVE + pos;
-    const int32_t g = gi[l];
+    const int32_t g = tb[r] + l;
     const int32_t idx = l < tn ? g : 0;
     cv[kk] = as_global(pcol)[idx];
     vv[kk] = as_global(pval)[idx];
-  }
+  });
   Key key[K];
   T *pv = lds_b;
 #pragma unroll
@@ -1903,7 +1859,7 @@ DEVI void piece_body(LongArgs<T> &a, const int32_t pid, const LongRow &lr, const
     }
   }
   group_bitonic_sort<WAVE, K, Key>(key);
-  wave_sync();  // gi is dead from here on
+  wave_sync();  // tb is dead from here on, pv complete
   int32_t *sc = reinterpret_cast<int32_t *>(lds_a);
   T *sv = lds_b;
   const int r = fold_runs<T, WAVE, K, Key>(key, tn, pv, sc, sv, c0);
@@ -1933,7 +1889,7 @@ DEVI void piece_body(LongArgs<T> &a, const int32_t pid, const LongRow &lr, const
 // folded in that order.  Larger pieces are listed for the work-group kernel.
 template <typename T, int K, typename Key, int MAXS>
 DEVI void wave_piece(LongArgs<T> &a, const int32_t pid, unsigned char *lds_a, T *lds_b,
-                     unsigned int *olist, unsigned int *ocnt) {
+                     uint32_t *hd, unsigned int *olist, unsigned int *ocnt) {
   constexpr int U = WAVE * K;
   constexpr int LOGU = Log2<U>::v;
   constexpr Key KMAX = KeyMax<Key>::v;
@@ -1984,38 +1940,47 @@ DEVI void wave_piece(LongArgs<T> &a, const int32_t pid, unsigned char *lds_a, T 
     return;
   }
   const int tn = static_cast<int>(E);
-  // seg_at[t] = segment whose part starts at stream index t (non-empty parts
-  // start at distinct indices), tbase[s] = partial-buffer index of stream
-  // index 0 for segment s; both in the tile buffers, dead before those are
-  // used
-  int32_t *seg_at = reinterpret_cast<int32_t *>(lds_a);
-  int32_t *tbase = reinterpret_cast<int32_t *>(lds_b);
-#pragma unroll
-  for (int kk = 0; kk < K; ++kk) seg_at[pos * K + kk] = -1;
+  // tb[r] = partial-buffer index of stream index 0 for the r-th non-empty
+  // segment, a bit of hd (less one) at the stream index where it starts
+  int32_t *tb = reinterpret_cast<int32_t *>(lds_a);
+  if (pos < 2 * K) hd[pos] = 0u;
   wave_sync();
   {
     int32_t run = static_cast<int32_t>((incl - packed) & 0xffffffffll);
+    int nrun = 0;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) nrun += slen[j] > 0 ? 1 : 0;
+    int r = group_incl_sum<WAVE>(nrun) - nrun;
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
       const int32_t sg = pos * KS + j;
-      if (sg < nseg) {
-        tbase[sg] = static_cast<int32_t>(static_cast<int64_t>(sg) * lr.segp + slo[j] - run);
-        if (slen[j] > 0) seg_at[run] = sg;
+      if (slen[j] > 0) {
+        tb[r++] = static_cast<int32_t>(static_cast<int64_t>(sg) * lr.segp + slo[j] - run);
+        if (run > 0) atomicOr(&hd[(run - 1) >> 5], 1u << ((run - 1) & 31));
       }
       run += slen[j];
     }
   }
   wave_sync();
-  // in the 512-entry pass, a stream that fits half the tile takes the
-  // half-size network (fewer keys per lane to gather, sort and fold); the
-  // 1024-entry pass only receives streams above 512
+  // a stream that leaves part of the tile unused takes fewer entries per lane
+  // (the 1024-entry pass only receives streams above 512)
   if constexpr (K == 8) {
-    if (tn <= WAVE * (K / 2)) {
-      piece_body<T, K / 2, Key>(a, pid, lr, lri, c0, tn, E, obase, lds_a, lds_b);
+    if (tn <= WAVE * 4) {
+      piece_body<T, 4, Key>(a, pid, lr, lri, c0, tn, E, obase, lds_a, lds_b, hd);
       return;
     }
+    if constexpr (sizeof(Key) == 4) {
+      if (tn <= WAVE * 5) {
+        piece_body<T, 5, Key>(a, pid, lr, lri, c0, tn, E, obase, lds_a, lds_b, hd);
+        return;
+      }
+      if (tn <= WAVE * 6) {
+        piece_body<T, 6, Key>(a, pid, lr, lri, c0, tn, E, obase, lds_a, lds_b, hd);
+        return;
+      }
+    }
   }
-  piece_body<T, K, Key>(a, pid, lr, lri, c0, tn, E, obase, lds_a, lds_b);
+  piece_body<T, K, Key>(a, pid, lr, lri, c0, tn, E, obase, lds_a, lds_b, hd);
 }
 
 // Every piece (in_list == nullptr), or the listed ones in a grid-stride
@@ -2032,6 +1997,7 @@ void k_combine_w(LongArgs<T> a, int64_t npieces,
   constexpr int KB = sizeof(Key) > 4 ? static_cast<int>(sizeof(Key)) : 4;
   __shared__ __align__(16) unsigned char s_a[NWV][U * KB];
   __shared__ __align__(16) T s_b[NWV][U];
+  __shared__ uint32_t s_m[NWV][U / 32];
   // wave-uniform (so piece and row records are read through the scalar cache);
   // runs of 4 work-groups (16 neighbouring ranges, which read neighbouring
   // entries of every segment) share an XCD
@@ -2039,13 +2005,14 @@ void k_combine_w(LongArgs<T> a, int64_t npieces,
   const int64_t id = xcd_block_id<4>() * NWV + w;
   if (in_list == nullptr) {
     if (id >= npieces) return;  // uniform across the wavefront; no work-group barriers here
-    wave_piece<T, K, Key, MAXS>(a, static_cast<int32_t>(id), s_a[w], s_b[w], out_list, out_cnt);
+    wave_piece<T, K, Key, MAXS>(a, static_cast<int32_t>(id), s_a[w], s_b[w], s_m[w], out_list,
+                                out_cnt);
     return;
   }
   const int64_t n = *in_cnt;
   for (int64_t x = id; x < n; x += static_cast<int64_t>(gridDim.x) * NWV)
-    wave_piece<T, K, Key, MAXS>(a, static_cast<int32_t>(in_list[x]), s_a[w], s_b[w], out_list,
-                                out_cnt);
+    wave_piece<T, K, Key, MAXS>(a, static_cast<int32_t>(in_list[x]), s_a[w], s_b[w], s_m[w],
+                                out_list, out_cnt);
 }
 
 // ------------------------------------------------------------ long table
