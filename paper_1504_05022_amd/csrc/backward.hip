@@ -52,7 +52,9 @@ __global__ __launch_bounds__(256) void k_grad_b(const int64_t *tptr, const int32
 // order, one per lane: consecutive lanes read consecutive entries of b_j* and
 // write consecutive products of W.  For product q of entry e = (i, j),
 // y = dC_ik is looked up -- by its rank in an LDS bitmap of the row's columns
-// when C has few columns, else by a binary search in c_i* -- and
+// when C has few columns, else by a binary search in c_i*, whose first steps
+// go over samples of the rows in LDS (every step in global memory: 168 us wide,
+// then 136; 512 / 2048 samples 138 / 138) -- and
 //   dA_e = sum of y * b_jk        (a segmented scan across the lanes)
 //   W[P_e + q] = a_ij * y         (q = position of b_jk in b_j*)
 // where P_e is the product offset of entry e from stage 1.  W holds every
@@ -67,18 +69,19 @@ __global__ __launch_bounds__(256) void k_grad_b(const int64_t *tptr, const int32
 // line or two per b_j* and array), not the VALU (37% busy).  One lane per
 // entry of A, as before, left ragged rows waiting on their longest entry and
 // touched 64 lines per load: 2374 us where B is narrow (A 300000^2 with 6M
-// entries x B 300000x4096, 32 per row, binary32; now 1187), 1389 us where it
+// entries x B 300000x4096, 32 per row, binary32; now 1098), 1389 us where it
 // is wide (A 50000^2 with 600k entries x B 50000^2, 12 per row, binary64; now
-// 163).  Few entries per chunk spread the long tail of a small product; with
+// 119).  The chunk's rows are found by the whole wavefront (wave_row_of; a
+// bisection by one lane: 1187 and 136).  Few entries per chunk spread the long tail of a small product; with
 // the bitmap a row cut by a chunk is mapped twice, so chunks are longer there
-// (64 / 128 / 256 / 512 entries measured 1292 / 1257 / 1287 / 1404 us narrow,
-// 163 / 200 / 230 / 369 wide).  Overlapping the next group's loads of B with
+// (64 / 128 / 256 entries measure 1128 / 1098 / 1112 us narrow, 64 / 128 136 /
+// 163 wide).  Overlapping the next group's loads of B with
 // this group's dC costs more in resident wavefronts than it hides (1371).
 constexpr int BW_WIN = 2048;  // products whose entry starts the bit mask covers
 template <bool DENSE> constexpr int bw_ch() { return DENSE ? 128 : 64; }
 // blocks of 64 products whose loads are in flight together (narrow: 3 / 4 / 6
-// blocks 1333 / 1257 / 1187 us; wide: 6 cost it two wavefronts per SIMD)
-template <bool DENSE> constexpr int bw_u() { return DENSE ? 6 : 4; }
+// blocks 1333 / 1257 / 1187 us; wide: 134 / 128 / 119)
+constexpr int BW_U = 6;
 constexpr int BW_SC = 4;  // passes of a row of C whose column loads are in flight together
 // columns of the bitmap: 1 KB of it and 512 bytes of ranks per wavefront,
 // where a dense copy of a dC row of 4096 columns took 16 KB and left 9
@@ -95,6 +98,19 @@ DEVI int32_t row_of(const int32_t *arp, int32_t lo, int32_t hi, int64_t e) {
       lo = mid;
     else
       hi = mid;
+  }
+  return lo;
+}
+
+// The same by a whole wavefront for one e, 64 rows at a time: three dependent
+// loads in 250000 rows, where one lane's bisection takes 18.
+DEVI int32_t wave_row_of(const int32_t *arp, int32_t lo, int32_t hi, int64_t e) {
+  while (hi - lo > 1) {
+    const int32_t step = (hi - lo + WAVE - 1) / WAVE;
+    const int64_t i = lo + static_cast<int64_t>(lane()) * step;
+    const int n = __popcll(__ballot(i < hi && arp[i < hi ? i : lo] <= e));  // the first n
+    lo += (n - 1) * step;
+    hi = hi - lo < step ? hi : lo + step;
   }
   return lo;
 }
@@ -118,6 +134,10 @@ template <typename T> DEVI T segment_scan(T v, int dist) {
   return v;
 }
 
+// wide C: columns of the batch's rows of C that are held in LDS, for the first
+// steps of the searches
+constexpr int BW_SAMPLES = 1024;
+
 template <typename T, bool DENSE> struct GradTable {
   alignas(16) uint32_t bits[DENSE ? BW_MAP / 32 : 4];  // columns of one row of C
   uint16_t rank[DENSE ? BW_MAP / 32 : 1];              // columns before each word
@@ -126,7 +146,8 @@ template <typename T, bool DENSE> struct GradTable {
   uint32_t ent[WAVE];          // its lane (entry of the batch)
   int32_t row[WAVE];           // dense: its row
   T av[WAVE];
-  int32_t c0[DENSE ? 1 : WAVE], c1[DENSE ? 1 : WAVE];  // its row of C
+  int32_t c0[DENSE ? 1 : WAVE], c1[DENSE ? 1 : WAVE];  // its row of C, less cs
+  int32_t sample[DENSE ? 1 : BW_SAMPLES];  // every 2^sh-th column of the batch's rows of C
 };
 
 constexpr int BW_NT = 256;  // four independent wavefronts
@@ -138,7 +159,6 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
     const int32_t *ccol, const T *dc, T *dA, T *W) {
   constexpr int NWV = BW_NT / WAVE;
   constexpr int BW_CH = bw_ch<DENSE>();
-  constexpr int BW_U = bw_u<DENSE>();
   __shared__ GradTable<T, DENSE> tabs[NWV];
   const int w = threadIdx.x / WAVE;
   const int ln = lane();
@@ -146,8 +166,13 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
   const int64_t e0 = (static_cast<int64_t>(blockIdx.x) * NWV + w) * BW_CH;
   if (e0 >= nnz) return;  // uniform across the wavefront; no work-group barriers here
   const int64_t e1 = e0 + BW_CH < nnz ? e0 + BW_CH : nnz;
-  int32_t row_lo = row_of(arp, 0, static_cast<int32_t>(m), e0);
-  const int32_t row_hi = row_of(arp, row_lo, static_cast<int32_t>(m), e1 - 1) + 1;
+  // its rows [row_lo, row_hi), mostly within 64: their starts one per lane
+  const int32_t row_lo = wave_row_of(arp, 0, static_cast<int32_t>(m), e0);
+  const int32_t ahead = m - row_lo < WAVE ? static_cast<int32_t>(m) - row_lo : WAVE;
+  const int32_t start = arp[row_lo + (ln < ahead ? ln : 0)];
+  const int32_t rows = __popcll(__ballot(ln < ahead && start < e1));
+  int32_t row_hi = row_lo + rows;
+  if (rows == WAVE) row_hi = wave_row_of(arp, row_hi - 1, static_cast<int32_t>(m), e1 - 1) + 1;
   int32_t mapped = -1;  // row in the bitmap
   int32_t mapped_c0 = 0;  // its first entry of C
   const uint64_t le_mask = ~0ull >> (WAVE - 1 - ln);
@@ -161,19 +186,47 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
     const int64_t pre = P[e] - Pb;
     const int64_t len = P[e + 1] - Pb - pre;
     const int64_t tot = P[eb + nb] - Pb;
-    const int32_t row = row_of(arp, row_lo, row_hi, e);
-    row_lo = __builtin_amdgcn_readlane(row, nb - 1);
+    int32_t row = row_lo;
+    if (row_hi - row_lo <= WAVE) {
+      for (int r = 1; r < rows; ++r)
+        row += __builtin_amdgcn_readlane(start, r) <= static_cast<int32_t>(e) ? 1 : 0;
+    } else {
+      row = row_of(arp, row_lo, row_hi, e);
+    }
     const int32_t c0 = crp[row], c1 = crp[row + 1];
     const bool some = in && len > 0;
     const int c = __popcll(__ballot(some) & (le_mask >> 1));  // entries with products below
+    // wide C: the batch's rows of C begin at entry cs; samples 2^sh apart
+    const int32_t cs = __builtin_amdgcn_readfirstlane(c0);
+    int sh = 0;
     wave_sync();  // the previous batch's table is dead
     if (some) {
       tb.ent[c] = ln;
       tb.row[c] = row;
       tb.av[c] = av;
       if (!DENSE) {
-        tb.c0[c] = c0;
-        tb.c1[c] = c1;
+        tb.c0[c] = c0 - cs;
+        tb.c1[c] = c1 - cs;
+      }
+    }
+    if (!DENSE && tot > 0) {
+      const int32_t L = __builtin_amdgcn_readlane(c1, nb - 1) - cs;
+      const int32_t most =
+          tot < WAVE ? WAVE : tot < BW_SAMPLES ? static_cast<int32_t>(tot) : BW_SAMPLES;
+      while (((L - 1) >> sh) >= most) ++sh;
+      const int32_t last = (L - 1) >> sh;
+      for (int32_t xs = 0; xs <= last; xs += BW_SC * WAVE) {
+        int32_t cc[BW_SC];
+#pragma unroll
+        for (int p = 0; p < BW_SC; ++p) {
+          const int32_t x = xs + p * WAVE + ln;
+          cc[p] = ccol[cs + ((x < last ? x : last) << sh)];
+        }
+#pragma unroll
+        for (int p = 0; p < BW_SC; ++p) {
+          const int32_t x = xs + p * WAVE + ln;
+          if (x <= last) tb.sample[x] = cc[p];
+        }
       }
     }
     if (dA && in && len == 0) dA[e] = T(0);
@@ -279,14 +332,44 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
           }
         } else {
           // lower bounds of the BW_U columns in their rows of C, one step of
-          // every search at a time (their loads are in flight together)
-          int32_t lo[BW_U], hi[BW_U];
+          // every search at a time (their loads are in flight together): the
+          // first sample of the row that is not below, then the entries
+          // between it and the sample before
+          int32_t lo[BW_U], hi[BW_U], a0[BW_U], a1[BW_U];
           int32_t most = 0;
+          const int32_t up = (1 << sh) - 1;
 #pragma unroll
           for (int u = 0; u < BW_U; ++u) {
             const bool ok = x0 + u * WAVE + ln < wl;
-            lo[u] = ok ? tb.c0[cur.ce[u]] : 0;
-            hi[u] = ok ? tb.c1[cur.ce[u]] : 0;
+            a0[u] = ok ? tb.c0[cur.ce[u]] : 0;
+            a1[u] = ok ? tb.c1[cur.ce[u]] : 0;
+            lo[u] = (a0[u] + up) >> sh;
+            hi[u] = (a1[u] + up) >> sh;
+            most = max(most, hi[u] - lo[u]);
+          }
+          while (__any(most > 0)) {
+            int32_t mc[BW_U];
+#pragma unroll
+            for (int u = 0; u < BW_U; ++u) {
+              const int32_t mid = (lo[u] + hi[u]) >> 1;
+              mc[u] = tb.sample[lo[u] < hi[u] ? mid : 0];
+            }
+            most = 0;
+#pragma unroll
+            for (int u = 0; u < BW_U; ++u) {
+              const int32_t mid = (lo[u] + hi[u]) >> 1;
+              const bool open = lo[u] < hi[u], below = mc[u] < cur.kk[u];
+              lo[u] = open && below ? mid + 1 : lo[u];
+              hi[u] = open && !below ? mid : hi[u];
+              most = max(most, hi[u] - lo[u]);
+            }
+          }
+          most = 0;
+#pragma unroll
+          for (int u = 0; u < BW_U; ++u) {
+            const int32_t t = lo[u] << sh;
+            lo[u] = cs + max(a0[u], t - up);
+            hi[u] = cs + min(a1[u], t);
             most = max(most, hi[u] - lo[u]);
           }
           while (__any(most > 0)) {

@@ -155,3 +155,41 @@ def test_long_rows_in_few_columns(dtype, u):
     B = S.Csr(k, n, B.row_ptr, B.col_idx + 77, B.val)
     A = _ragged(rng, len(deg), deg, k, dtype)
     check(A, B)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_backward_wide_rows_around_samples(dtype):
+    """C wider than a bitmap, its rows around the 1024 columns that are sampled
+    for the searches and the strides above, short and long rows and empty ones
+    in one batch of entries; more rows than lanes in a chunk; very few
+    products against a long row of C."""
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, Plan
+    rng = np.random.default_rng(9)
+    n = 40000
+    lens = [0, 1, 1, 2, 500, 1023, 1024, 1025, 2048, 2049, 5000, 0] + [1] * 200
+    k = len(lens)
+    B = _ragged(rng, k, lens, n, dtype)
+    rows = [[4], [5], [6], [7], [8], [9], [10], [], [1, 2, 10], [0, 11], list(range(12)),
+            list(range(12, k))] + [[12 + x] for x in range(150)] + [[]] * 80 + [[3, 10, 20, 30]]
+    rp = np.r_[0, np.cumsum([len(r) for r in rows])].astype(np.int32)
+    ci = np.concatenate([np.array(r, np.int32) for r in rows])
+    A = S.Csr(len(rows), k, rp, ci.astype(np.int32), rng.standard_normal(ci.size).astype(dtype))
+    print("case: %s products of %d entries" % (np.dtype(dtype), A.nnz), flush=True)
+    plan = Plan(CsrMatrix.from_host(A), CsrMatrix.from_host(B))
+    C = plan.compute()
+    dc = rng.standard_normal(C.nnz).astype(dtype)
+    gA, gB = plan.backward(C, torch.from_numpy(dc).cuda())
+    _, _, crp, cci, _ = C.to_host()
+
+    def grads(f):
+        x, y = A.astype(np.float64), B.astype(np.float64)
+        x.val, y.val = f(x.val), f(y.val)
+        return oracle.grad(x.as_tuple(), y.as_tuple(), crp.astype(np.int64), cci,
+                           f(dc.astype(np.float64)))
+
+    refs, mags = grads(lambda v: v), grads(np.abs)
+    eps = np.finfo(dtype).eps  # a sum of t rounded products, in any order
+    terms = (np.array(lens)[A.col_idx], np.bincount(A.col_idx, minlength=k).repeat(lens))
+    for got, ref, mag, t in zip((gA, gB), refs, mags, terms):
+        assert np.all(np.abs(got.cpu().numpy() - ref) <= (t + 2) * eps * mag)
