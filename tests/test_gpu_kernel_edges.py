@@ -193,3 +193,29 @@ def test_backward_wide_rows_around_samples(dtype):
     terms = (np.array(lens)[A.col_idx], np.bincount(A.col_idx, minlength=k).repeat(lens))
     for got, ref, mag, t in zip((gA, gB), refs, mags, terms):
         assert np.all(np.abs(got.cpu().numpy() - ref) <= (t + 2) * eps * mag)
+
+
+def test_training_steps_give_their_memory_back():
+    """The plan and the matrices of a differentiable product are released with
+    its last tensor, without Python's cycle collector."""
+    import gc
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, matmul
+    rng = np.random.default_rng(3)
+    A = CsrMatrix.from_host(_ragged(rng, 300, [20] * 300, 300, np.float64))
+    A.val.requires_grad_(True)
+
+    def step():
+        C = matmul(A, A)
+        torch.autograd.grad(C.val.sum(), A.val)
+
+    step()
+    gc.collect()
+    gc.disable()
+    try:
+        base = torch.cuda.memory_allocated()
+        for _ in range(3):
+            step()
+        assert torch.cuda.memory_allocated() == base
+    finally:
+        gc.enable()
