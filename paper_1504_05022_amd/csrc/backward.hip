@@ -72,11 +72,12 @@ __global__ __launch_bounds__(256) void k_grad_b(const int64_t *tptr, const int32
 // entries x B 300000x4096, 32 per row, binary32; now 1098), 1389 us where it
 // is wide (A 50000^2 with 600k entries x B 50000^2, 12 per row, binary64; now
 // 119).  The chunk's rows are found by the whole wavefront (wave_row_of; a
-// bisection by one lane: 1187 and 136).  Few entries per chunk spread the long tail of a small product; with
-// the bitmap a row cut by a chunk is mapped twice, so chunks are longer there
-// (64 / 128 / 256 entries measure 1128 / 1098 / 1112 us narrow, 64 / 128 136 /
-// 163 wide).  Overlapping the next group's loads of B with
-// this group's dC costs more in resident wavefronts than it hides (1371).
+// bisection by one lane: 1187 and 136).  Few entries per chunk spread the long
+// tail of a small product; with the bitmap a row cut by a chunk is mapped
+// twice, so chunks are longer there (64 / 128 / 256 entries measure 1128 / 1098
+// / 1112 us narrow, 64 / 128 136 / 163 wide).  Overlapping the next group's
+// loads of B with this group's dC costs more in resident wavefronts than it
+// hides (1371).
 constexpr int BW_WIN = 2048;  // products whose entry starts the bit mask covers
 template <bool DENSE> constexpr int bw_ch() { return DENSE ? 128 : 64; }
 // blocks of 64 products whose loads are in flight together (narrow: 3 / 4 / 6
@@ -425,35 +426,46 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
 }
 
 // dB_jk = sum over A's column j (ascending i) of the products a_ij dC_ik in W.
-// BW_SUB lanes per row of B (each lane sums its own entries, so rows share
-// a wavefront without any ordering between them).
+// BW_SUB lanes per row of B (each lane sums its own entries, so rows share a
+// wavefront without any ordering between them).  Bound by the gathers of W
+// past the L2 (128 bytes per entry of A and row of B: 710 MB, 266 us for the
+// narrow B above; 27 us for the wide one).  The lanes fetch the product
+// offsets of BW_SUB entries of A's column together and share them through
+// LDS (each lane fetching those of the next BW_SU products itself, three
+// dependent loads per BW_SU: 284 and 35 us); then BW_SU products are in flight
+// per lane (16: the same).  16 lanes: 471 and 27 us, 64: 269 narrow.
 constexpr int BW_SUB = 32;
-constexpr int BW_SU = 8;  // entries of A's column whose loads are in flight together
+constexpr int BW_SU = 8;
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_grad_b_sum(const int64_t *tptr, const int32_t *tpos,
                                                     const int64_t *P, const int32_t *brp,
                                                     int64_t kb, const T *W, T *dB) {
+  __shared__ int64_t offs[256];
   const int64_t j = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / BW_SUB;
-  if (j >= kb) return;
+  if (j >= kb) return;  // the lanes of a group together; no work-group barriers here
+  const int l = lane() & (BW_SUB - 1);
+  int64_t *off = offs + (threadIdx.x - l);
   const int64_t t0 = tptr[j], t1 = tptr[j + 1];
   const int32_t q0 = brp[j], q1 = brp[j + 1];
-  for (int32_t q = q0 + (lane() & (BW_SUB - 1)); q < q1; q += BW_SUB) {
+  for (int32_t qb = q0; qb < q1; qb += BW_SUB) {
+    const int32_t q = qb + l;
+    const GLOBAL_AS T *Wq = as_global(W) + (q < q1 ? q - q0 : 0);
     T s = T(0);
-    // blocks of BW_SU entries of A's column j: offsets, then products, each
-    // loaded together (clamped to the column), then added in order
-    for (int64_t db = t0; db < t1; db += BW_SU) {
-      int64_t off[BW_SU];
+    for (int64_t db = t0; db < t1; db += BW_SUB) {
+      const int n = static_cast<int>(t1 - db < BW_SUB ? t1 - db : BW_SUB);
+      wave_sync();  // the previous offsets are read
+      off[l] = P[tpos[db + (l < n ? l : n - 1)]];
+      wave_sync();
+      for (int d = 0; d < n; d += BW_SU) {
+        T v[BW_SU];  // entries past the end reread the last one and are not added
 #pragma unroll
-      for (int u = 0; u < BW_SU; ++u) off[u] = P[tpos[db + u < t1 ? db + u : t1 - 1]];
-      T v[BW_SU];
+        for (int u = 0; u < BW_SU; ++u) v[u] = Wq[off[d + u < n ? d + u : n - 1]];
 #pragma unroll
-      for (int u = 0; u < BW_SU; ++u) v[u] = W[off[u] + (q - q0)];
-#pragma unroll
-      for (int u = 0; u < BW_SU; ++u)
-        if (db + u < t1) s = s + v[u];
+        for (int u = 0; u < BW_SU; ++u) s = d + u < n ? s + v[u] : s;
+      }
     }
-    dB[q] = s;
+    if (q < q1) dB[q] = s;
   }
 }
 
@@ -494,11 +506,9 @@ template void launch_grad_entries<double>(const int32_t *, const double *,
                                           const int32_t *, const int32_t *, const double *,
                                           double *, double *, hipStream_t);
 template void launch_grad_b_sum<float>(const int64_t *, const int32_t *, const int64_t *,
-                                       const int32_t *, int64_t, const float *, float *,
-                                       hipStream_t);
+                                      const int32_t *, int64_t, const float *, float *, hipStream_t);
 template void launch_grad_b_sum<double>(const int64_t *, const int32_t *, const int64_t *,
-                                        const int32_t *, int64_t, const double *, double *,
-                                        hipStream_t);
+                                      const int32_t *, int64_t, const double *, double *, hipStream_t);
 
 // Column counts of A.
 __global__ void k_col_count(const int32_t *acol, int64_t nnz, int32_t *cnt) {
