@@ -678,6 +678,23 @@ struct StatusEnd {
   }
 };
 
+// Words to pinned host memory, then the token that announces them (one
+// work-group).
+__global__ __launch_bounds__(256) void k_publish(const uint64_t *src, int64_t words, uint64_t *dst,
+                                                 uint64_t *at, uint64_t token) {
+  for (int64_t k = threadIdx.x; k < words; k += 256)
+    __hip_atomic_store(&dst[k], src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(at, token, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+void launch_publish(const uint64_t *src, int64_t words, uint64_t *dst, uint64_t *at,
+                    uint64_t token, hipStream_t s) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, s, src, words, dst, at, token);
+}
+
 __global__ void k_status(const int64_t *rowoff, int64_t m, StatusEnd end) { end(rowoff[m]); }
 
 void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, const LongCounters *cnt,

@@ -179,10 +179,10 @@ HostSlot *take_slot(int which, uint64_t *token) {
   return &hs->slot[which];
 }
 
-// Waits for the record; a wait beyond a few milliseconds is left to the
-// runtime, which also reports errors of the stream.
-hipError_t wait_slot(HostSlot *slot, uint64_t token, void *dst, size_t bytes, hipStream_t s) {
-  const auto arrived = [&] { return __atomic_load_n(&slot->token, __ATOMIC_ACQUIRE) == token; };
+// Waits for a token in pinned memory; a wait beyond a few milliseconds is left
+// to the runtime, which also reports errors of the stream.
+hipError_t wait_token(const uint64_t *at, uint64_t token, hipStream_t s) {
+  const auto arrived = [&] { return __atomic_load_n(at, __ATOMIC_ACQUIRE) == token; };
   const auto t0 = std::chrono::steady_clock::now();
   for (int spin = 0; !arrived(); ++spin) {
     __builtin_ia32_pause();
@@ -193,8 +193,13 @@ hipError_t wait_slot(HostSlot *slot, uint64_t token, void *dst, size_t bytes, hi
       break;
     }
   }
-  std::memcpy(dst, slot->word, bytes);
   return hipSuccess;
+}
+
+hipError_t wait_slot(HostSlot *slot, uint64_t token, void *dst, size_t bytes, hipStream_t s) {
+  const hipError_t e = wait_token(&slot->token, token, s);
+  if (e == hipSuccess) std::memcpy(dst, slot->word, bytes);
+  return e;
 }
 
 // Device -> host copy of a small record through the pinned staging area;
@@ -213,6 +218,42 @@ hipError_t read_small(void *dst, const void *src, size_t bytes, hipStream_t s) {
 }
 
 }  // namespace
+
+namespace spg {
+
+// `words` 8-byte words of device memory, read back on the stream's order:
+// written into pinned memory by a kernel, with a token that the host waits
+// for (one such area per thread; larger records go by copy command).
+hipError_t read_words(void *dst, const void *src, int64_t words, hipStream_t s) {
+  constexpr int64_t kMost = 8191;  // 64 KB with the token
+  thread_local uint64_t *area = nullptr;
+  thread_local uint64_t last = 0;
+  if (words <= kMost && !area) {
+    void *p = nullptr;
+    if (hipHostMalloc(&p, (kMost + 1) * 8,
+                      hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent) ==
+        hipSuccess) {
+      std::memset(p, 0, (kMost + 1) * 8);
+      area = static_cast<uint64_t *>(p);
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  if (words > kMost || !area) {
+    hipError_t e = hipMemcpyAsync(dst, src, static_cast<size_t>(words) * 8,
+                                  hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    return e;
+  }
+  const uint64_t token = ++last;
+  launch_publish(static_cast<const uint64_t *>(src), words, area + 1, area, token, s);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = wait_token(area, token, s);
+  if (e == hipSuccess) std::memcpy(dst, area + 1, static_cast<size_t>(words) * 8);
+  return e;
+}
+
+}  // namespace spg
 
 struct spgemm_plan_s {
   // identity of the analyzed inputs

@@ -918,9 +918,16 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
     off = round256(off + std::max<size_t>(bytes, 1));
     return o0;
   };
-  const size_t o_prob = add(sizeof(BmProblem) * count);
+  // the tables that the host fills come first, in the order in which they are
+  // uploaded: tiles and problems at the start; problems, kernel arguments,
+  // list places and items after the counts are read
   const size_t o_et = add(sizeof(BmTile) * etile.size());
   const size_t o_rt = add(sizeof(BmTile) * rtile.size());
+  const size_t o_prob = add(sizeof(BmProblem) * count);
+  const size_t o_bp = add(sizeof(BatchProblem) * count);
+  const size_t o_cur = add(sizeof(unsigned long long) * ncnt);
+  const size_t o_io = add(sizeof(int64_t) * ncnt);
+  const size_t o_tables = off;
   const size_t o_w = add(sizeof(int32_t) * E);
   const size_t o_P = add(sizeof(int64_t) * (E + 1));
   const size_t o_part = add(sizeof(int64_t) * scan_part_len(std::max<int64_t>(std::max(E, R), 1)));
@@ -929,12 +936,9 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   const size_t o_RN = add(sizeof(int64_t) * R);
   const size_t o_RO = add(sizeof(int64_t) * (R + 1));
   const size_t o_cnt = add(sizeof(unsigned long long) * (ncnt + count));  // counts, then sums of u
-  const size_t o_cur = add(sizeof(unsigned long long) * ncnt);
-  const size_t o_io = add(sizeof(int64_t) * ncnt);
   const size_t o_list = add(sizeof(RowRec) * R);
   const size_t o_bst = add(sizeof(int32_t) * E);
   const size_t o_g = add(sizeof(int64_t) * (count + 1));
-  const size_t o_bp = add(sizeof(BatchProblem) * count);
   char *ws = static_cast<char *>(mem.get(off));
   if (!ws) return bfail(SPGEMM_ENOMEM, "batch scratch allocation failed");
   BmProblem *dprob = reinterpret_cast<BmProblem *>(ws + o_prob);
@@ -957,13 +961,20 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   BatchProblem *dbp = reinterpret_cast<BatchProblem *>(ws + o_bp);
   int64_t bytes_scratch = static_cast<int64_t>(off);
 
-  auto h2d = [&](void *dst, const void *src, size_t bytes) {
-    return bytes == 0 || hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
+  // neighbouring tables are uploaded together: a copy from pageable memory
+  // costs the host about 10 us, whatever its size
+  std::vector<char> tables(o_tables);
+  auto fill = [&](size_t at, const void *src, size_t bytes) {
+    if (bytes) std::memcpy(tables.data() + at, src, bytes);
   };
-  if (!h2d(dprob, hp.data(), sizeof(BmProblem) * count) ||
-      !h2d(det, etile.data(), sizeof(BmTile) * etile.size()) ||
-      !h2d(drt, rtile.data(), sizeof(BmTile) * rtile.size()))
-    return bfail(SPGEMM_EHIP, "batch table upload failed");
+  auto upload = [&](size_t from, size_t to) {
+    return hipMemcpyAsync(ws + from, tables.data() + from, to - from, hipMemcpyHostToDevice, s) ==
+           hipSuccess;
+  };
+  fill(o_et, etile.data(), sizeof(BmTile) * etile.size());
+  fill(o_rt, rtile.data(), sizeof(BmTile) * rtile.size());
+  fill(o_prob, hp.data(), sizeof(BmProblem) * count);
+  if (!upload(o_et, o_bp)) return bfail(SPGEMM_EHIP, "batch table upload failed");
   launch_zero(dcnt, sizeof(unsigned long long) * (ncnt + count), s);
 
   // stage 1 over every problem: products per entry, their scan, u_i
@@ -973,10 +984,11 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   scan_i32(dw, E, dP, dpart, s);
   hipLaunchKernelGGL(k_bm_rows, dim3(static_cast<unsigned int>(rtile.size())), dim3(BM_NT), 0, s,
                      drt, dprob, dP, dU, dRN, dcnt, dsumu);
+  // C~ offsets, before the host knows of fallback problems: again without them
+  // if there are any
+  scan_i64(dU, R, dCTO, dpart, s);
   std::vector<unsigned long long> hcnt(ncnt + count);
-  if (hipMemcpyAsync(hcnt.data(), dcnt, sizeof(unsigned long long) * (ncnt + count),
-                     hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
+  if (read_words(hcnt.data(), dcnt, ncnt + count, s) != hipSuccess)
     return bfail(SPGEMM_EHIP, std::string("batch analysis failed: ") +
                                   hipGetErrorString(hipGetLastError()));
 
@@ -1001,6 +1013,7 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
     cbase[p] = ntilde;
     ntilde += static_cast<int64_t>(hcnt[ncnt + p]);
   }
+  if (!fallback.empty()) scan_i64(dU, R, dCTO, dpart, s);
   // class lists grouped by class, then problem; items of at most 256 / G
   // rows, written on the device from each list's first item (-1: none)
   std::vector<unsigned long long> hcur(ncnt, 0);
@@ -1039,14 +1052,14 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
 
   // C~ (columns; values in 8-byte slots whatever the problem's type, so
   // that binary32 and binary64 problems share one offset space) and items
-  char *tcol = static_cast<char *>(mem.get(std::max<int64_t>(ntilde, 1) * 4));
-  char *tval = static_cast<char *>(mem.get(std::max<int64_t>(ntilde, 1) * 8));
-  BatchItem *ditems =
-      static_cast<BatchItem *>(mem.get(sizeof(BatchItem) * std::max<int64_t>(nitems, 1)));
-  if (!tcol || !tval || !ditems) return bfail(SPGEMM_ENOMEM, "C~ allocation failed");
-  bytes_scratch += static_cast<int64_t>(round256(std::max<int64_t>(ntilde, 1) * 4) +
-                                        round256(std::max<int64_t>(ntilde, 1) * 8) +
-                                        round256(sizeof(BatchItem) * std::max<int64_t>(nitems, 1)));
+  const size_t tcol_bytes = round256(std::max<int64_t>(ntilde, 1) * 4);
+  const size_t tval_bytes = round256(std::max<int64_t>(ntilde, 1) * 8);
+  const size_t item_bytes = round256(sizeof(BatchItem) * std::max<int64_t>(nitems, 1));
+  char *tcol = static_cast<char *>(mem.get(tcol_bytes + tval_bytes + item_bytes));
+  if (!tcol) return bfail(SPGEMM_ENOMEM, "C~ allocation failed");
+  char *tval = tcol + tcol_bytes;
+  BatchItem *ditems = reinterpret_cast<BatchItem *>(tval + tval_bytes);
+  bytes_scratch += static_cast<int64_t>(tcol_bytes + tval_bytes + item_bytes);
   std::vector<BatchProblem> hbp(count);
   for (int32_t p = 0; p < count; ++p) {
     // a binary32 problem's values at slot offset cbase + k sit at byte
@@ -1071,16 +1084,15 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
     q.dtype = A[p].dtype;
     q.pad = 0;
   }
-  if (!h2d(dprob, hp.data(), sizeof(BmProblem) * count) ||
-      !h2d(dbp, hbp.data(), sizeof(BatchProblem) * count) ||
-      !h2d(dcur, hcur.data(), sizeof(unsigned long long) * ncnt) ||
-      !h2d(dio, hio.data(), sizeof(int64_t) * ncnt))
-    return bfail(SPGEMM_EHIP, "batch table upload failed");
+  fill(o_prob, hp.data(), sizeof(BmProblem) * count);
+  fill(o_bp, hbp.data(), sizeof(BatchProblem) * count);
+  fill(o_cur, hcur.data(), sizeof(unsigned long long) * ncnt);
+  fill(o_io, hio.data(), sizeof(int64_t) * ncnt);
+  if (!upload(o_prob, o_tables)) return bfail(SPGEMM_EHIP, "batch table upload failed");
   hipLaunchKernelGGL(k_bm_items, dim3(static_cast<unsigned int>(ncnt)), dim3(BM_NT), 0, s, dcnt,
                      dcur, dio, set, map, ditems);
 
-  // C~ offsets, class lists, the ESC per class, row sizes of C
-  scan_i64(dU, R, dCTO, dpart, s);
+  // class lists, the ESC per class, row sizes of C
   hipLaunchKernelGGL(k_bm_scatter, dim3(static_cast<unsigned int>(rtile.size())), dim3(BM_NT), 0,
                      s, drt, dprob, dU, dcur, dlist);
   launch_classes(s, ditems, dbp, cls_off, set);
@@ -1088,9 +1100,7 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   hipLaunchKernelGGL(k_bm_gather, dim3(static_cast<unsigned int>((count + 256) / 256)), dim3(256),
                      0, s, dprob, count, dRO, R, dg);
   std::vector<int64_t> hg(count + 1);
-  if (hipMemcpyAsync(hg.data(), dg, sizeof(int64_t) * (count + 1), hipMemcpyDeviceToHost, s) !=
-          hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
+  if (read_words(hg.data(), dg, count + 1, s) != hipSuccess)
     return bfail(SPGEMM_EHIP, std::string("batch numeric stage failed: ") +
                                   hipGetErrorString(hipGetLastError()));
 
@@ -1163,8 +1173,8 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
       if (!ok) return bfail(SPGEMM_EHIP, "output copy failed");
     }
   }
-  if (!h2d(dprob, hp.data(), sizeof(BmProblem) * count))
-    return bfail(SPGEMM_EHIP, "batch table upload failed");
+  fill(o_prob, hp.data(), sizeof(BmProblem) * count);
+  if (!upload(o_prob, o_bp)) return bfail(SPGEMM_EHIP, "batch table upload failed");
   const auto copy = [&](auto r) {
     constexpr int RR = decltype(r)::value;
     hipLaunchKernelGGL(k_bm_compact<RR>,

@@ -587,6 +587,10 @@ void launch_grad_b(const int64_t *tptr, const int32_t *trow, const int32_t *tpos
                    const int32_t *ccol, const T *dc, T *dB, hipStream_t s);
 void launch_zero(void *p, size_t bytes, hipStream_t s);
 void launch_set_pool(Pool *dst, Pool value, hipStream_t s);
+// A small record read back from device memory, on the stream's order.
+hipError_t read_words(void *dst, const void *src, int64_t words, hipStream_t s);
+void launch_publish(const uint64_t *src, int64_t words, uint64_t *dst, uint64_t *at,
+                    uint64_t token, hipStream_t s);
 // Status of compute (pool, cnt: nullptr without the merge method): to `slot`
 // with `token`, or to `st` if there is no slot.
 void launch_status(const int64_t *rowoff, int64_t m, const Pool *pool, const LongCounters *cnt,

@@ -219,3 +219,29 @@ def test_training_steps_give_their_memory_back():
         assert torch.cuda.memory_allocated() == base
     finally:
         gc.enable()
+
+
+@pytest.mark.parametrize("count", [1, 580, 680])
+def test_one_shot_batch_of_many_problems(count):
+    """One-shot batches up to and beyond the counts that fit the pinned area,
+    with an empty problem and one that goes through the plain path."""
+    from paper_1504_05022_amd import CsrMatrix, batch_multiply
+    rng = np.random.default_rng(count)
+    pairs = []
+    for p in range(count):
+        n = 1 + p % 4
+        lens = np.zeros(n, int) if p == 5 else rng.integers(0, n + 1, n)
+        pairs.append((_ragged(rng, n, lens, n, np.float64), _ragged(rng, n, lens, n, np.float64)))
+    wide = _ragged(rng, 60, [40] * 60, 60, np.float32)  # 1600 products per row
+    pairs.insert(count // 2, (wide, wide))
+    print("case: %d problems" % len(pairs), flush=True)
+    out = batch_multiply([(CsrMatrix.from_host(a), CsrMatrix.from_host(b)) for a, b in pairs])
+    for C, (a, b) in zip(out, pairs):
+        _, _, rp, ci, v = C.to_host()
+        ref = oracle.spgemm(a.astype(np.float64).as_tuple(), b.astype(np.float64).as_tuple())
+        assert np.array_equal(rp, ref.row_ptr) and np.array_equal(ci, ref.col_idx)
+        # a sum of t rounded products: t eps of the sum of their magnitudes
+        scale = 40 * np.finfo(v.dtype).eps
+        mag = oracle.spgemm(a.astype(np.float64).as_tuple()[:4] + (np.abs(a.val.astype(float)),),
+                            b.astype(np.float64).as_tuple()[:4] + (np.abs(b.val.astype(float)),))
+        assert np.all(np.abs(v - ref.val) <= scale * mag.val)
