@@ -103,17 +103,9 @@ DEVI int32_t row_of(const int32_t *arp, int32_t lo, int32_t hi, int64_t e) {
   return lo;
 }
 
-// The same by a whole wavefront for one e, 64 rows at a time: three dependent
-// loads in 250000 rows, where one lane's bisection takes 18.
+// The same by a whole wavefront for one e.
 DEVI int32_t wave_row_of(const int32_t *arp, int32_t lo, int32_t hi, int64_t e) {
-  while (hi - lo > 1) {
-    const int32_t step = (hi - lo + WAVE - 1) / WAVE;
-    const int64_t i = lo + static_cast<int64_t>(lane()) * step;
-    const int n = __popcll(__ballot(i < hi && arp[i < hi ? i : lo] <= e));  // the first n
-    lo += (n - 1) * step;
-    hi = hi - lo < step ? hi : lo + step;
-  }
-  return lo;
+  return static_cast<int32_t>(wave_last(lo, hi, [&](int64_t i) { return arp[i] <= e; }));
 }
 
 // Sums of the lanes from the last segment head at or below each lane (dist

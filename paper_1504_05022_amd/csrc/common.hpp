@@ -16,6 +16,20 @@ constexpr int WAVE = 64;
 
 DEVI int lane() { return static_cast<int>(__lane_id()); }
 
+// Last i of [lo, hi) for which ok(i) holds (it does for lo, and for no i above
+// one for which it does not), by a whole wavefront: 64 places at a time, three
+// dependent loads in 250000, where one lane's bisection takes 18.
+template <typename Ok> DEVI int64_t wave_last(int64_t lo, int64_t hi, Ok ok) {
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + WAVE - 1) / WAVE;
+    const int64_t i = lo + lane() * step;
+    const int n = __popcll(__ballot(i < hi && ok(i < hi ? i : lo)));  // the first n
+    lo += (n - 1) * step;
+    hi = hi - lo < step ? hi : lo + step;
+  }
+  return lo;
+}
+
 // Orders the LDS accesses of one wavefront (no work-group barrier): for
 // data that only the lanes of one wavefront share.
 DEVI void wave_sync() {

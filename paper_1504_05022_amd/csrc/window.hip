@@ -205,27 +205,17 @@ template <typename First> DEVI int64_t owner_row(int64_t nlong, int64_t t, First
 }
 
 // One thread per work unit: items (WHAT 0; e0 set for the product ranges
-// of direct dense rows), segments (WHAT 1; e0 always) or dense partial rows
-// (WHAT 2; the owning long row in slot_row, and its item: they are the
-// product ranges of rows that have several).
+// of direct dense rows) or segments (WHAT 1; e0 always).
 template <int WHAT>
 __global__ __launch_bounds__(256) void k_wplan_units(const WinRow *rows, int64_t nlong,
                                                      int64_t nunits, const int32_t *arp,
-                                                     const int64_t *P, WinWork *work,
-                                                     int32_t *slot_row) {
+                                                     const int64_t *P, WinWork *work) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (t >= nunits) return;
   const int64_t k = owner_row(nlong, t, [&](int64_t x) {
-    return WHAT == 0 ? rows[x].item0 : WHAT == 1 ? rows[x].seg0 : rows[x].dslot0;
+    return WHAT == 0 ? rows[x].item0 : rows[x].seg0;
   });
   const WinRow r = rows[k];
-  if (WHAT == 2) {
-    slot_row[t] = static_cast<int32_t>(k);
-    const int64_t q = t - r.dslot0;
-    work[r.item0 + q] = WinWork{static_cast<int32_t>(k), static_cast<int32_t>(q),
-                                entry_of(arp, P, r.row, q * kWinSplit), 0};
-    return;
-  }
   const int32_t q = static_cast<int32_t>(t - (WHAT == 0 ? r.item0 : r.seg0));
   int32_t e0 = -1;
   if (WHAT == 1)
@@ -233,6 +223,29 @@ __global__ __launch_bounds__(256) void k_wplan_units(const WinRow *rows, int64_t
   else if (r.mode == WIN_DD)
     e0 = entry_of(arp, P, r.row, static_cast<int64_t>(q) * kWinSplit);
   work[t] = WinWork{static_cast<int32_t>(k), q, e0, 0};
+}
+
+// One wavefront per dense partial row (the owning long row in slot_row, and
+// its item: they are the product ranges of rows that have several).  There
+// are few, and everything behind them waits: both searches go 64 ways at a
+// time, three dependent loads each where a lane's bisections take 17 and up
+// to 18 (13 us, 32 beside the short rows; now 6 and 12).
+__global__ __launch_bounds__(256) void k_wplan_ranges(const WinRow *rows, int64_t nlong,
+                                                      int64_t nslots, const int32_t *arp,
+                                                      const int64_t *P, WinWork *items,
+                                                      int32_t *slot_row) {
+  const int64_t t = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / WAVE;
+  if (t >= nslots) return;  // uniform across the wavefront
+  const int64_t k = wave_last(0, nlong, [&](int64_t x) { return rows[x].dslot0 <= t; });
+  const WinRow r = rows[k];
+  const int64_t q = t - r.dslot0;
+  const int64_t p = P[arp[r.row]] + q * kWinSplit;
+  const int64_t e0 = wave_last(arp[r.row], arp[r.row + 1], [&](int64_t e) { return P[e] <= p; });
+  if (lane() == 0) {
+    slot_row[t] = static_cast<int32_t>(k);
+    items[r.item0 + q] = WinWork{static_cast<int32_t>(k), static_cast<int32_t>(q),
+                                 static_cast<int32_t>(e0), 0};
+  }
 }
 
 // ---------------------------------------------- wavefront product sources
@@ -1405,13 +1418,13 @@ void win_plan_launch(const int32_t *lrows, int64_t nlong, const int64_t *u, int6
   const bool dense = n <= (int64_t(1) << win_dense_log(vbytes));
   if (nitems > 0 && !dense)
     hipLaunchKernelGGL(k_wplan_units<0>, dim3((nitems + 255) / 256), dim3(256), 0, s, rows, nlong,
-                       nitems, arp, P, items, static_cast<int32_t *>(nullptr));
+                       nitems, arp, P, items);
   if (nsegs > 0)
     hipLaunchKernelGGL(k_wplan_units<1>, dim3((nsegs + 255) / 256), dim3(256), 0, s, rows, nlong,
-                       nsegs, arp, P, segs, static_cast<int32_t *>(nullptr));
+                       nsegs, arp, P, segs);
   if (nslots > 0)
-    hipLaunchKernelGGL(k_wplan_units<2>, dim3((nslots + 255) / 256), dim3(256), 0, s, rows, nlong,
-                       nslots, arp, P, items, slot_row);
+    hipLaunchKernelGGL(k_wplan_ranges, dim3((nslots * WAVE + 255) / 256), dim3(256), 0, s, rows,
+                       nlong, nslots, arp, P, items, slot_row);
 }
 
 template <typename T>
