@@ -373,9 +373,11 @@ void give_event(int dev, hipEvent_t e) {
   g_ev_free.emplace_back(dev, e);
 }
 
-// Auxiliary streams outlive plans too (one is taken per plan that computes
-// and returned when the plan is destroyed); default priority, not
-// synchronized with the null stream.
+// Auxiliary streams outlive plans too: one is taken for a compute and returned
+// when all of it is enqueued and joined (kept by the plan to its end when the
+// compute failed: a capture may still hold it).  A stream per plan cost each
+// plan's first compute 0.16 ms.  Default priority, not synchronized with the
+// null stream.
 std::vector<std::pair<int, hipStream_t>> g_aux_free;
 
 hipError_t take_aux(int dev, hipStream_t *st) {
@@ -1250,6 +1252,8 @@ extern "C" int spgemm_compute(spgemm_plan plan, const spgemm_csr *A, const spgem
     release_compute(p, s);
     return rc;
   }
+  give_aux(p->dev, p->aux);  // joined: what a later user adds follows its own fork
+  p->aux = nullptr;
   if (p->events) {
     // waits only for the timed stages (the copy into C may still run)
     static const int kComputeStages[] = {SPGEMM_T_TINY,   SPGEMM_T_MEDIUM,    SPGEMM_T_LONG,
