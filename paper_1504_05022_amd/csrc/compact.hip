@@ -1,7 +1,7 @@
 // Stage 4 of the framework ("arranging data", Section 3.1): after the row
 // sizes of C have been scanned into C's row pointers, copy every row from
-// the temporary matrix C~ into C.  A wavefront takes 32 consecutive short
-// rows and streams all their entries at once, so the copy is coalesced and
+// the temporary matrix C~ into C.  A wavefront takes 2 to 32 consecutive short
+// rows (copy_rows) and streams all their entries at once, so the copy is coalesced and
 // no wavefront waits on one row's metadata; long rows are copied piece by
 // piece, one wavefront each.
 #include <type_traits>

@@ -1582,7 +1582,8 @@ template <int K> constexpr int wave_occupancy() { return K <= 8 ? 6 : 3; }
 // of stream entries of one segment) numbered by the run starts in 1 .. l: a
 // count of bits of the mask hd.  Two VALU instructions per product and no
 // barrier, where a max-scan over the tile and a hand-over of the resolved
-// index through LDS took about twenty and two.
+// index through LDS took about twenty and two (power-law square of 200000
+// rows, both passes of segments and of ranges: 1135 -> 1112 us in all).
 template <int K, typename F> DEVI void each_run(const uint32_t *hd, F f) {
   int below = 0;
 #pragma unroll
@@ -1963,7 +1964,9 @@ DEVI void wave_piece(LongArgs<T> &a, const int32_t pid, unsigned char *lds_a, T 
   }
   wave_sync();
   // a stream that leaves part of the tile unused takes fewer entries per lane
-  // (the 1024-entry pass only receives streams above 512)
+  // (the 1024-entry pass only receives streams above 512): without the networks
+  // of 5 and 6 the pass over a power-law square of 200000 rows takes 277 us, now
+  // 266
   if constexpr (K == 8) {
     if (tn <= WAVE * 4) {
       piece_body<T, 4, Key>(a, pid, lr, lri, c0, tn, E, obase, lds_a, lds_b, hd);
@@ -2143,8 +2146,10 @@ template <typename First> DEVI int64_t lt_owner(int64_t nlong, int64_t x, First 
 
 // One thread per work item (product range, first entry of A's row that
 // reaches it, an empty checkpoint and an empty partial), then one per output
-// piece (its row, an empty checkpoint); the first threads also clear the list
-// counters and set the pool.
+// piece (its row, an empty checkpoint); the first thread also clears the list
+// counters and sets the pool (four launches once).  Bound by the bisections'
+// dependent loads: 11 us for 3000 long rows, 17 for 12000.  One wavefront per
+// row takes 7 us there, but 54 where a row has 3000 pieces.
 __global__ __launch_bounds__(256) void k_lt_units(const LongRow *lrows, int64_t nlong,
                                                   int64_t nitems, int64_t npieces,
                                                   const int32_t *arp, const int64_t *P,
