@@ -213,8 +213,9 @@ int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B, const spgemm_option
  * Stages 3-4: computes every row of C into C~ (bin groups 1-5 with their
  * own kernels), sums the row sizes into C's row pointers, allocates C's
  * column and value arrays (exactly nnz(C) entries) with the plan's allocator
- * and copies C~ into C.  Synchronizes `stream` once to read nnz(C), plus once
- * more per exhaustion of the long-row pool (the pool then grows 2x and the
+ * and copies C~ into C.  Waits on `stream` once to read nnz(C), once more
+ * where column ranges of long rows are left to larger kernels, and once more
+ * per exhaustion of the long-row pool (the pool then grows 2x and the
  * affected long rows resume from their checkpoints).  C receives rows = m,
  * cols = n, nnz, three owned arrays and A's dtype.  Entries of every row are
  * in ascending column order without duplicates; structural products that

@@ -245,3 +245,37 @@ def test_one_shot_batch_of_many_problems(count):
         mag = oracle.spgemm(a.astype(np.float64).as_tuple()[:4] + (np.abs(a.val.astype(float)),),
                             b.astype(np.float64).as_tuple()[:4] + (np.abs(b.val.astype(float)),))
         assert np.all(np.abs(v - ref.val) <= scale * mag.val)
+
+
+def test_products_from_threads_on_their_streams():
+    """Plans of several threads, each on a stream of its own, share the second
+    streams and wait for their own records: same results as one by one."""
+    import threading
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, Plan, spgemm
+    cases = [S.config2(n=n, cap=1500)[0] for n in (3000, 5000, 7000)]
+    mats = [CsrMatrix.from_host(A) for A in cases]
+    refs = [spgemm(M, M).to_host() for M in mats]
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for r in range(8):
+                    M, ref = mats[(k + r) % 3], refs[(k + r) % 3]
+                    plan = Plan(M, M)
+                    for _ in range(2):
+                        C = plan.compute()
+                        torch.cuda.current_stream().synchronize()
+                        for got, want in zip(C.to_host()[2:], ref[2:]):
+                            assert np.array_equal(got, want)
+        except BaseException as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
