@@ -69,13 +69,13 @@ __global__ __launch_bounds__(256) void k_grad_b(const int64_t *tptr, const int32
 // line or two per b_j* and array), not the VALU (37% busy).  One lane per
 // entry of A, as before, left ragged rows waiting on their longest entry and
 // touched 64 lines per load: 2374 us where B is narrow (A 300000^2 with 6M
-// entries x B 300000x4096, 32 per row, binary32; now 1098), 1389 us where it
+// entries x B 300000x4096, 32 per row, binary32; now 1046), 1389 us where it
 // is wide (A 50000^2 with 600k entries x B 50000^2, 12 per row, binary64; now
 // 119).  The chunk's rows are found by the whole wavefront (wave_row_of; a
 // bisection by one lane: 1187 and 136).  Few entries per chunk spread the long
 // tail of a small product; with the bitmap a row cut by a chunk is mapped
-// twice, so chunks are longer there (64 / 128 / 256 entries measure 1128 / 1098
-// / 1112 us narrow, 64 / 128 136 / 163 wide).  Overlapping the next group's
+// twice, so chunks are longer there (64 / 128 / 256 entries 1128 / 1098 / 1112
+// us narrow, 64 / 128 136 / 163 wide, each when measured).  Overlapping the next group's
 // loads of B with this group's dC costs more in resident wavefronts than it
 // hides (1371).
 constexpr int BW_WIN = 2048;  // products whose entry starts the bit mask covers
@@ -83,7 +83,11 @@ template <bool DENSE> constexpr int bw_ch() { return DENSE ? 128 : 64; }
 // blocks of 64 products whose loads are in flight together (narrow: 3 / 4 / 6
 // blocks 1333 / 1257 / 1187 us; wide: 134 / 128 / 119)
 constexpr int BW_U = 6;
-constexpr int BW_SC = 4;  // passes of a row of C whose column loads are in flight together
+// consecutive entries of a row of C per lane when its columns are mapped: a
+// lane joins the bits that fall into one word, so that few lanes meet on one
+// (one entry per lane: 1100 us narrow, now 1046; 2 / 8 per lane 1083 / 1170),
+// and passes of loads in flight when they are sampled
+constexpr int BW_SC = 4;
 // columns of the bitmap: 1 KB of it and 512 bytes of ranks per wavefront,
 // where a dense copy of a dC row of 4096 columns took 16 KB and left 9
 // wavefronts per CU (the same time, but only up to 2048 binary64 columns)
@@ -291,14 +295,21 @@ __global__ __launch_bounds__(BW_NT) void k_grad_entries(
                 const int32_t m1 = __builtin_amdgcn_readlane(c1, hl);
                 for (int32_t xs = m0; xs < m1; xs += BW_SC * WAVE) {
                   int32_t cc[BW_SC];
+                  const int32_t x = xs + ln * BW_SC;
 #pragma unroll
-                  for (int p = 0; p < BW_SC; ++p) {
-                    const int32_t x = xs + p * WAVE + ln;
-                    cc[p] = ccol[x < m1 ? x : m1 - 1];
+                  for (int p = 0; p < BW_SC; ++p) cc[p] = ccol[x + p < m1 ? x + p : m1 - 1];
+                  if (x < m1) {
+                    int32_t wd = cc[0] >> 5;
+                    uint32_t mk = 1u << (cc[0] & 31);
+#pragma unroll
+                    for (int p = 1; p < BW_SC; ++p) {
+                      const bool next = cc[p] >> 5 != wd;
+                      if (next) atomicOr(&tb.bits[wd], mk);
+                      mk = (next ? 0u : mk) | 1u << (cc[p] & 31);
+                      wd = cc[p] >> 5;
+                    }
+                    atomicOr(&tb.bits[wd], mk);
                   }
-#pragma unroll
-                  for (int p = 0; p < BW_SC; ++p)
-                    if (xs + p * WAVE + ln < m1) atomicOr(&tb.bits[cc[p] >> 5], 1u << (cc[p] & 31));
                 }
                 mapped = rc;
                 mapped_c0 = m0;
