@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "mailbox.hpp"
 
 using namespace spg;
 
@@ -147,36 +148,36 @@ void *pinned_staging() {
   return buf;
 }
 
+// Zeroed pinned memory that kernels write (nullptr if there is none).
+void *pinned_zeroed(size_t bytes) {
+  void *p = nullptr;
+  if (hipHostMalloc(&p, bytes, hipHostMallocMapped | hipHostMallocPortable |
+                                   hipHostMallocCoherent) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  std::memset(p, 0, bytes);
+  return p;
+}
+
 // Records that kernels write straight into pinned host memory, two slots per
 // thread (the summary of analyze, the status of compute): the host waits for
 // the token of its request instead of for a copy command and the stream.
-struct HostSlots {
-  HostSlot slot[2];
-  uint64_t next;  // last token given out
-};
-
-HostSlots *host_slots() {
-  thread_local HostSlots *hs = nullptr;
-  if (!hs) {
-    void *p = nullptr;
-    if (hipHostMalloc(&p, sizeof(HostSlots), hipHostMallocMapped | hipHostMallocPortable |
-                                                 hipHostMallocCoherent) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    std::memset(p, 0, sizeof(HostSlots));
-    hs = static_cast<HostSlots *>(p);
-  }
-  return hs;
-}
-
-// A slot (nullptr if there is none: the kernels then write to device memory,
-// read back by read_small) and the token that will announce its record.
+//
+// A slot (nullptr if there is none, or an earlier call's kernel has yet to
+// write to it: the kernels then write to device memory, read back by
+// read_small) and the token that will announce its record.
 HostSlot *take_slot(int which, uint64_t *token) {
-  HostSlots *hs = host_slots();
-  if (!hs) return nullptr;
-  *token = ++hs->next;
-  return &hs->slot[which];
+  thread_local HostSlot *slots = nullptr;
+  thread_local Mailbox box[2];
+  if (!slots) {
+    slots = static_cast<HostSlot *>(pinned_zeroed(2 * sizeof(HostSlot)));
+    if (!slots) return nullptr;
+    for (int i = 0; i < 2; ++i) box[i].token = &slots[i].token;
+  }
+  if (!box[which].idle()) return nullptr;
+  *token = box[which].request();
+  return &slots[which];
 }
 
 // Waits for a token in pinned memory; a wait beyond a few milliseconds is left
@@ -226,30 +227,20 @@ namespace spg {
 // for (one such area per thread; larger records go by copy command).
 hipError_t read_words(void *dst, const void *src, int64_t words, hipStream_t s) {
   constexpr int64_t kMost = 8191;  // 64 KB with the token
-  thread_local uint64_t *area = nullptr;
-  thread_local uint64_t last = 0;
-  if (words <= kMost && !area) {
-    void *p = nullptr;
-    if (hipHostMalloc(&p, (kMost + 1) * 8,
-                      hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent) ==
-        hipSuccess) {
-      std::memset(p, 0, (kMost + 1) * 8);
-      area = static_cast<uint64_t *>(p);
-    } else {
-      (void)hipGetLastError();
-    }
-  }
-  if (words > kMost || !area) {
+  thread_local Mailbox box;
+  if (words <= kMost && !box.token)
+    box.token = static_cast<uint64_t *>(pinned_zeroed((kMost + 1) * 8));
+  if (words > kMost || !box.token || !box.idle()) {
     hipError_t e = hipMemcpyAsync(dst, src, static_cast<size_t>(words) * 8,
                                   hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     return e;
   }
-  const uint64_t token = ++last;
-  launch_publish(static_cast<const uint64_t *>(src), words, area + 1, area, token, s);
+  const uint64_t token = box.request();
+  launch_publish(static_cast<const uint64_t *>(src), words, box.token + 1, box.token, token, s);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = wait_token(area, token, s);
-  if (e == hipSuccess) std::memcpy(dst, area + 1, static_cast<size_t>(words) * 8);
+  if (e == hipSuccess) e = wait_token(box.token, token, s);
+  if (e == hipSuccess) std::memcpy(dst, box.token + 1, static_cast<size_t>(words) * 8);
   return e;
 }
 
