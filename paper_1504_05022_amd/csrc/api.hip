@@ -11,7 +11,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -160,47 +159,14 @@ void *pinned_zeroed(size_t bytes) {
   return p;
 }
 
-// Records that kernels write straight into pinned host memory, two slots per
-// thread (the summary of analyze, the status of compute): the host waits for
-// the token of its request instead of for a copy command and the stream.
-//
-// A slot (nullptr if there is none, or an earlier call's kernel has yet to
-// write to it: the kernels then write to device memory, read back by
-// read_small) and the token that will announce its record.
-HostSlot *take_slot(int which, uint64_t *token) {
-  thread_local HostSlot *slots = nullptr;
-  thread_local Mailbox box[2];
-  if (!slots) {
-    slots = static_cast<HostSlot *>(pinned_zeroed(2 * sizeof(HostSlot)));
-    if (!slots) return nullptr;
-    for (int i = 0; i < 2; ++i) box[i].token = &slots[i].token;
-  }
-  if (!box[which].idle()) return nullptr;
-  *token = box[which].request();
-  return &slots[which];
-}
-
-// Waits for a token in pinned memory; a wait beyond a few milliseconds is left
-// to the runtime, which also reports errors of the stream.
-hipError_t wait_token(const uint64_t *at, uint64_t token, hipStream_t s) {
-  const auto arrived = [&] { return __atomic_load_n(at, __ATOMIC_ACQUIRE) == token; };
-  const auto t0 = std::chrono::steady_clock::now();
-  for (int spin = 0; !arrived(); ++spin) {
-    __builtin_ia32_pause();
-    if ((spin & 255) == 255 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(5)) {
-      const hipError_t e = hipStreamSynchronize(s);
-      if (e != hipSuccess) return e;
-      if (!arrived()) return hipErrorUnknown;
-      break;
-    }
-  }
-  return hipSuccess;
-}
-
-hipError_t wait_slot(HostSlot *slot, uint64_t token, void *dst, size_t bytes, hipStream_t s) {
-  const hipError_t e = wait_token(&slot->token, token, s);
-  if (e == hipSuccess) std::memcpy(dst, slot->word, bytes);
-  return e;
+// Waits for the latest record of a mailbox, asked for on stream s.
+hipError_t wait_record(Mailbox &box, hipStream_t s) {
+  return static_cast<hipError_t>(wait_mailbox(
+      box, [&] { return static_cast<int>(hipStreamSynchronize(s)); },
+      [] {
+        const hipError_t e = hipGetLastError();
+        return static_cast<int>(e != hipSuccess ? e : hipErrorUnknown);
+      }));
 }
 
 // Device -> host copy of a small record through the pinned staging area;
@@ -217,6 +183,39 @@ hipError_t read_small(void *dst, const void *src, size_t bytes, hipStream_t s) {
   if (e == hipSuccess) std::memcpy(dst, stage, bytes);
   return e;
 }
+
+// Records that kernels write straight into pinned host memory, two slots per
+// thread (the summary of analyze, the status of compute): the host waits for
+// the token of its request instead of for a copy command and the stream.
+// Without a slot (no pinned memory, or an earlier call's kernel has yet to
+// write to it) the kernels write to device memory, read back by read_small.
+struct SlotRequest {
+  HostSlot *slot = nullptr;
+  Mailbox *box = nullptr;
+  uint64_t token = 0;
+
+  void ask(int which) {
+    thread_local HostSlot *slots = nullptr;
+    thread_local Mailbox boxes[2];
+    slot = nullptr;
+    if (!slots) {
+      slots = static_cast<HostSlot *>(pinned_zeroed(2 * sizeof(HostSlot)));
+      if (!slots) return;
+      for (int i = 0; i < 2; ++i) boxes[i].token = &slots[i].token;
+    }
+    box = &boxes[which];
+    if (!box->idle()) return;
+    token = box->request();
+    slot = &slots[which];
+  }
+  // the record (src: its place in device memory without a slot), and any
+  // error of the launches before it
+  hipError_t wait(void *dst, const void *src, size_t bytes, hipStream_t s) {
+    hipError_t e = slot ? wait_record(*box, s) : read_small(dst, src, bytes, s);
+    if (slot && e == hipSuccess) std::memcpy(dst, slot->word, bytes);
+    return e == hipSuccess ? hipGetLastError() : e;
+  }
+};
 
 }  // namespace
 
@@ -238,10 +237,10 @@ hipError_t read_words(void *dst, const void *src, int64_t words, hipStream_t s) 
   }
   const uint64_t token = box.request();
   launch_publish(static_cast<const uint64_t *>(src), words, box.token + 1, box.token, token, s);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = wait_token(box.token, token, s);
-  if (e == hipSuccess) std::memcpy(dst, box.token + 1, static_cast<size_t>(words) * 8);
-  return e;
+  const hipError_t e = wait_record(box, s);
+  if (e != hipSuccess) return e;
+  std::memcpy(dst, box.token + 1, static_cast<size_t>(words) * 8);
+  return hipGetLastError();
 }
 
 }  // namespace spg
@@ -613,8 +612,8 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   scan_row_lengths(A->col_idx, B->row_ptr, p->nnzA, p->P, p->bst, p->part, s);
   stage_end(p, SPGEMM_T_UPPER, s);
   // stage 2 (Algorithm 3): u_i, bin lists, C~ offsets, summary
-  uint64_t token = 0;
-  HostSlot *slot = take_slot(0, &token);
+  SlotRequest summary;
+  summary.ask(0);
   stage_begin(p, SPGEMM_T_BIN, s);
   {
     RowStatsArgs ra;
@@ -638,14 +637,12 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
     ra.bpart = at<int64_t>(p->ws, obp);
     ra.tot = at<int64_t>(p->ws, otot);
     ra.sum = p->dsum;
-    ra.slot = slot;
-    ra.token = token;
+    ra.slot = summary.slot;
+    ra.token = summary.token;
     launch_binning(ra, s);
   }
   stage_end(p, SPGEMM_T_BIN, s);
-  hipError_t e = slot ? wait_slot(slot, token, p->hsum, sizeof(Summary), s)
-                      : read_small(p->hsum, p->dsum, sizeof(Summary), s);
-  if (e == hipSuccess) e = hipGetLastError();
+  const hipError_t e = summary.wait(p->hsum, p->dsum, sizeof(Summary), s);
   if (e != hipSuccess) {
     destroy_plan(p);
     return hip_fail(e, "analyze");
@@ -930,24 +927,21 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     if (set) launch_set_pool(p->dpool, *p->hpool, s);
     return SPGEMM_OK;
   };
-  uint64_t token = 0;
-  HostSlot *slot = nullptr;
+  SlotRequest status;
   auto wait_status = [&]() -> int {
-    HIP_TRY(slot ? wait_slot(slot, token, p->hstat, sizeof(ComputeStatus), s)
-                 : read_small(p->hstat, p->dstat, sizeof(ComputeStatus), s));
-    HIP_TRY(hipGetLastError());
+    HIP_TRY(status.wait(p->hstat, p->dstat, sizeof(ComputeStatus), s));
     return SPGEMM_OK;
   };
   auto read_status = [&]() -> int {
-    slot = take_slot(1, &token);
-    launch_status(p->rowoff, m, p->dpool, lcnt, p->dstat, slot, token, s);
+    status.ask(1);
+    launch_status(p->rowoff, m, p->dpool, lcnt, p->dstat, status.slot, status.token, s);
     return wait_status();
   };
   // row pointers of C, and the status with their total
   auto scan_rows = [&]() {
-    slot = take_slot(1, &token);
+    status.ask(1);
     scan_rows_status(p->rownnz, m, p->rowoff, p->part, legacy ? p->dpool : nullptr,
-                     legacy ? lcnt : nullptr, p->dstat, slot, token, s);
+                     legacy ? lcnt : nullptr, p->dstat, status.slot, status.token, s);
     // where every piece goes in its row: not needed before C is allocated
     if (legacy) scan_piece_counts(pieces, npieces, pscan, ppart, s);
   };

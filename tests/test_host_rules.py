@@ -35,13 +35,36 @@ int main() {
   b.token = &word;
   CHECK(b.idle());
   const uint64_t t1 = b.request();
-  CHECK(t1 != 0 && !b.idle() && !b.arrived(t1));
+  CHECK(t1 != 0 && !b.idle());
   word = t1;  // the kernel writes
-  CHECK(b.arrived(t1) && b.idle());
+  CHECK(b.idle());
   const uint64_t t2 = b.request();  // left without a wait
   CHECK(t2 != t1 && !b.idle());
   CHECK(!b.idle());
   word = t2;  // late
   CHECK(b.idle());
+}
+""")
+
+
+def test_record_of_a_kernel_that_was_not_launched(tmp_path):
+    """The wait reports the launch's error, and takes it away: the thread's
+    next call must not find it.  Errors of the stream come first, a record
+    that arrives during the wait for the stream is taken."""
+    run_cpp(tmp_path, ["mailbox.hpp"], r"""
+int main() {
+  uint64_t word = 0;
+  spg::Mailbox b;
+  b.token = &word;
+  int last = 9, syncs = 0;  // as left by the failed launch
+  auto why = [&] { const int e = last; last = 0; return e; };
+  b.request();
+  CHECK(spg::wait_mailbox(b, [&] { ++syncs; return 0; }, why) == 9);
+  CHECK(syncs == 1 && last == 0 && b.idle());
+  b.request();
+  CHECK(spg::wait_mailbox(b, [&] { return 7; }, why) == 7 && !b.idle());
+  CHECK(spg::wait_mailbox(b, [&] { word = b.asked; return 0; }, why) == 0 && b.idle());
+  word = b.request();
+  CHECK(spg::wait_mailbox(b, [&] { return 7; }, why) == 0);
 }
 """)
