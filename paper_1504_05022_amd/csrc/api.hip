@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -134,19 +135,6 @@ int check_csr(const spgemm_csr *M, const char *name) {
   return SPGEMM_OK;
 }
 
-// Pinned staging for the small device<->host records, one per thread,
-// allocated once (hipHostMalloc is far too slow to call per plan).
-void *pinned_staging() {
-  thread_local void *buf = nullptr;
-  if (!buf) {
-    if (hipHostMalloc(&buf, 4096, hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      buf = nullptr;
-    }
-  }
-  return buf;
-}
-
 // Zeroed pinned memory that kernels write (nullptr if there is none).
 void *pinned_zeroed(size_t bytes) {
   void *p = nullptr;
@@ -158,6 +146,11 @@ void *pinned_zeroed(size_t bytes) {
   std::memset(p, 0, bytes);
   return p;
 }
+void pinned_free(void *p) { (void)hipHostFree(p); }
+
+constexpr int64_t kAreaWords = 8191;  // 64 KB with the token
+MailboxPool g_slots(sizeof(HostSlot), offsetof(HostSlot, token), pinned_zeroed, pinned_free);
+MailboxPool g_areas((kAreaWords + 1) * 8, 0, pinned_zeroed, pinned_free);
 
 // Waits for the latest record of a mailbox, asked for on stream s.
 hipError_t wait_record(Mailbox &box, hipStream_t s) {
@@ -169,49 +162,48 @@ hipError_t wait_record(Mailbox &box, hipStream_t s) {
       }));
 }
 
-// Device -> host copy of a small record through the pinned staging area;
-// synchronizes the stream.
+// Device -> host copy of a small record through pinned memory; synchronizes
+// the stream.
 hipError_t read_small(void *dst, const void *src, size_t bytes, hipStream_t s) {
-  void *stage = pinned_staging();
-  if (!stage || bytes > 4096) {
+  MailboxLease stage(g_slots);
+  if (!stage.box || bytes > sizeof(HostSlot::word)) {
     hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     return e;
   }
-  hipError_t e = hipMemcpyAsync(stage, src, bytes, hipMemcpyDeviceToHost, s);
+  HostSlot *slot = static_cast<HostSlot *>(stage.box->mem);
+  hipError_t e = hipMemcpyAsync(slot->word, src, bytes, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess) std::memcpy(dst, stage, bytes);
+  if (e == hipSuccess)
+    std::memcpy(dst, slot->word, bytes);
+  else
+    (void)stage.box->request();  // the copy may yet be made
   return e;
 }
 
-// Records that kernels write straight into pinned host memory, two slots per
-// thread (the summary of analyze, the status of compute): the host waits for
-// the token of its request instead of for a copy command and the stream.
-// Without a slot (no pinned memory, or an earlier call's kernel has yet to
-// write to it) the kernels write to device memory, read back by read_small.
+// Records that kernels write straight into pinned host memory (the summary of
+// analyze, the status of compute): the host waits for the token of its request
+// instead of for a copy command and the stream.  Without a slot the kernels
+// write to device memory, read back by read_small.
 struct SlotRequest {
+  static KeptMailbox *kept() {
+    thread_local KeptMailbox k(g_slots);
+    return &k;
+  }
+  MailboxLease lease{g_slots, kept()};
   HostSlot *slot = nullptr;
-  Mailbox *box = nullptr;
   uint64_t token = 0;
 
-  void ask(int which) {
-    thread_local HostSlot *slots = nullptr;
-    thread_local Mailbox boxes[2];
+  void ask() {
     slot = nullptr;
-    if (!slots) {
-      slots = static_cast<HostSlot *>(pinned_zeroed(2 * sizeof(HostSlot)));
-      if (!slots) return;
-      for (int i = 0; i < 2; ++i) boxes[i].token = &slots[i].token;
-    }
-    box = &boxes[which];
-    if (!box->idle()) return;
-    token = box->request();
-    slot = &slots[which];
+    if (!lease.box || !lease.box->idle()) return;
+    token = lease.box->request();
+    slot = static_cast<HostSlot *>(lease.box->mem);
   }
   // the record (src: its place in device memory without a slot), and any
   // error of the launches before it
   hipError_t wait(void *dst, const void *src, size_t bytes, hipStream_t s) {
-    hipError_t e = slot ? wait_record(*box, s) : read_small(dst, src, bytes, s);
+    hipError_t e = slot ? wait_record(*lease.box, s) : read_small(dst, src, bytes, s);
     if (slot && e == hipSuccess) std::memcpy(dst, slot->word, bytes);
     return e == hipSuccess ? hipGetLastError() : e;
   }
@@ -223,24 +215,22 @@ namespace spg {
 
 // `words` 8-byte words of device memory, read back on the stream's order:
 // written into pinned memory by a kernel, with a token that the host waits
-// for (one such area per thread; larger records go by copy command).
+// for (larger records go by copy command).
 hipError_t read_words(void *dst, const void *src, int64_t words, hipStream_t s) {
-  constexpr int64_t kMost = 8191;  // 64 KB with the token
-  thread_local Mailbox box;
-  if (words <= kMost && !box.token)
-    box.token = static_cast<uint64_t *>(pinned_zeroed((kMost + 1) * 8));
-  if (words > kMost || !box.token || !box.idle()) {
-    hipError_t e = hipMemcpyAsync(dst, src, static_cast<size_t>(words) * 8,
-                                  hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    return e;
+  if (words <= kAreaWords) {
+    MailboxLease area(g_areas);
+    if (area.box) {
+      uint64_t *at = area.box->token;
+      launch_publish(static_cast<const uint64_t *>(src), words, at + 1, at, area.box->request(), s);
+      const hipError_t e = wait_record(*area.box, s);
+      if (e != hipSuccess) return e;
+      std::memcpy(dst, at + 1, static_cast<size_t>(words) * 8);
+      return hipGetLastError();
+    }
   }
-  const uint64_t token = box.request();
-  launch_publish(static_cast<const uint64_t *>(src), words, box.token + 1, box.token, token, s);
-  const hipError_t e = wait_record(box, s);
-  if (e != hipSuccess) return e;
-  std::memcpy(dst, box.token + 1, static_cast<size_t>(words) * 8);
-  return hipGetLastError();
+  hipError_t e = hipMemcpyAsync(dst, src, static_cast<size_t>(words) * 8, hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  return e;
 }
 
 }  // namespace spg
@@ -613,7 +603,7 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   stage_end(p, SPGEMM_T_UPPER, s);
   // stage 2 (Algorithm 3): u_i, bin lists, C~ offsets, summary
   SlotRequest summary;
-  summary.ask(0);
+  summary.ask();
   stage_begin(p, SPGEMM_T_BIN, s);
   {
     RowStatsArgs ra;
@@ -933,13 +923,13 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     return SPGEMM_OK;
   };
   auto read_status = [&]() -> int {
-    status.ask(1);
+    status.ask();
     launch_status(p->rowoff, m, p->dpool, lcnt, p->dstat, status.slot, status.token, s);
     return wait_status();
   };
   // row pointers of C, and the status with their total
   auto scan_rows = [&]() {
-    status.ask(1);
+    status.ask();
     scan_rows_status(p->rownnz, m, p->rowoff, p->part, legacy ? p->dpool : nullptr,
                      legacy ? lcnt : nullptr, p->dstat, status.slot, status.token, s);
     // where every piece goes in its row: not needed before C is allocated

@@ -988,9 +988,8 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   // if there are any
   scan_i64(dU, R, dCTO, dpart, s);
   std::vector<unsigned long long> hcnt(ncnt + count);
-  if (read_words(hcnt.data(), dcnt, ncnt + count, s) != hipSuccess)
-    return bfail(SPGEMM_EHIP, std::string("batch analysis failed: ") +
-                                  hipGetErrorString(hipGetLastError()));
+  if (const hipError_t re = read_words(hcnt.data(), dcnt, ncnt + count, s); re != hipSuccess)
+    return bfail(SPGEMM_EHIP, std::string("batch analysis failed: ") + hipGetErrorString(re));
 
   // problems of the batched kernels (rows up to 1024 products, 32-bit keys);
   // C~ holds u_i entries for each of their rows (hybrid allocation)
@@ -1100,9 +1099,8 @@ int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *
   hipLaunchKernelGGL(k_bm_gather, dim3(static_cast<unsigned int>((count + 256) / 256)), dim3(256),
                      0, s, dprob, count, dRO, R, dg);
   std::vector<int64_t> hg(count + 1);
-  if (read_words(hg.data(), dg, count + 1, s) != hipSuccess)
-    return bfail(SPGEMM_EHIP, std::string("batch numeric stage failed: ") +
-                                  hipGetErrorString(hipGetLastError()));
+  if (const hipError_t re = read_words(hg.data(), dg, count + 1, s); re != hipSuccess)
+    return bfail(SPGEMM_EHIP, std::string("batch numeric stage failed: ") + hipGetErrorString(re));
 
   // fallback problems through the plain path (their outputs are moved into
   // the output block below)

@@ -2,9 +2,12 @@
 // when such memory may be asked for another record.  Host code only.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <chrono>
+#include <mutex>
+#include <new>
 
 namespace spg {
 
@@ -14,8 +17,10 @@ namespace spg {
 // next request, possibly on a stream that nothing orders behind it, must not
 // get the same memory until that kernel's token has come.
 struct Mailbox {
-  uint64_t *token = nullptr;  // in pinned memory, 0 at first
+  void *mem = nullptr;        // pinned memory, zeroed at first
+  uint64_t *token = nullptr;  // in it
   uint64_t asked = 0;         // token of the latest request
+  Mailbox *next = nullptr;    // in its pool
 
   // no kernel is still to write here: the record of the latest request came
   bool idle() const { return __atomic_load_n(token, __ATOMIC_ACQUIRE) == asked; }
@@ -43,5 +48,110 @@ template <typename Sync, typename Why> int wait_mailbox(Mailbox &box, Sync sync,
   }
   return 0;
 }
+
+// Mailboxes for the calls of every thread, given back when the call or its
+// thread ends, so that threads leave nothing behind (allocating pinned memory
+// is far too slow to do it per call).  At most kKeep idle ones are kept; of
+// those left by failed calls, whose kernels or copies may yet write, at most
+// kLeft are replaced: take() then gives none, and records go by copy.
+class MailboxPool {
+ public:
+  static constexpr int kKeep = 64, kLeft = 16;
+
+  // token_at: offset of the token in the memory of a mailbox; alloc: zeroed
+  // pinned memory, nullptr if there is none
+  MailboxPool(size_t bytes, size_t token_at, void *(*alloc)(size_t), void (*release)(void *))
+      : bytes_(bytes), token_at_(token_at), alloc_(alloc), release_(release) {}
+
+  Mailbox *take() {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      for (Mailbox **at = &free_; *at; at = &(*at)->next) {
+        Mailbox *b = *at;
+        if (!b->idle()) continue;
+        *at = b->next;
+        --count_;
+        return b;
+      }
+      if (count_ >= kLeft) return nullptr;  // none of them idle
+    }
+    Mailbox *b = new (std::nothrow) Mailbox();
+    if (b) b->mem = alloc_(bytes_);
+    if (b && !b->mem) {
+      delete b;
+      b = nullptr;
+    }
+    if (b) b->token = reinterpret_cast<uint64_t *>(static_cast<char *>(b->mem) + token_at_);
+    return b;
+  }
+
+  void give(Mailbox *b) {
+    if (!b) return;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (count_ < kKeep || !b->idle()) {
+        b->next = free_;
+        free_ = b;
+        ++count_;
+        return;
+      }
+    }
+    release_(b->mem);
+    delete b;
+  }
+
+ private:
+  const size_t bytes_, token_at_;
+  void *(*const alloc_)(size_t);
+  void (*const release_)(void *);
+  std::mutex mu_;
+  Mailbox *free_ = nullptr;
+  int count_ = 0;
+};
+
+// The mailbox that stays with a thread from one of its calls to the next
+// (taking it from the pool in every call: 54 instead of 51 us for a product of
+// two reads and seven launches).
+struct KeptMailbox {
+  MailboxPool &pool;
+  Mailbox *box = nullptr;
+  bool lent = false;  // to a call of the thread that has not ended
+  explicit KeptMailbox(MailboxPool &p) : pool(p) {}
+  ~KeptMailbox() { pool.give(box); }
+};
+
+// A mailbox for the length of a call: the thread's own, or another while
+// that one is taken or an earlier kernel may still write to it.
+class MailboxLease {
+ public:
+  explicit MailboxLease(MailboxPool &pool, KeptMailbox *kept = nullptr)
+      : box(nullptr), pool_(pool), kept_(kept && !kept->lent ? kept : nullptr) {
+    if (kept_) {
+      kept_->lent = true;
+      box = kept_->box;
+      if (box && !box->idle()) {
+        pool.give(box);
+        box = nullptr;
+      }
+    }
+    if (!box) box = pool.take();
+  }
+  ~MailboxLease() {
+    if (!kept_) {
+      pool_.give(box);
+      return;
+    }
+    kept_->box = box;
+    kept_->lent = false;
+  }
+  MailboxLease(const MailboxLease &) = delete;
+  MailboxLease &operator=(const MailboxLease &) = delete;
+
+  Mailbox *box;  // nullptr: none to be had
+
+ private:
+  MailboxPool &pool_;
+  KeptMailbox *kept_;
+};
 
 }  // namespace spg

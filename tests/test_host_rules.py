@@ -1,5 +1,6 @@
 """Host-side rules of the library's sources, compiled with the host compiler:
-when pinned memory that a kernel writes may be asked for another record."""
+pinned memory that kernels write, when it may be asked for another record and
+who holds it."""
 import os
 import subprocess
 
@@ -17,7 +18,8 @@ HEAD = r"""
 def run_cpp(tmp_path, includes, body, *flags):
     """Compile and run a program that checks `body`; fails with what it printed."""
     src = tmp_path / "check.cpp"
-    src.write_text(HEAD + "".join('#include "%s"\n' % i for i in includes) + body)
+    lines = ['#include "%s"\n' % i if i.endswith(".hpp") else "#include <%s>\n" % i for i in includes]
+    src.write_text(HEAD + "".join(lines) + body)
     exe = tmp_path / "check"
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-I", CSRC, *flags, str(src),
                            "-o", str(exe)])
@@ -68,3 +70,77 @@ int main() {
   CHECK(spg::wait_mailbox(b, [&] { return 7; }, why) == 0);
 }
 """)
+
+
+def test_mailboxes_outlive_threads_and_are_bounded(tmp_path):
+    """Threads that end leave their pinned memory to the next ones; a mailbox
+    left by a failed call is not handed out before its token and at most a few
+    are replaced; beyond what is kept, memory is released."""
+    run_cpp(tmp_path, ["mailbox.hpp", "thread", "vector"], r"""
+static int made = 0, freed = 0;
+static bool full = false;
+static void *get(size_t n) { if (full) return nullptr; ++made; return calloc(1, n); }
+static void put(void *p) { ++freed; free(p); }
+int main() {
+  using spg::Mailbox; using spg::MailboxPool;
+  MailboxPool pool(512, 504, get, put);
+  for (int i = 0; i < 100; ++i)  // one thread after another
+    std::thread([&] {
+      Mailbox *b = pool.take();
+      *b->token = b->request();
+      pool.give(b);
+    }).join();
+  CHECK(made == 1);
+  std::vector<Mailbox *> v;  // many calls at once
+  for (int i = 0; i < 100; ++i) v.push_back(pool.take());
+  CHECK(made == 100);
+  for (Mailbox *b : v) pool.give(b);
+  CHECK(freed == 100 - MailboxPool::kKeep);
+  MailboxPool late(512, 504, get, put);
+  made = 0;
+  v.clear();
+  for (int i = 0; i < MailboxPool::kLeft; ++i) {
+    Mailbox *b = late.take();
+    for (Mailbox *o : v) CHECK(b != o);
+    b->request();  // its kernel has not written when the call ends
+    v.push_back(b);
+    late.give(b);
+  }
+  CHECK(made == MailboxPool::kLeft && late.take() == nullptr);
+  *v[3]->token = v[3]->asked;  // one kernel writes
+  CHECK(late.take() == v[3]);
+  *v[3]->token = v[3]->request();
+  late.give(v[3]);
+  CHECK(late.take() == v[3]);
+  made = 0;
+  MailboxPool own(512, 504, get, put);
+  for (int t = 0; t < 3; ++t)  // a thread keeps its mailbox between calls
+    std::thread([&] {
+      spg::KeptMailbox kept(own);
+      Mailbox *first = nullptr;
+      for (int call = 0; call < 3; ++call) {
+        spg::MailboxLease lease(own, &kept);
+        if (!call) first = lease.box;
+        CHECK(lease.box == first);
+        spg::MailboxLease inner(own, &kept);  // a call inside this one
+        CHECK(inner.box && inner.box != first);
+        *first->token = first->request();
+      }
+    }).join();
+  CHECK(made == 2);
+  {
+    spg::KeptMailbox kept(own);
+    Mailbox *a = nullptr;
+    {
+      spg::MailboxLease lease(own, &kept);
+      a = lease.box;
+      a->request();  // left without a wait
+    }
+    spg::MailboxLease lease(own, &kept);
+    CHECK(lease.box != a);
+  }
+  MailboxPool none(512, 504, get, put);
+  full = true;
+  CHECK(none.take() == nullptr);
+}
+""", "-pthread")
