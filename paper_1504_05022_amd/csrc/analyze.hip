@@ -487,7 +487,8 @@ __global__ __launch_bounds__(BIN_NT) void k_bin_scan(int32_t *hist, int64_t *hpa
   if (t == 0) tot[c] = carry;
 }
 
-// Rows into their bins, C~ offsets; the first work-group writes the summary.
+// Rows into their bins, C~ offsets; the first work-group writes the summary
+// (unless k_summary does).
 template <int RPT>
 __global__ __launch_bounds__(BIN_NT) void k_bin_scatter(RowStatsArgs a) {
   __shared__ int64_t off[NBINS + 1];
@@ -522,8 +523,17 @@ __global__ __launch_bounds__(BIN_NT) void k_bin_scatter(RowStatsArgs a) {
   if (b == 0) {
     const int64_t sum_h = a.tot[NBINS];
     if (t == 0) a.cto[a.m] = sum_h;
-    write_summary(off, a.tot + NBINS + 1, a.P[a.nnz], sum_h, a.sum, a.slot, a.token);
+    if (!a.whole)
+      write_summary(off, a.tot + NBINS + 1, a.P[a.nnz], sum_h, a.sum, a.slot, a.token);
   }
+}
+
+// The summary once every work-group of k_bin_scatter is done.
+__global__ __launch_bounds__(WAVE) void k_summary(RowStatsArgs a) {
+  __shared__ int64_t off[NBINS + 1];
+  bin_offsets(a.tot, off);
+  __syncthreads();
+  write_summary(off, a.tot + NBINS + 1, a.P[a.nnz], a.tot[NBINS], a.sum, a.slot, a.token);
 }
 
 // Everything after stage 1's scan for up to ROWS_SMALL rows.
@@ -585,6 +595,10 @@ __global__ __launch_bounds__(SMALL_NT) void k_rows_small(RowStatsArgs a) {
     ho += all;
   }
   if (t == 0) a.cto[a.m] = ho;
+  if (a.whole) {
+    __threadfence();
+    __syncthreads();
+  }
   write_summary(off, stats, a.P[a.nnz], ho, a.sum, a.slot, a.token);
 }
 
@@ -613,6 +627,7 @@ void launch_binning(const RowStatsArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_bin_scatter<4>, dim3(nb), dim3(BIN_NT), 0, s, a);
   else
     hipLaunchKernelGGL(k_bin_scatter<1>, dim3(nb), dim3(BIN_NT), 0, s, a);
+  if (a.whole) hipLaunchKernelGGL(k_summary, dim3(1), dim3(WAVE), 0, s, a);
 }
 
 __global__ void k_fill_i64(int64_t *p, int64_t n, int64_t v) {

@@ -476,10 +476,12 @@ void stage_end(spgemm_plan p, int st, hipStream_t s) {
 
 }  // namespace
 
-extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
-                              const spgemm_options *opt, spgemm_alloc_fn alloc_fn,
-                              spgemm_free_fn free_fn, void *ctx, void *stream,
-                              spgemm_plan *plan, spgemm_info *info) {
+namespace {
+
+// whole: nothing of the analysis is still running on return.
+int analyze(const spgemm_csr *A, const spgemm_csr *B, const spgemm_options *opt,
+            spgemm_alloc_fn alloc_fn, spgemm_free_fn free_fn, void *ctx, void *stream, bool whole,
+            spgemm_plan *plan, spgemm_info *info) {
   if (!plan) return fail(SPGEMM_EINVAL, "plan is NULL");
   *plan = nullptr;
   int rc;
@@ -629,6 +631,7 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
     ra.sum = p->dsum;
     ra.slot = summary.slot;
     ra.token = summary.token;
+    ra.whole = whole;
     launch_binning(ra, s);
   }
   stage_end(p, SPGEMM_T_BIN, s);
@@ -666,6 +669,25 @@ extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
   *plan = p;
   return SPGEMM_OK;
 }
+
+}  // namespace
+
+// The plan may be computed on another stream next, which nothing orders behind
+// this one, so the wait is for all of the analysis (one small launch more).
+extern "C" int spgemm_analyze(const spgemm_csr *A, const spgemm_csr *B,
+                              const spgemm_options *opt, spgemm_alloc_fn alloc_fn,
+                              spgemm_free_fn free_fn, void *ctx, void *stream,
+                              spgemm_plan *plan, spgemm_info *info) {
+  return analyze(A, B, opt, alloc_fn, free_fn, ctx, stream, true, plan, info);
+}
+
+namespace spg {
+int analyze_in_order(const spgemm_csr *A, const spgemm_csr *B, const spgemm_options *opt,
+                     spgemm_alloc_fn alloc_fn, spgemm_free_fn free_fn, void *ctx, void *stream,
+                     spgemm_plan *plan, spgemm_info *info) {
+  return analyze(A, B, opt, alloc_fn, free_fn, ctx, stream, false, plan, info);
+}
+}  // namespace spg
 
 namespace {
 
@@ -1266,7 +1288,7 @@ extern "C" int spgemm_multiply(const spgemm_csr *A, const spgemm_csr *B,
                                spgemm_info *info) {
   if (!C) return fail(SPGEMM_EINVAL, "C is NULL");
   spgemm_plan plan = nullptr;
-  int rc = spgemm_analyze(A, B, opt, alloc_fn, free_fn, ctx, stream, &plan, nullptr);
+  int rc = analyze_in_order(A, B, opt, alloc_fn, free_fn, ctx, stream, &plan, nullptr);
   if (rc != SPGEMM_OK) return rc;
   rc = spgemm_compute(plan, A, B, C, stream, info);
   spgemm_plan_destroy(plan);

@@ -601,7 +601,7 @@ int spgemm_batch_create(int32_t count, const spgemm_csr *A, const spgemm_csr *B,
     std::vector<spgemm_info> infos(count);
     for (int32_t p = 0; p < count && rc == SPGEMM_OK; ++p) {
       spgemm_info I;
-      rc = spgemm_analyze(&A[p], &B[p], &o, alloc_fn, free_fn, ctx, stream, &cd.plans[p], &I);
+      rc = analyze_in_order(&A[p], &B[p], &o, alloc_fn, free_fn, ctx, stream, &cd.plans[p], &I);
       if (rc != SPGEMM_OK) break;
       if (ci == 0) {
         // the structure of C_p, once, with the plain path

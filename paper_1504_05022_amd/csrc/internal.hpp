@@ -365,6 +365,10 @@ struct RowStatsArgs {
   Summary *sum;
   HostSlot *slot;
   uint64_t token;
+  // the summary comes last: whoever has it may use the plan on any stream.
+  // Otherwise it comes with the scatter of the rows into their bins, and only
+  // work behind that on the same stream may use the plan.
+  bool whole;
 };
 // max u, sum u (long), sum min(u,n) (long), items, pieces,
 // sum u (multi), split entries, pool (single), sum min(u,n) (multi), spill,
@@ -600,6 +604,12 @@ void scan_rows_status(const int64_t *v, int64_t n, int64_t *out, int64_t *part, 
                       const LongCounters *cnt, ComputeStatus *st, HostSlot *slot, uint64_t token,
                       hipStream_t s);
 
+// spgemm_analyze for callers that go on on the same stream, or wait for it
+// before the plan leaves their hands: returns with the summary, while rows
+// are still being written to their bins.
+int analyze_in_order(const spgemm_csr *A, const spgemm_csr *B, const spgemm_options *opt,
+                     spgemm_alloc_fn alloc_fn, spgemm_free_fn free_fn, void *ctx, void *stream,
+                     spgemm_plan *plan, spgemm_info *info);
 // Access to a plan's device arrays (defined with the plan in api.hip).
 const int64_t *plan_rowoff(spgemm_plan p);
 const int64_t *plan_scan(spgemm_plan p);

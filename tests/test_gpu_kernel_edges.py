@@ -279,3 +279,30 @@ def test_products_from_threads_on_their_streams():
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+@pytest.mark.parametrize("m", [4000, 70000, 300000])
+def test_plan_computed_on_another_stream(m):
+    """A plan is whole when it is returned: computed at once on a stream that
+    nothing orders behind the one it was analysed on, by each form of the
+    binning (one work-group, one and four rows per thread)."""
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, Plan, spgemm
+    rng = np.random.default_rng(m)
+    B = CsrMatrix.from_host(_ragged(rng, 64, [0, 1, 2, 40] * 16, 5000, np.float64))
+    lens = np.arange(m) % 5
+    lens[-3:] = 60
+    A = CsrMatrix.from_host(_ragged(rng, m, lens, 64, np.float64))
+    ref = spgemm(A, B).to_host()
+    torch.cuda.synchronize()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    for r in range(5):
+        print("case: %d rows, pass %d" % (m, r), flush=True)
+        with torch.cuda.stream(s1):
+            plan = Plan(A, B)
+        with torch.cuda.stream(s2):
+            C = plan.compute()
+            s2.synchronize()
+        for got, want in zip(C.to_host()[2:], ref[2:]):
+            assert np.array_equal(got, want)
+        torch.cuda.synchronize()
