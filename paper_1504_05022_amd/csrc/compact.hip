@@ -82,9 +82,8 @@ void launch_compact(const CompactArgs<T> &a, int64_t m, int64_t products, int64_
   if (m <= 0) return;
   const auto rows = [&](auto r) {
     constexpr int RR = decltype(r)::value;
-    const int64_t waves = (m + RR - 1) / RR;
-    hipLaunchKernelGGL((k_compact_rows<T, RR>), dim3((waves * WAVE + CP_NT - 1) / CP_NT),
-                       dim3(CP_NT), 0, s, a, m);
+    hipLaunchKernelGGL((k_compact_rows<T, RR>), dim3(copy_threads(m, RR) / CP_NT), dim3(CP_NT), 0,
+                       s, a, m);
   };
   switch (copy_rows(m, products)) {
     case 32: rows(std::integral_constant<int, 32>{}); break;

@@ -1,0 +1,35 @@
+// Rules that size launches.  Host code only, without the HIP headers.
+#pragma once
+
+#include <stdint.h>
+
+namespace spg {
+
+// HIP takes fewer than 2^32 threads in a dimension of a launch.
+constexpr int64_t kLaunchThreads = (int64_t(1) << 32) - 1;
+
+constexpr int CP_NT = 256;   // threads per work-group of the copies into C
+constexpr int CP_ROWS = 32;  // short rows per wavefront, at most
+
+// Threads of a copy of `rows` rows, r per wavefront.
+inline int64_t copy_threads(int64_t rows, int r) {
+  const int64_t per = int64_t(CP_NT / 64) * r;  // rows per work-group
+  return (rows + per - 1) / per * CP_NT;
+}
+
+// Rows per wavefront for `rows` rows of `products` products: about 320 of
+// them, so that a wavefront's passes can all be in flight (32 rows each,
+// whatever their length, before: 20 banded products 453 us, now 370; the
+// short rows of a power-law square 83 and 68; C of 300000 narrow rows 231 and
+// 184), more rows where they are tiny (9 products: 32 rows 22 us, two 53), and
+// four wavefronts per SIMD or more; no fewer rows than a launch can hold.
+inline int copy_rows(int64_t rows, int64_t products) {
+  int r = CP_ROWS;
+  while (r > 2 &&
+         (static_cast<int64_t>(r) * products > 320 * rows || rows < 4096 * static_cast<int64_t>(r)) &&
+         copy_threads(rows, r / 2) <= kLaunchThreads)
+    r /= 2;
+  return r;
+}
+
+}  // namespace spg

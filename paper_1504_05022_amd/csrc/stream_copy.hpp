@@ -4,25 +4,11 @@
 #pragma once
 
 #include "common.hpp"
+#include "launch_rules.hpp"
 
 namespace spg {
 
-constexpr int CP_NT = 256;
-constexpr int CP_ROWS = 32;    // short rows per wavefront, at most
 constexpr int CP_BATCH = 4;    // passes whose loads are issued before their stores
-
-// Rows per wavefront for `rows` rows of `products` products: about 320 of
-// them, so that a wavefront's passes can all be in flight (32 rows each,
-// whatever their length, before: 20 banded products 453 us, now 370; the
-// short rows of a power-law square 83 and 68; C of 300000 narrow rows 231 and
-// 184), more rows where they are tiny (9 products: 32 rows 22 us, two 53), and
-// four wavefronts per SIMD or more.
-inline int copy_rows(int64_t rows, int64_t products) {
-  int r = CP_ROWS;
-  while (r > 2 && (static_cast<int64_t>(r) * products > 320 * rows || rows < 4096 * static_cast<int64_t>(r)))
-    r /= 2;
-  return r;
-}
 
 // LDS table of the sources of one wavefront.
 template <int R> struct CopyTable {

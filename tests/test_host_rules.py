@@ -1,6 +1,6 @@
 """Host-side rules of the library's sources, compiled with the host compiler:
 pinned memory that kernels write, when it may be asked for another record and
-who holds it."""
+who holds it, and the sizes of launches."""
 import os
 import subprocess
 
@@ -144,3 +144,23 @@ int main() {
   CHECK(none.take() == nullptr);
 }
 """, "-pthread")
+
+
+def test_copy_rows_stay_within_a_launch(tmp_path):
+    """Rows per wavefront of the copy into C: as measured up to sizes where
+    the launch would reach 2^32 threads, more of them beyond."""
+    run_cpp(tmp_path, ["launch_rules.hpp", "initializer_list"], r"""
+using spg::copy_rows; using spg::copy_threads;
+int main() {
+  CHECK(copy_rows(300000, 300000 * 9ll) == 32 && copy_rows(300000, 300000 * 200ll) == 2);
+  CHECK(copy_rows(1000, 5000) == 2 && copy_rows(0, 0) == 2);
+  for (int64_t rows = 1; rows < (int64_t(1) << 31) - 256; rows = rows * 5 / 4 + 1)
+    for (int64_t each : {0ll, 1ll, 9ll, 11ll, 30ll, 81ll, 500ll, 100000ll}) {
+      const int r = copy_rows(rows, rows * each);
+      CHECK(r == 2 || r == 4 || r == 8 || r == 16 || r == 32);
+      CHECK(copy_threads(rows, r) <= 0xffffffffll);
+      CHECK(r == 2 || copy_threads(rows, r / 2) > 0xffffffffll || (r * each <= 320 && rows >= 4096ll * r));
+    }
+  CHECK(copy_rows(1ll << 27, (1ll << 27) * 100) == 4);  // 2: 2^32 threads
+}
+""")
