@@ -32,4 +32,18 @@ inline int copy_rows(int64_t rows, int64_t products) {
   return r;
 }
 
+// The batch's copy: work-groups per row tile (a problem's rows in tiles of
+// tile_rows, the last or only one of each in part).  As many as the tiles'
+// rows fill on average, r per wavefront: one for every r rows a tile could hold
+// launches up to 32 for a problem of one row (10000 problems of five rows: 828
+// us, now 52).  A work-group takes the tile's further rows in turn.
+inline int copy_parts(int64_t tiles, int64_t rows, int r, int tile_rows) {
+  const int64_t per = int64_t(CP_NT / 64) * r;
+  int64_t parts = (rows + tiles * per - 1) / (tiles * per);
+  const int64_t most = kLaunchThreads / (CP_NT * tiles);
+  if (parts > tile_rows / per) parts = tile_rows / per;
+  if (parts > most) parts = most;
+  return parts > 1 ? static_cast<int>(parts) : 1;
+}
+
 }  // namespace spg

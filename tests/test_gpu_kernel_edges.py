@@ -306,3 +306,22 @@ def test_plan_computed_on_another_stream(m):
         for got, want in zip(C.to_host()[2:], ref[2:]):
             assert np.array_equal(got, want)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("sizes", [[1, 2, 5] * 60, [1] * 300 + [900], [700, 256, 257, 1, 300]])
+def test_one_shot_batch_copy_parts(sizes):
+    """Row tiles full and nearly empty, taken by one work-group and by many,
+    with long products per row (two rows per wavefront)."""
+    from paper_1504_05022_amd import CsrMatrix, batch_multiply
+    rng = np.random.default_rng(len(sizes))
+    k = 40
+    B = _ragged(rng, k, [20] * k, 500, np.float64)
+    As = [_ragged(rng, n, rng.integers(5, 30, n), k, np.float64) for n in sizes]
+    print("case: %d problems" % len(sizes), flush=True)
+    dB = CsrMatrix.from_host(B)
+    out = batch_multiply([(CsrMatrix.from_host(a), dB) for a in As])
+    for C, a in zip(out, As):
+        _, _, rp, ci, v = C.to_host()
+        ref = oracle.spgemm(a.as_tuple(), B.as_tuple())
+        assert np.array_equal(rp, ref.row_ptr) and np.array_equal(ci, ref.col_idx)
+        assert np.array_equal(v, ref.val)  # Gustavson's order

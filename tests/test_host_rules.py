@@ -164,3 +164,25 @@ int main() {
   CHECK(copy_rows(1ll << 27, (1ll << 27) * 100) == 4);  // 2: 2^32 threads
 }
 """)
+
+
+def test_batch_copy_work_groups(tmp_path):
+    """Work-groups per tile of the batch's copy: every place of a full tile,
+    one for problems of a few rows, and never 2^32 threads in a launch."""
+    run_cpp(tmp_path, ["launch_rules.hpp", "initializer_list"], r"""
+using spg::copy_parts;
+int main() {
+  CHECK(copy_parts(400, 400 * 256, 2, 256) == 32 && copy_parts(400, 400 * 256, 32, 256) == 2);
+  CHECK(copy_parts(10000, 10000 * 5, 2, 256) == 1 && copy_parts(10000, 10000, 32, 256) == 1);
+  CHECK(copy_parts(1, 0, 2, 256) == 1);
+  for (int64_t tiles = 1; tiles < (1 << 24); tiles = tiles * 3 + 1)
+    for (int64_t each : {0, 1, 9, 100, 255, 256})
+      for (int r : {2, 4, 8, 16, 32}) {
+        const int parts = copy_parts(tiles, tiles * each, r, 256);
+        CHECK(parts >= 1 && parts * 4 * r <= 256);
+        CHECK(tiles * parts * 256 <= 0xffffffffll);
+        CHECK(parts == 1 || (parts - 1) * 4 * r < each);
+      }
+  CHECK(copy_parts(1 << 20, 256ll << 20, 2, 256) == 15);  // 32: beyond a launch
+}
+""")
