@@ -299,8 +299,10 @@ void launch_validate(const int32_t *rp, const int32_t *ci, int64_t rows, int64_t
 // 2000 rows, against one of 8).
 constexpr int BIN_NT = 256;
 
-// What row i adds to the long-row planning sums (v: see kBlockStats).
-DEVI void long_sums(int64_t ui, int bin, const RowStatsArgs &a, int64_t (&v)[kBlockStats]) {
+// What a row with ne entries of A from e0 adds to the long-row planning sums
+// (v: see kBlockStats).
+DEVI void long_sums(int64_t ui, int bin, int32_t e0, int32_t ne, const RowStatsArgs &a,
+                    int64_t (&v)[kBlockStats]) {
   v[0] = v[0] > ui ? v[0] : ui;
   if (bin != LONG_BIN) return;
   const int64_t rmax = ui < a.ncols ? ui : a.ncols;
@@ -331,6 +333,16 @@ DEVI void long_sums(int64_t ui, int bin, const RowStatsArgs &a, int64_t (&v)[kBl
   v[13] += wp.partial;
   v[14] += wp.dslots;
   v[15] += wp.mode == WIN_NONE ? 1 : 0;
+  if (wp.mode == WIN_DD) {  // the lengths of eight of its rows of B
+    int wide = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t e = e0 + (static_cast<int64_t>(ne) * (2 * k + 1) >> 4);
+      wide += a.P[e + 1] - a.P[e] > 32 ? 1 : 0;
+    }
+    v[16] += ne;
+    v[17] += static_cast<int64_t>(ne) * wide;
+  }
 }
 
 // Work-group totals of the planning sums; the result of sum k is returned to
@@ -428,14 +440,15 @@ __global__ __launch_bounds__(BIN_NT) void k_row_stats(RowStatsArgs a) {
   for (int r = 0; r < RPT; ++r) {
     const int64_t i = (static_cast<int64_t>(blockIdx.x) * RPT + r) * BIN_NT + t;
     if (i >= a.m) continue;
-    const int64_t ui = a.P[a.arp[i + 1]] - a.P[a.arp[i]];
+    const int32_t e0 = a.arp[i], e1 = a.arp[i + 1];
+    const int64_t ui = a.P[e1] - a.P[e0];
     const int bin = bin_of(ui, a.be);
     a.u[i] = ui;
     if (ui == 0) a.rownnz[i] = 0;
     h += tilde_size(ui, bin, a);
     any_long |= bin == LONG_BIN;
     atomicAdd(&cnt[bin], 1);
-    long_sums(ui, bin, a, v);
+    long_sums(ui, bin, e0, e1 - e0, a, v);
   }
   int64_t hs;
   block_excl_sum<BIN_NT>(h, sm, hs);
@@ -568,7 +581,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_rows_small(RowStatsArgs a) {
     if (u[r] == 0) a.rownnz[i] = 0;
     any_long |= bin[r] == LONG_BIN;
     atomicAdd(&cnt[bin[r]], 1);
-    long_sums(u[r], bin[r], a, v);
+    long_sums(u[r], bin[r], e0[r], ne[r], a, v);
   }
   const int64_t st = block_stats<SMALL_NT>(v, any_long, red);  // (its barrier orders cnt too)
   if (t < kBlockStats) stats[t] = st;

@@ -974,7 +974,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     win_partition<T>(ea, wrows, wsegs, w_segs, wtable, wpkey, wpval, s);
     stage_end(p, SPGEMM_T_LONG_WAVE, s);
     stage_begin(p, SPGEMM_T_LONG_SYM, s);
-    win_symbolic<T>(ea, p->n, wrows, witems, w_items, wtable, wpkey, wslot, w_slots, wlist + 1,
+    win_symbolic<T>(ea, p->n, win_short_rows(S), wrows, witems, w_items, wtable, wpkey, wslot, w_slots, wlist + 1,
                     wlist, wdbits, wcnt, s);
     stage_end(p, SPGEMM_T_LONG_SYM, s);
     scan_i64(wcnt, w_items, wiscan, wpart, s);
@@ -1180,7 +1180,7 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
     // numeric pass of the long rows, straight into C
     stage_begin(p, SPGEMM_T_COMBINE, s);
     stage_begin(p, SPGEMM_T_COMBINE_WAVE, s);
-    win_numeric<T>(ea, p->n, wrows, witems, w_items, wtable, wpkey, wpval, wslot, w_slots,
+    win_numeric<T>(ea, p->n, win_short_rows(S), wrows, witems, w_items, wtable, wpkey, wpval, wslot, w_slots,
                    wlist + 1, wlist, wdbits, wdacc, wiscan, p->rowoff,
                    static_cast<int32_t *>(ccol), static_cast<T *>(cval), s);
     stage_end(p, SPGEMM_T_COMBINE_WAVE, s);

@@ -54,6 +54,8 @@ struct Summary {
   int64_t w_partial;          // window path: partial entries
   int64_t w_dslots;           // window path: dense partial rows
   int64_t w_none;             // long rows without a window plan
+  int64_t w_entries;          // narrow B: entries of A in the long rows
+  int64_t w_wide;             // and, in eighths, those whose row of B has more than 32
   int32_t err;                // nonzero: input validation failed
   int32_t pad;
 };
@@ -373,8 +375,8 @@ struct RowStatsArgs {
 // max u, sum u (long), sum min(u,n) (long), items, pieces,
 // sum u (multi), split entries, pool (single), sum min(u,n) (multi), spill,
 // then the window plan: items, segments, table entries, partial entries,
-// dense partial rows, rows without a window plan
-constexpr int kBlockStats = 16;
+// dense partial rows, rows without a window plan, entries, wide entries
+constexpr int kBlockStats = 18;
 int64_t bin_blocks(int64_t m);
 void launch_binning(const RowStatsArgs &a, hipStream_t s);
 
@@ -503,6 +505,10 @@ void launch_long_rownnz(const LongRow *lrows, int64_t nlong, const Piece *pieces
 void scan_piece_counts(const Piece *pieces, int64_t n, int64_t *out, int64_t *part,
                        hipStream_t s);
 
+// Whether most batches of 64 entries of the long rows meet only rows of B of at
+// most 32 entries: at most one entry in 96 has a longer one.
+inline bool win_short_rows(const Summary &S) { return 12 * S.w_wide <= S.w_entries; }
+
 // Window path for long rows (window.hip).  Planning: row records, the
 // item and segment lists (bsum: 5 * ceil(nlong / 256) int64).
 void win_plan_launch(const int32_t *lrows, int64_t nlong, const int64_t *u, int64_t n,
@@ -515,9 +521,10 @@ void win_partition(const EscArgs<T> &e, const WinRow *rows, const WinWork *segs,
                    uint16_t *table, uint32_t *pkey, T *pval, hipStream_t s);
 // Symbolic pass: output count of every item (cnt), dense partial bitmaps;
 // lists (list_ids, list_count: nitems + 1 entries) the items that the
-// work-group kernels finish.
+// work-group kernels finish.  short_rows: the dense windows' kernel for rows of
+// B of at most 32 entries (win_short_rows).
 template <typename T>
-void win_symbolic(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinWork *items,
+void win_symbolic(const EscArgs<T> &e, int64_t n, bool short_rows, const WinRow *rows, const WinWork *items,
                   int64_t nitems, const uint16_t *table, const uint32_t *pkey,
                   const int32_t *slot_row, int64_t nslots, uint32_t *list_ids,
                   uint32_t *list_count, uint32_t *dbits, int64_t *cnt, hipStream_t s);
@@ -526,7 +533,7 @@ void win_rownnz(const WinRow *rows, int64_t nlong, const int64_t *iscan, int64_t
                 hipStream_t s);
 // Numeric pass: every item written to its place in C.
 template <typename T>
-void win_numeric(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinWork *items,
+void win_numeric(const EscArgs<T> &e, int64_t n, bool short_rows, const WinRow *rows, const WinWork *items,
                  int64_t nitems, const uint16_t *table, const uint32_t *pkey, const T *pval,
                  const int32_t *slot_row, int64_t nslots, uint32_t *list_ids,
                  uint32_t *list_count, const uint32_t *dbits, T *dacc, const int64_t *iscan,

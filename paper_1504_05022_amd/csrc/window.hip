@@ -670,6 +670,13 @@ __global__ __launch_bounds__(WAVE) void k_wpart(EscArgs<T> e, const WinRow *rows
 // symbolic pass of the long rows of a 300000^2 x 4096 product, 32 per row of
 // B, binary32: 626 / 209 us with one entry per slot, 546 / 174 now; of a
 // 90001^2 x 2000 one, 24 per row, binary64: 227 / 112 and 174 / 74.
+//
+// SHORT: with the half and quarter slots.  Their values take registers from
+// every batch (numeric binary64 240 against 108, symbolic 96 against 40) and so
+// wavefronts, which is only worth it where most batches of 64 entries meet no
+// longer row of B (win_short_rows): 700^2 dense binary64 1059 / 267 us, without
+// them 924 / 208; 60000^2 x 4096 with 0 to 89 per row of B, binary32, 546 / 220
+// and 480 / 166.
 
 // slots per group (16 and 8 measured 573 and 546 us binary32, 174 and 181
 // binary64: two wavefronts per SIMD with 255 registers are all LDS allows)
@@ -733,7 +740,7 @@ template <bool NUM> constexpr int dense_waves_per_simd() { return NUM ? 2 : 5; }
 // kept as a bitmap for the reduction (product ranges).  Numeric: the row
 // written to C in column order (one-range items) or the dense partial row
 // of the range.
-template <typename T, bool NUM>
+template <typename T, bool NUM, bool SHORT>
 __global__ __launch_bounds__(WAVE * dense_nwv<NUM>())
 __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd<NUM>())))
 void k_wdense(WinArgsW<T> a, uint32_t *dbits, T *dacc) {
@@ -814,7 +821,7 @@ void k_wdense(WinArgsW<T> a, uint32_t *dbits, T *dacc) {
         constexpr int SUB = decltype(sub_c)::value;
         constexpr int EPS = WAVE / SUB;           // entries per slot
         constexpr int G = dense_slots<T, NUM, SUB>();
-        const int sub = ln / SUB, x = ln & (SUB - 1);
+        const int sub = SUB == WAVE ? 0 : ln / SUB, x = SUB == WAVE ? ln : ln & (SUB - 1);
         struct Group {
           int32_t st[SUB == WAVE ? G : 1], ls[G], bc[G];
           T as[G], bv[G];
@@ -875,12 +882,16 @@ void k_wdense(WinArgsW<T> a, uint32_t *dbits, T *dacc) {
           cur = nxt;
         }
       };
-      if (!__any(len > 16))
-        take(std::integral_constant<int, 16>{});
-      else if (!__any(len > 32))
-        take(std::integral_constant<int, 32>{});
-      else
+      if constexpr (SHORT) {
+        if (!__any(len > 16))
+          take(std::integral_constant<int, 16>{});
+        else if (!__any(len > 32))
+          take(std::integral_constant<int, 32>{});
+        else
+          take(std::integral_constant<int, 64>{});
+      } else {
         take(std::integral_constant<int, 64>{});
+      }
       if (a.e.P[eb + nb] - P0 >= q1) break;
     }
     group_sync();
@@ -1440,8 +1451,8 @@ void win_partition(const EscArgs<T> &e, const WinRow *rows, const WinWork *segs,
 constexpr int kListGrid = 512;
 
 template <typename T>
-void win_symbolic(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinWork *items,
-                  int64_t nitems, const uint16_t *table, const uint32_t *pkey,
+void win_symbolic(const EscArgs<T> &e, int64_t n, bool short_rows, const WinRow *rows,
+                  const WinWork *items, int64_t nitems, const uint16_t *table, const uint32_t *pkey,
                   const int32_t *slot_row, int64_t nslots, uint32_t *list_ids,
                   uint32_t *list_count, uint32_t *dbits, int64_t *cnt, hipStream_t s) {
   if (nitems <= 0) return;
@@ -1457,8 +1468,8 @@ void win_symbolic(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinW
   a.cnt = cnt;
   if (n <= (int64_t(1) << ValTraits<T>::dl)) {
     // every long row is a direct dense row
-    hipLaunchKernelGGL((k_wdense<T, false>), dim3(nitems), dim3(WAVE), 0, s, a, dbits,
-                       static_cast<T *>(nullptr));
+    hipLaunchKernelGGL((short_rows ? k_wdense<T, false, true> : k_wdense<T, false, false>),
+                       dim3(nitems), dim3(WAVE), 0, s, a, dbits, static_cast<T *>(nullptr));
     if (nslots > 0)
       hipLaunchKernelGGL(k_wsym_reduce, dim3(nslots), dim3(SYM_NT), 0, s, rows, slot_row, nslots,
                          n, dbits, cnt);
@@ -1478,8 +1489,8 @@ void win_rownnz(const WinRow *rows, int64_t nlong, const int64_t *iscan, int64_t
 }
 
 template <typename T>
-void win_numeric(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinWork *items,
-                 int64_t nitems, const uint16_t *table, const uint32_t *pkey, const T *pval,
+void win_numeric(const EscArgs<T> &e, int64_t n, bool short_rows, const WinRow *rows,
+                 const WinWork *items, int64_t nitems, const uint16_t *table, const uint32_t *pkey, const T *pval,
                  const int32_t *slot_row, int64_t nslots, uint32_t *list_ids,
                  uint32_t *list_count, const uint32_t *dbits, T *dacc, const int64_t *iscan,
                  const int64_t *rowoff, int32_t *c_col, T *c_val, hipStream_t s) {
@@ -1499,8 +1510,9 @@ void win_numeric(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinWo
   a.c_col = c_col;
   a.c_val = c_val;
   if (n <= (int64_t(1) << ValTraits<T>::dl)) {
-    hipLaunchKernelGGL((k_wdense<T, true>), dim3(nitems), dim3(WAVE * dense_nwv<true>()), 0, s,
-                       a, static_cast<uint32_t *>(nullptr), dacc);
+    hipLaunchKernelGGL((short_rows ? k_wdense<T, true, true> : k_wdense<T, true, false>),
+                       dim3(nitems), dim3(WAVE * dense_nwv<true>()), 0, s, a,
+                       static_cast<uint32_t *>(nullptr), dacc);
     if (nslots > 0)
       hipLaunchKernelGGL((k_wnum_reduce<T>), dim3(nslots * ((n + WNT - 1) / WNT)), dim3(WNT), 0, s,
                          rows, slot_row, nslots, n, dbits, dacc, rowoff, c_col, c_val);
@@ -1526,12 +1538,12 @@ void win_numeric(const EscArgs<T> &e, int64_t n, const WinRow *rows, const WinWo
 #define WIN_INST(T)                                                                             \
   template void win_partition<T>(const EscArgs<T> &, const WinRow *, const WinWork *, int64_t,  \
                                  uint16_t *, uint32_t *, T *, hipStream_t);                     \
-  template void win_symbolic<T>(const EscArgs<T> &, int64_t, const WinRow *, const WinWork *,   \
-                                int64_t, const uint16_t *, const uint32_t *, const int32_t *,   \
+  template void win_symbolic<T>(const EscArgs<T> &, int64_t, bool, const WinRow *,              \
+                                const WinWork *, int64_t, const uint16_t *, const uint32_t *, const int32_t *,   \
                                 int64_t, uint32_t *, uint32_t *, uint32_t *, int64_t *,         \
                                 hipStream_t);                                                   \
-  template void win_numeric<T>(const EscArgs<T> &, int64_t, const WinRow *, const WinWork *,    \
-                               int64_t, const uint16_t *, const uint32_t *, const T *,          \
+  template void win_numeric<T>(const EscArgs<T> &, int64_t, bool, const WinRow *,               \
+                               const WinWork *, int64_t, const uint16_t *, const uint32_t *, const T *,          \
                                const int32_t *, int64_t, uint32_t *, uint32_t *,                \
                                const uint32_t *, T *, const int64_t *, const int64_t *,         \
                                int32_t *, T *, hipStream_t);

@@ -140,6 +140,20 @@ def test_dense_windows_by_b_row_length(dtype, most):
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("rare", [33, 64, 65, 200])
+def test_dense_windows_with_a_rare_long_row(dtype, rare):
+    """Rows of B of at most 16 entries but for one in 200: the kernel for short
+    rows, in whose batches the long one is met alone."""
+    from test_gpu_parity import check
+    rng = np.random.default_rng(rare)
+    lens = np.r_[rng.integers(8, 17, 100), rare, rng.integers(8, 17, 99)]
+    B = _ragged(rng, 200, lens, 256, dtype)
+    deg = [d for d in (63, 64, 65, 130, 199, 200) for _ in range(6)]
+    A = _ragged(rng, len(deg), deg, 200, dtype)
+    check(A, B)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("u", [(1025, 600), (3000, 1025, 4000), (40000, 4100, 520, 3000)])
 def test_long_rows_in_few_columns(dtype, u):
     """Cut rows of C whose products share one range of columns: streams above
