@@ -1398,7 +1398,7 @@ __global__ __launch_bounds__(WNT) void k_wnum_reduce(const WinRow *rows, const i
   if (!on) return;
   const T *src = dacc + wr.dslot0 * n + c;
   T v = src[0];
-#pragma unroll 32
+#pragma unroll 8  // (32: 50 instead of 46 us for a 300000^2 x 4096 product, 41 and 32 for 700^2)
   for (int32_t k = 1; k < wr.nitem; ++k) v = v + src[static_cast<int64_t>(k) * n];
   const int64_t dst = rowoff[wr.row] + before + o;
   c_col[dst] = static_cast<int32_t>(c);
