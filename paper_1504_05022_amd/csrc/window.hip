@@ -1068,13 +1068,11 @@ __global__ __launch_bounds__(WNT) void k_wsym_g(EscArgs<T> e, int64_t n, const W
 
 // Dense partial rows of a direct dense row: OR of their bitmaps (kept in
 // the first one) and the row's count (on its first item; the others 0).
-constexpr int SYM_NT = 1024;
-
-__global__ __launch_bounds__(SYM_NT) void k_wsym_reduce(const WinRow *rows,
-                                                        const int32_t *slot_row, int64_t nslots,
-                                                        int64_t n, uint32_t *dbits, int64_t *cnt) {
+__global__ __launch_bounds__(WNT) void k_wsym_reduce(const WinRow *rows, const int32_t *slot_row,
+                                                     int64_t nslots, int64_t n, uint32_t *dbits,
+                                                     int64_t *cnt) {
   constexpr int MAXW = 4096 / 32;  // words of the widest dense window
-  __shared__ int64_t red[SYM_NT / WAVE + 1];
+  __shared__ int64_t red[WNT / WAVE + 1];
   __shared__ uint32_t acc[MAXW];
   const int64_t sl = blockIdx.x;
   if (sl >= nslots) return;
@@ -1084,9 +1082,12 @@ __global__ __launch_bounds__(SYM_NT) void k_wsym_reduce(const WinRow *rows,
   if (nwords > MAXW) return;  // launched only for dense windows
   if (threadIdx.x < MAXW) acc[threadIdx.x] = 0u;
   __syncthreads();
-  // the ranges are dealt to groups of nwords threads (the longest row has
-  // hundreds: one group with one load in flight took 90 us for 586)
-  const int ng = SYM_NT / nwords;
+  // the ranges are dealt to groups of nwords threads, eight loads in flight in
+  // each: the longest row has hundreds.  300000^2 x 4096, binary32, the short
+  // rows' kernels beside it: 67 us with one group and one load at a time, 17 now,
+  // 123 in work-groups of 1024, which find a place only when those kernels end;
+  // 700^2 dense, 30 ranges a row: 17, 10 and 29
+  const int ng = WNT / nwords;
   const int g = threadIdx.x / nwords, q = threadIdx.x % nwords;
   uint32_t *bits = dbits + wr.dslot0 * static_cast<int64_t>(nwords);
   if (g < ng) {
@@ -1102,7 +1103,7 @@ __global__ __launch_bounds__(SYM_NT) void k_wsym_reduce(const WinRow *rows,
     c = __popc(acc[threadIdx.x]);
   }
   int64_t tot;
-  (void)block_excl_sum<SYM_NT, int64_t>(c, red, tot);
+  (void)block_excl_sum<WNT, int64_t>(c, red, tot);
   if (threadIdx.x == 0) {
     cnt[wr.item0] = tot;
     for (int32_t k = 1; k < wr.nitem; ++k) cnt[wr.item0 + k] = 0;
@@ -1471,7 +1472,7 @@ void win_symbolic(const EscArgs<T> &e, int64_t n, bool short_rows, const WinRow 
     hipLaunchKernelGGL((short_rows ? k_wdense<T, false, true> : k_wdense<T, false, false>),
                        dim3(nitems), dim3(WAVE), 0, s, a, dbits, static_cast<T *>(nullptr));
     if (nslots > 0)
-      hipLaunchKernelGGL(k_wsym_reduce, dim3(nslots), dim3(SYM_NT), 0, s, rows, slot_row, nslots,
+      hipLaunchKernelGGL(k_wsym_reduce, dim3(nslots), dim3(WNT), 0, s, rows, slot_row, nslots,
                          n, dbits, cnt);
     return;
   }
