@@ -1387,7 +1387,7 @@ int backward_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, const sp
   p->info.bytes_scratch = held_bytes(p) + static_cast<int64_t>(extra);
   if (want_a || W)
     launch_grad_entries<T>(A->row_ptr, aval, p->m, p->nnzA, p->P, p->bst,
-                           B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, W, s);
+                           p->info.nnz_hat, B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, W, s);
   if (want_b) {
     if (W) {
       launch_grad_b_sum<T>(p->tptr, p->tpos, p->P, B->row_ptr, p->k, W, dB, s);
@@ -1467,7 +1467,7 @@ int backward_static_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B,
   T *dB = want_b ? static_cast<T *>(dB_val) : nullptr;
   if (!want_b) {
     launch_grad_entries<T>(A->row_ptr, aval, p->m, p->nnzA, p->P, p->bst,
-                           B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, nullptr, s);
+                           p->info.nnz_hat, B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, nullptr, s);
     return SPGEMM_OK;
   }
   // A's transposed pattern, then the staged dB products if they fit too
@@ -1494,7 +1494,7 @@ int backward_static_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B,
                            tpart, s);
   if (want_a || W)
     launch_grad_entries<T>(A->row_ptr, aval, p->m, p->nnzA, p->P, p->bst,
-                           B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, W, s);
+                           p->info.nnz_hat, B->col_idx, bval, p->n, C->row_ptr, C->col_idx, dc, dA, W, s);
   if (W)
     launch_grad_b_sum<T>(tptr, tpos, p->P, B->row_ptr, p->k, W, dB, s);
   else

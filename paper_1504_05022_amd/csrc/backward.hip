@@ -11,6 +11,7 @@
 // a tree across the lanes, block by block (a fixed order).
 #include "common.hpp"
 #include "internal.hpp"
+#include "launch_rules.hpp"
 
 namespace spg {
 
@@ -153,16 +154,15 @@ template <typename T, bool DENSE>
 __global__ __launch_bounds__(BW_NT) void k_grad_entries(
     const int32_t *arp, const T *aval, int64_t m, int64_t nnz,
     const int64_t *P, const int32_t *bst, const int32_t *bcol, const T *bval, const int32_t *crp,
-    const int32_t *ccol, const T *dc, T *dA, T *W) {
+    const int32_t *ccol, const T *dc, T *dA, T *W, int ch) {
   constexpr int NWV = BW_NT / WAVE;
-  constexpr int BW_CH = bw_ch<DENSE>();
   __shared__ GradTable<T, DENSE> tabs[NWV];
   const int w = threadIdx.x / WAVE;
   const int ln = lane();
   GradTable<T, DENSE> &tb = tabs[w];
-  const int64_t e0 = (static_cast<int64_t>(blockIdx.x) * NWV + w) * BW_CH;
+  const int64_t e0 = (static_cast<int64_t>(blockIdx.x) * NWV + w) * ch;
   if (e0 >= nnz) return;  // uniform across the wavefront; no work-group barriers here
-  const int64_t e1 = e0 + BW_CH < nnz ? e0 + BW_CH : nnz;
+  const int64_t e1 = e0 + ch < nnz ? e0 + ch : nnz;
   // its rows [row_lo, row_hi), mostly within 64: their starts one per lane
   const int32_t row_lo = wave_row_of(arp, 0, static_cast<int32_t>(m), e0);
   const int32_t ahead = m - row_lo < WAVE ? static_cast<int32_t>(m) - row_lo : WAVE;
@@ -474,20 +474,15 @@ __global__ __launch_bounds__(256) void k_grad_b_sum(const int64_t *tptr, const i
 
 template <typename T>
 void launch_grad_entries(const int32_t *arp, const T *aval, int64_t m, int64_t nnz,
-                         const int64_t *P, const int32_t *bst, const int32_t *bcol,
-                         const T *bval, int64_t n, const int32_t *crp, const int32_t *ccol,
-                         const T *dc, T *dA, T *W, hipStream_t s) {
+                         const int64_t *P, const int32_t *bst, int64_t products,
+                         const int32_t *bcol, const T *bval, int64_t n, const int32_t *crp,
+                         const int32_t *ccol, const T *dc, T *dA, T *W, hipStream_t s) {
   if (nnz <= 0) return;
-  constexpr int NWV = BW_NT / WAVE;
-  if (n <= BW_MAP) {
-    constexpr int64_t PER = int64_t(NWV) * bw_ch<true>();
-    hipLaunchKernelGGL((k_grad_entries<T, true>), dim3((nnz + PER - 1) / PER), dim3(BW_NT), 0, s,
-                       arp, aval, m, nnz, P, bst, bcol, bval, crp, ccol, dc, dA, W);
-  } else {
-    constexpr int64_t PER = int64_t(NWV) * bw_ch<false>();
-    hipLaunchKernelGGL((k_grad_entries<T, false>), dim3((nnz + PER - 1) / PER), dim3(BW_NT), 0, s,
-                       arp, aval, m, nnz, P, bst, bcol, bval, crp, ccol, dc, dA, W);
-  }
+  const int ch = grad_chunk(n <= BW_MAP ? bw_ch<true>() : bw_ch<false>(), nnz, products);
+  const int64_t per = int64_t(BW_NT / WAVE) * ch;
+  hipLaunchKernelGGL((n <= BW_MAP ? k_grad_entries<T, true> : k_grad_entries<T, false>),
+                     dim3((nnz + per - 1) / per), dim3(BW_NT), 0, s, arp, aval, m, nnz, P, bst, bcol,
+                     bval, crp, ccol, dc, dA, W, ch);
 }
 
 template <typename T>
@@ -499,13 +494,13 @@ void launch_grad_b_sum(const int64_t *tptr, const int32_t *tpos, const int64_t *
 }
 
 template void launch_grad_entries<float>(const int32_t *, const float *, int64_t,
-                                         int64_t, const int64_t *, const int32_t *,
+                                         int64_t, const int64_t *, const int32_t *, int64_t,
                                          const int32_t *, const float *, int64_t,
                                          const int32_t *, const int32_t *, const float *, float *,
                                          float *, hipStream_t);
 template void launch_grad_entries<double>(const int32_t *, const double *,
                                           int64_t, int64_t, const int64_t *, const int32_t *,
-                                          const int32_t *, const double *, int64_t,
+                                          int64_t, const int32_t *, const double *, int64_t,
                                           const int32_t *, const int32_t *, const double *,
                                           double *, double *, hipStream_t);
 template void launch_grad_b_sum<float>(const int64_t *, const int32_t *, const int64_t *,

@@ -583,12 +583,13 @@ void launch_transpose_parts(const TransposeParts &tp, const int32_t *acol, int64
 void launch_transpose_rows(const int32_t *arp, int64_t m, const int32_t *tpos, int64_t nnz,
                            int32_t *trow, hipStream_t s);
 // Product-parallel gradient: dA (nullable) and the products W (nullable,
-// sum(u) entries) of the dB sums; then dB from W over A's transposed pattern.
+// sum(u) = products entries) of the dB sums; then dB from W over A's transposed
+// pattern.
 template <typename T>
 void launch_grad_entries(const int32_t *arp, const T *aval, int64_t m, int64_t nnz,
-                         const int64_t *P, const int32_t *bst, const int32_t *bcol,
-                         const T *bval, int64_t n, const int32_t *crp, const int32_t *ccol,
-                         const T *dc, T *dA, T *W, hipStream_t s);
+                         const int64_t *P, const int32_t *bst, int64_t products,
+                         const int32_t *bcol, const T *bval, int64_t n, const int32_t *crp,
+                         const int32_t *ccol, const T *dc, T *dA, T *W, hipStream_t s);
 template <typename T>
 void launch_grad_b_sum(const int64_t *tptr, const int32_t *tpos, const int64_t *P,
                        const int32_t *brp, int64_t kb, const T *W, T *dB, hipStream_t s);

@@ -46,4 +46,16 @@ inline int copy_parts(int64_t tiles, int64_t rows, int r, int tile_rows) {
   return parts > 1 ? static_cast<int>(parts) : 1;
 }
 
+// Entries of A per wavefront of the gradient kernel: `full`, or as few as give
+// 2048 wavefronts (eight per CU), with at least 384 products (the loads that
+// one has in flight) on average.  One row of 100 entries, 100 products each:
+// dA 84 us in one wavefront, 17 in 25.
+inline int grad_chunk(int full, int64_t nnz, int64_t products) {
+  int ch = full;
+  while (ch > 1 && nnz < int64_t(2048) * ch &&
+         static_cast<double>(products) * (ch / 2) >= 384.0 * static_cast<double>(nnz))
+    ch /= 2;
+  return ch;
+}
+
 }  // namespace spg

@@ -57,6 +57,35 @@ def test_backward_ragged_rows(dtype, n):
         assert np.all(np.abs(got.cpu().numpy() - ref) <= (t + 2) * eps * mag)
 
 
+@pytest.mark.parametrize("n", [8192, 8193])
+def test_backward_full_chunks(n):
+    """Enough entries of A for chunks of 128 and 64 of them per wavefront (a
+    smaller A takes fewer), with windows of 2048 products inside them."""
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, Plan
+    rng = np.random.default_rng(6)
+    k, m = 500, 2700
+    lens = [int(x) for x in np.r_[rng.integers(0, 60, k - 12), [2047, 2048, 2049, 64] * 3]]
+    B = _ragged(rng, k, lens, n, np.float64)
+    A = _ragged(rng, m, rng.integers(0, 200, m), k, np.float64)
+    A = S.Csr(m, k, A.row_ptr, A.col_idx, np.abs(A.val))
+    assert A.nnz > 2048 * 128
+    print("case: n %d products of %d entries" % (n, A.nnz), flush=True)
+    plan = Plan(CsrMatrix.from_host(A), CsrMatrix.from_host(B))
+    C = plan.compute()
+    dc = rng.standard_normal(C.nnz)
+    gA, gB = plan.backward(C, torch.from_numpy(dc).cuda())
+    _, _, rp, ci, _ = C.to_host()
+    args = (rp.astype(np.int64), ci)
+    refs = oracle.grad(A.as_tuple(), B.as_tuple(), *args, dc)
+    absB = S.Csr(k, n, B.row_ptr, B.col_idx, np.abs(B.val))
+    mags = oracle.grad(A.as_tuple(), absB.as_tuple(), *args, np.abs(dc))
+    eps = np.finfo(np.float64).eps  # a sum of t rounded products, in any order
+    terms = (np.array(lens)[A.col_idx], np.bincount(A.col_idx, minlength=k).repeat(lens))
+    for got, ref, mag, t in zip((gA, gB), refs, mags, terms):
+        assert np.all(np.abs(got.cpu().numpy() - ref) <= (t + 2) * eps * mag)
+
+
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("col_range", [None, 60])
 def test_short_rows_around_network_sizes(dtype, col_range):

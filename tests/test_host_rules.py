@@ -186,3 +186,21 @@ int main() {
   CHECK(copy_parts(1 << 20, 256ll << 20, 2, 256) == 15);  // 32: beyond a launch
 }
 """)
+
+
+def test_gradient_chunks(tmp_path):
+    """Entries of A per wavefront: all of a chunk for a large A, fewer for a
+    small one as long as they have products to fill a wavefront."""
+    run_cpp(tmp_path, ["launch_rules.hpp", "initializer_list"], r"""
+using spg::grad_chunk;
+int main() {
+  CHECK(grad_chunk(128, 6000000, 192000000) == 128 && grad_chunk(64, 600000, 7200000) == 64);
+  CHECK(grad_chunk(128, 100, 10000) == 4 && grad_chunk(128, 100, 1000) == 64);
+  CHECK(grad_chunk(64, 1, 1000000) == 1 && grad_chunk(64, 1000, 0) == 64);
+  for (int64_t nnz = 1; nnz < (int64_t(1) << 31); nnz = nnz * 3 + 1)
+    for (int64_t each : {0ll, 1ll, 5ll, 100ll, 100000ll}) {
+      const int ch = grad_chunk(128, nnz, nnz * each);
+      CHECK(ch >= 1 && ch <= 128 && (ch == 128 || (nnz < 4096ll * ch && ch * each >= 384)));
+    }
+}
+""")
