@@ -49,7 +49,7 @@ inline int copy_parts(int64_t tiles, int64_t rows, int r, int tile_rows) {
 // Entries of A per wavefront of the gradient kernel: `full`, or as few as give
 // 2048 wavefronts (eight per CU), with at least 384 products (the loads that
 // one has in flight) on average.  One row of 100 entries, 100 products each:
-// dA 84 us in one wavefront, 17 in 25.
+// dA 84 us in one wavefront, 11 in 25.
 inline int grad_chunk(int full, int64_t nnz, int64_t products) {
   int ch = full;
   while (ch > 1 && nnz < int64_t(2048) * ch &&
