@@ -1302,32 +1302,32 @@ namespace {
 int ensure_transpose(spgemm_plan p, const spgemm_csr *A, size_t *temp, hipStream_t s) {
   *temp = 0;
   if (p->bws) return SPGEMM_OK;
-  // by partition where its temporary space can be had, else in place
+  // by partition where its temporary space can be had beside the plan's, else
+  // in place
   TransposeParts tp;
-  bool parts = transpose_parts(p->k, p->nnzA, tp);
-  Layout T;
+  Layout T, L;
   size_t oe = 0, otab = 0, ooff = 0, oprt = 0;
-  void *t = nullptr;
-  if (parts) {
+  void *t = nullptr, *bws = nullptr;
+  const size_t ot = L.add<int64_t>(p->k + 1);
+  const size_t op = L.add<int32_t>(p->nnzA);
+  if (transpose_parts(p->k, p->nnzA, tp)) {
     const int64_t nt = tp.groups * tp.tiles;
     oe = T.add<unsigned char>(p->nnzA * static_cast<int64_t>(kTransposeEntryBytes));
     otab = T.add<int32_t>(nt);
     ooff = T.add<int64_t>(nt + 1);
     oprt = T.add<int64_t>(scan_part_len(nt));
     t = p->al.get(T.bytes(), s);
-    parts = t != nullptr;
+    if (t && !(bws = p->al.get(L.bytes(), s))) {
+      p->al.put(t, s);
+      t = nullptr;
+    }
   }
-  Layout L;
-  const size_t ot = L.add<int64_t>(p->k + 1);
-  const size_t op = L.add<int32_t>(p->nnzA);
+  const bool parts = t != nullptr;
   const size_t oc = parts ? 0 : L.add<int32_t>(p->k);
   const size_t orr = parts ? 0 : L.add<int32_t>(p->nnzA);
   const size_t opa = parts ? 0 : L.add<int64_t>(scan_part_len(std::max<int64_t>(p->k, 1)));
-  void *bws = p->al.get(L.bytes(), s);
-  if (!bws) {
-    p->al.put(t, s);
-    return fail(SPGEMM_ENOMEM, "backward scratch allocation failed");
-  }
+  if (!bws) bws = p->al.get(L.bytes(), s);
+  if (!bws) return fail(SPGEMM_ENOMEM, "backward scratch allocation failed");
   int64_t *tptr = at<int64_t>(bws, ot);
   int32_t *tpos = at<int32_t>(bws, op);
   if (parts) {
