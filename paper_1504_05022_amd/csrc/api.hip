@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "launch_rules.hpp"
 #include "mailbox.hpp"
 
 using namespace spg;
@@ -835,37 +836,43 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
   auto launch_short_rows = [&]() -> int {
     if (short_done) return SPGEMM_OK;
     short_done = true;
-    // one launch per power-of-two capacity; a capacity with few rows joins
-    // the next larger one up to eight times its size (its rows then sort
-    // with idle lanes, which is cheaper than a launch of its own)
-    constexpr int64_t kFewRows = 2048;
-    struct Launch {
-      int64_t r0, r1;
-      int cap;
-    };
-    auto launch_bins = [&](std::vector<Launch> &v) -> int {
-      for (size_t i = 0; i + 1 < v.size(); ++i) {
-        if (v[i].r0 == v[i].r1) continue;
-        size_t j = i + 1;  // the next capacity with rows
-        while (j < v.size() && v[j].r0 == v[j].r1) ++j;
-        if (j == v.size() || v[j].cap > 8 * v[i].cap || v[i].r1 - v[i].r0 > kFewRows) continue;
-        v[j].r0 = v[i].r0;  // bins are stored in order
-        v[i].r1 = v[i].r0;
+    // one launch per power-of-two capacity, those with few rows joined
+    // (join_classes)
+    struct Launches {
+      int n = 0;
+      int64_t r0[6], rows[6];  // bins are stored in order
+      int cap[6];
+      void add(int64_t lo, int64_t hi, int c) {
+        r0[n] = lo;
+        rows[n] = hi - lo;
+        cap[n++] = c;
       }
+    };
+    auto launch_bins = [&](const Launches &v) -> int {
+      int to[6];
+      join_classes(v.n, v.rows, v.cap, to);
       // the largest first: its kernel runs long enough for the host to queue
       // the short ones behind it
-      for (size_t i = v.size(); i-- > 0;)
-        if (launch_esc<T>(ea, p->recs + v[i].r0, v[i].r1 - v[i].r0, v[i].cap, p->n, es))
+      for (int d = v.n; d-- > 0;) {
+        if (to[d] != d) continue;
+        int64_t r0 = v.r0[d], rows = 0;
+        for (int c = 0; c <= d; ++c)
+          if (to[c] == d && v.rows[c] > 0) {
+            if (rows == 0) r0 = v.r0[c];
+            rows += v.rows[c];
+          }
+        if (launch_esc<T>(ea, p->recs + r0, rows, v.cap[d], p->n, es))
           return fail(SPGEMM_EINVAL, "no ESC kernel for this capacity");
+      }
       return SPGEMM_OK;
     };
     // ---- bin group 4: the four range bins
     stage_begin(p, SPGEMM_T_MEDIUM, es);
-    std::vector<Launch> v;
+    Launches medium, tiny;
     int lrc;
     for (int b = 33; b <= 36; ++b)
-      v.push_back({S.bin_off[b], S.bin_off[b + 1], static_cast<int>(next_pow2(p->be.e[b - 32]))});
-    if ((lrc = launch_bins(v)) != SPGEMM_OK) return lrc;
+      medium.add(S.bin_off[b], S.bin_off[b + 1], static_cast<int>(next_pow2(p->be.e[b - 32])));
+    if ((lrc = launch_bins(medium)) != SPGEMM_OK) return lrc;
     stage_end(p, SPGEMM_T_MEDIUM, es);
     // ---- stage 3, bin groups 2-3
     stage_begin(p, SPGEMM_T_TINY, es);
@@ -877,14 +884,13 @@ int compute_t(spgemm_plan p, const spgemm_csr *A, const spgemm_csr *B, spgemm_cs
         if (launch_heap<T>(ea, p->binlist + S.bin_off[b], S.bin_off[b + 1] - S.bin_off[b], b, es))
           return fail(SPGEMM_EINVAL, "no heap kernel for this size");
     } else {
-      v.clear();
       for (int b = 1; b <= p->be.e[0];) {
         const int cap = static_cast<int>(next_pow2(b));
         const int hi = std::min<int>(cap, p->be.e[0]);
-        v.push_back({S.bin_off[b], S.bin_off[hi + 1], cap});
+        tiny.add(S.bin_off[b], S.bin_off[hi + 1], cap);
         b = hi + 1;
       }
-      if ((lrc = launch_bins(v)) != SPGEMM_OK) return lrc;
+      if ((lrc = launch_bins(tiny)) != SPGEMM_OK) return lrc;
     }
     stage_end(p, SPGEMM_T_TINY, es);
     return SPGEMM_OK;

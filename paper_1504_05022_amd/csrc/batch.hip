@@ -132,29 +132,17 @@ BatchKernel batch_kernel(int set, int c) {
   return set == 1 ? k1[c] : (set == 2 ? k2[c] : k0[c]);
 }
 
-// Kernel class of every capacity class: a class with few rows over all
-// problems joins the next one with rows, up to eight times its capacity
-// (its rows then sort with idle lanes, which is cheaper than a launch of its
-// own: one shot of four problems of 300 .. 3000 rows 241 us, 213 merged).
-constexpr int64_t kFewRows = 2048;
+// Kernel class of every capacity class (2^c products), those with few rows
+// over all problems joined (join_classes: one shot of four problems of 300 ..
+// 3000 rows 241 us, 213 joined).
 struct ClassMap {
   int to[kBatchNumClasses];
 };
 ClassMap merge_classes(const int64_t (&count)[kBatchNumClasses]) {
+  int cap[kBatchNumClasses];
+  for (int c = 0; c < kBatchNumClasses; ++c) cap[c] = 1 << c;
   ClassMap m;
-  int64_t rows[kBatchNumClasses];
-  for (int c = 0; c < kBatchNumClasses; ++c) rows[c] = count[c];
-  for (int c = 0; c < kBatchNumClasses; ++c) {
-    m.to[c] = c;
-    if (rows[c] == 0 || rows[c] > kFewRows) continue;
-    for (int d = c + 1; d < kBatchNumClasses && d <= c + 3; ++d) {
-      if (rows[d] == 0) continue;
-      rows[d] += rows[c];
-      m.to[c] = d;
-      break;
-    }
-  }
-  for (int c = kBatchNumClasses; c-- > 0;) m.to[c] = m.to[m.to[c]];
+  join_classes(kBatchNumClasses, count, cap, m.to);
   return m;
 }
 

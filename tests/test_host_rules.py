@@ -204,3 +204,41 @@ int main() {
     }
 }
 """)
+
+
+def test_joined_capacity_classes(tmp_path):
+    """Classes with few rows join the next one with rows within eight times
+    their capacity, in chains; a kernel takes neighbouring classes only, and
+    at most 2048 rows below its own capacity."""
+    run_cpp(tmp_path, ["launch_rules.hpp", "stdlib.h"], r"""
+using spg::join_classes;
+int main() {
+  const int cap[11] = {1, 2, 4, 8, 16, 32, 64, 128, 256, 512, 1024};
+  int to[11];
+  int64_t chain[11] = {100, 0, 0, 100, 0, 0, 100, 0, 0, 100, 0};
+  join_classes(11, chain, cap, to);
+  CHECK(to[0] == 9 && to[3] == 9 && to[6] == 9 && to[9] == 9);
+  int64_t gap[11] = {100, 0, 0, 0, 100, 0, 0, 0, 0, 0, 5};
+  join_classes(11, gap, cap, to);
+  CHECK(to[0] == 0 && to[4] == 4 && to[10] == 10);
+  int64_t many[11] = {2000, 100, 100, 3000, 0, 0, 0, 0, 0, 0, 0};
+  join_classes(11, many, cap, to);
+  CHECK(to[0] == 1 && to[1] == 1 && to[2] == 3 && to[3] == 3);
+  for (int r = 0; r < 20000; ++r) {
+    int64_t rows[11];
+    for (auto &x : rows) x = rand() % 3 ? rand() % 1500 : rand() % 2 * 5000;
+    join_classes(11, rows, cap, to);
+    for (int d = 0; d < 11; ++d) {
+      int64_t below = 0;
+      int first = d;
+      for (int c = d - 1; c >= 0; --c)
+        if (to[c] == d) {
+          below += rows[c];
+          first = c;
+        }
+      CHECK(below <= spg::kFewRows && (below == 0 || to[d] == d) && to[d] >= d);
+      for (int c = first; c < d; ++c) CHECK(to[c] == d || rows[c] == 0);
+    }
+  }
+}
+""")
