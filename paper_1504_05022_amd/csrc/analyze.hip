@@ -643,19 +643,6 @@ void launch_binning(const RowStatsArgs &a, hipStream_t s) {
   if (a.whole) hipLaunchKernelGGL(k_summary, dim3(1), dim3(WAVE), 0, s, a);
 }
 
-__global__ void k_fill_i64(int64_t *p, int64_t n, int64_t v) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    p[i] = v;
-}
-
-void launch_fill_i64(int64_t *p, int64_t n, int64_t v, hipStream_t s) {
-  if (n <= 0) return;
-  int64_t nb = (n + 255) / 256;
-  if (nb > 4096) nb = 4096;
-  hipLaunchKernelGGL(k_fill_i64, dim3(nb), dim3(256), 0, s, p, n, v);
-}
-
 __global__ void k_zero(uint32_t *p, int64_t n) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)

@@ -201,28 +201,6 @@ template <int NT, typename V> DEVI V block_excl_sum(V x, V *smem, V &total) {
   return res;
 }
 
-// Work-group inclusive max of one int per thread (same contract).
-template <int NT> DEVI int block_incl_max(int x, int *smem) {
-  constexpr int NW = NT / WAVE;
-  int inc = group_incl_max<WAVE>(x);
-  const int w = threadIdx.x / WAVE;
-  if (lane() == WAVE - 1) smem[w] = inc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = -1;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      int t = smem[i];
-      smem[i] = run;
-      run = max(run, t);
-    }
-  }
-  __syncthreads();
-  int res = max(smem[w], inc);
-  __syncthreads();
-  return res;
-}
-
 // Work-group exclusive max of one int per thread: max over threads < t, or
 // -1 for thread 0.  `smem` holds NT/64 ints.  Contains barriers.
 template <int NT> DEVI int block_excl_max(int x, int *smem) {

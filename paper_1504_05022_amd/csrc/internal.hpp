@@ -473,7 +473,6 @@ void launch_long_table(const int32_t *binlist, int64_t off, int64_t nlong, const
                        hipStream_t s);
 void launch_cstate_init(LongState *state, int64_t n, LongCounters *cnt, hipStream_t s);
 int combine_maxs();
-int combine_l1cap();
 constexpr int kLongTile = 1024;
 int64_t long_table_tmp_len(int64_t nlong);
 
@@ -557,8 +556,6 @@ template <typename T> struct CompactArgs {
 template <typename T>
 void launch_compact(const CompactArgs<T> &a, int64_t m, int64_t products, int64_t npieces,
                     hipStream_t s);
-
-void launch_fill_i64(int64_t *p, int64_t n, int64_t v, hipStream_t s);
 
 // ------------------------------------------------------------- backward
 // A^T pattern (per column j of A: rows i ascending and entry positions)

@@ -2389,7 +2389,6 @@ int launch_combine(const LongArgs<T> &a, int64_t npieces, hipStream_t s) {
 }
 
 int combine_maxs() { return COMBINE_MAXS; }
-int combine_l1cap() { return COMBINE_L1; }
 
 template int launch_long<float>(const LongArgs<float> &, int64_t, int, hipStream_t);
 template int launch_long<double>(const LongArgs<double> &, int64_t, int, hipStream_t);
