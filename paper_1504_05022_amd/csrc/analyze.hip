@@ -333,11 +333,11 @@ DEVI void long_sums(int64_t ui, int bin, int32_t e0, int32_t ne, const RowStatsA
   v[13] += wp.partial;
   v[14] += wp.dslots;
   v[15] += wp.mode == WIN_NONE ? 1 : 0;
-  if (wp.mode == WIN_DD) {  // the lengths of eight of its rows of B
+  if (wp.mode == WIN_DD) {  // the lengths of four of its rows of B
     int wide = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int64_t e = e0 + (static_cast<int64_t>(ne) * (2 * k + 1) >> 4);
+    for (int k = 0; k < 4; ++k) {
+      const int64_t e = e0 + (static_cast<int64_t>(ne) * (2 * k + 1) >> 3);
       wide += a.P[e + 1] - a.P[e] > 32 ? 1 : 0;
     }
     v[16] += ne;
@@ -345,16 +345,23 @@ DEVI void long_sums(int64_t ui, int bin, int32_t e0, int32_t ne, const RowStatsA
   }
 }
 
+// Whether every long row is a direct dense row (win_plan).
+DEVI bool narrow_b(const RowStatsArgs &a) {
+  return a.ncols <= (int64_t(1) << win_dense_log(a.vbytes));
+}
+
 // Work-group totals of the planning sums; the result of sum k is returned to
 // thread k (< kBlockStats), others get 0.  Only the maximum is reduced where
-// no thread has a long row.  Contains barriers.
+// no thread has a long row, and the sums for dense windows only where B is
+// narrow.  Contains barriers.
 template <int NT> DEVI int64_t block_stats(const int64_t (&v)[kBlockStats], bool any_long,
+                                           bool narrow,
                                            int64_t (&red)[NT / WAVE][kBlockStats]) {
   const int w = threadIdx.x / WAVE;
   const bool wl = __any(any_long);
 #pragma unroll
   for (int k = 0; k < kBlockStats; ++k) {
-    if (k > 0 && !wl) {
+    if ((k > 0 && !wl) || (k >= kNarrowStats && !narrow)) {
       if (lane() == 0) red[w][k] = 0;
       continue;
     }
@@ -452,7 +459,7 @@ __global__ __launch_bounds__(BIN_NT) void k_row_stats(RowStatsArgs a) {
   }
   int64_t hs;
   block_excl_sum<BIN_NT>(h, sm, hs);
-  const int64_t st = block_stats<BIN_NT>(v, any_long, red);  // (its barrier orders cnt too)
+  const int64_t st = block_stats<BIN_NT>(v, any_long, narrow_b(a), red);  // (its barrier orders cnt too)
   const int64_t nb = gridDim.x, b = blockIdx.x;
   if (t < NBINS) a.hist[t * nb + b] = cnt[t];
   if (t == 0) a.hpart[b] = hs;
@@ -583,7 +590,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_rows_small(RowStatsArgs a) {
     atomicAdd(&cnt[bin[r]], 1);
     long_sums(u[r], bin[r], e0[r], ne[r], a, v);
   }
-  const int64_t st = block_stats<SMALL_NT>(v, any_long, red);  // (its barrier orders cnt too)
+  const int64_t st = block_stats<SMALL_NT>(v, any_long, narrow_b(a), red);  // (its barrier orders cnt too)
   if (t < kBlockStats) stats[t] = st;
   if (t < NBINS) tot[t] = cnt[t];
   __syncthreads();

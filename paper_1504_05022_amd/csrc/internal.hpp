@@ -55,7 +55,7 @@ struct Summary {
   int64_t w_dslots;           // window path: dense partial rows
   int64_t w_none;             // long rows without a window plan
   int64_t w_entries;          // narrow B: entries of A in the long rows
-  int64_t w_wide;             // and, in eighths, those whose row of B has more than 32
+  int64_t w_wide;             // and, in quarters, those whose row of B has more than 32
   int32_t err;                // nonzero: input validation failed
   int32_t pad;
 };
@@ -377,6 +377,7 @@ struct RowStatsArgs {
 // then the window plan: items, segments, table entries, partial entries,
 // dense partial rows, rows without a window plan, entries, wide entries
 constexpr int kBlockStats = 18;
+constexpr int kNarrowStats = 16;  // the first of the last two, 0 unless B is narrow
 int64_t bin_blocks(int64_t m);
 void launch_binning(const RowStatsArgs &a, hipStream_t s);
 
@@ -506,7 +507,7 @@ void scan_piece_counts(const Piece *pieces, int64_t n, int64_t *out, int64_t *pa
 
 // Whether most batches of 64 entries of the long rows meet only rows of B of at
 // most 32 entries: at most one entry in 96 has a longer one.
-inline bool win_short_rows(const Summary &S) { return 12 * S.w_wide <= S.w_entries; }
+inline bool win_short_rows(const Summary &S) { return 24 * S.w_wide <= S.w_entries; }
 
 // Window path for long rows (window.hip).  Planning: row records, the
 // item and segment lists (bsum: 5 * ceil(nlong / 256) int64).
