@@ -348,8 +348,8 @@ int spgemm_batch_destroy(spgemm_batch batch);
  * (hipFreeAsync).  *out_mem is NULL when count is 0 or on error (nothing
  * stays allocated then).  Every C_p equals spgemm_multiply's bit for bit
  * (same structure; each sum in the same (column, product index) order).
- * Synchronizes `stream` twice; the scratch is released in stream order
- * before returning.
+ * Waits twice, on the order of `stream`; the scratch is released in stream
+ * order before returning.
  */
 int spgemm_batch_multiply(int32_t count, const spgemm_csr *A, const spgemm_csr *B,
                           const spgemm_options *opt, spgemm_alloc_fn alloc_fn,

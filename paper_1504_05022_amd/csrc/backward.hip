@@ -67,16 +67,17 @@ __global__ __launch_bounds__(256) void k_grad_b(const int64_t *tptr, const int32
 // lane, so the lanes stay full whatever the row lengths of B.
 //
 // What bounds it: latency and the B rows gathered past the L2 (one 128-byte
-// line or two per b_j* and array), not the VALU (37% busy).  One lane per
-// entry of A, as before, left ragged rows waiting on their longest entry and
+// line or two per b_j* and array); the VALU is busy 57% of the time where B is
+// narrow.  One lane per entry of A, as before, left ragged rows waiting on their longest entry and
 // touched 64 lines per load: 2374 us where B is narrow (A 300000^2 with 6M
 // entries x B 300000x4096, 32 per row, binary32; now 1046), 1389 us where it
 // is wide (A 50000^2 with 600k entries x B 50000^2, 12 per row, binary64; now
 // 119).  The chunk's rows are found by the whole wavefront (wave_row_of; a
 // bisection by one lane: 1187 and 136).  Few entries per chunk spread the long
-// tail of a small product; with the bitmap a row cut by a chunk is mapped
+// tail of a product; with the bitmap a row cut by a chunk is mapped
 // twice, so chunks are longer there (64 / 128 / 256 entries 1128 / 1098 / 1112
-// us narrow, 64 / 128 136 / 163 wide, each when measured).  Overlapping the next group's
+// us narrow, 64 / 128 136 / 163 wide, each when measured).  A small A takes
+// smaller chunks (grad_chunk).  Overlapping the next group's
 // loads of B with this group's dC costs more in resident wavefronts than it
 // hides (1371).
 constexpr int BW_WIN = 2048;  // products whose entry starts the bit mask covers
