@@ -201,7 +201,7 @@ const char *spgemm_last_error(void);
  * Section 3.1).  Computes u_i for every row of C, bins the rows and reserves
  * the plan's scratch; waits once, on the order of `stream`, for a small
  * summary (sums, bin counts), written when all of this is done: the plan may
- * then be used on any stream.  A: m x k, B: k x n, same dtype.  The plan
+ * then be computed on another stream.  A: m x k, B: k x n, same dtype.  The plan
  * remembers the pointers and sizes of A's and B's index arrays; later calls
  * must pass the same matrices (values may change).  `opt` may be NULL
  * (defaults); `info` may be NULL.  On success *plan is a new plan.

@@ -106,12 +106,17 @@ def _torch_alloc(nbytes, ctx, stream):
     except RuntimeError:
         return None
     p = t.data_ptr()
+    t.spg_stream = stream
     _live[p] = t
     return p
 
 
 def _torch_free(ptr, ctx, stream):
-    _live.pop(ptr, None)
+    t = _live.pop(ptr, None)
+    # a plan last used on another stream than its memory is from: that stream's
+    # work still reads it
+    if t is not None and t.spg_stream != stream:
+        t.record_stream(torch.cuda.ExternalStream(stream or 0, t.device))
 
 
 _alloc_cb = _ALLOC_T(_torch_alloc)

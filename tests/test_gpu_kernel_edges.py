@@ -368,3 +368,35 @@ def test_one_shot_batch_copy_parts(sizes):
         ref = oracle.spgemm(a.as_tuple(), B.as_tuple())
         assert np.array_equal(rp, ref.row_ptr) and np.array_equal(ci, ref.col_idx)
         assert np.array_equal(v, ref.val)  # Gustavson's order
+
+
+@pytest.mark.parametrize("streams", ["two", "from default", "to default"])
+def test_plan_released_on_another_stream(streams):
+    """A plan computed on another stream than it was analysed on and released
+    at once: its memory is not handed out before that stream's copy into C,
+    which still reads it, has ended."""
+    import torch
+    from paper_1504_05022_amd import CsrMatrix, Plan, spgemm
+    A, _ = S.config2(n=30000, cap=1500)
+    M = CsrMatrix.from_host(A)
+    ref = spgemm(M, M).to_host()
+    torch.cuda.synchronize()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    if streams == "from default":
+        s1 = torch.cuda.default_stream()
+    if streams == "to default":
+        s2 = torch.cuda.default_stream()
+    for r in range(5):
+        print("case: %s, pass %d" % (streams, r), flush=True)
+        with torch.cuda.stream(s1):
+            plan = Plan(M, M)
+            size = plan.info.bytes_scratch
+        with torch.cuda.stream(s2):
+            C = plan.compute()
+            plan.close()
+        with torch.cuda.stream(s1):
+            for _ in range(4):
+                torch.zeros(size, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        for got, want in zip(C.to_host()[2:], ref[2:]):
+            assert np.array_equal(got, want)
