@@ -299,9 +299,9 @@ void launch_validate(const int32_t *rp, const int32_t *ci, int64_t rows, int64_t
 // 2000 rows, against one of 8).
 constexpr int BIN_NT = 256;
 
-// What a row with ne entries of A from e0 adds to the long-row planning sums
+// What row i, with ne entries of A from e0, adds to the long-row planning sums
 // (v: see kBlockStats).
-DEVI void long_sums(int64_t ui, int bin, int32_t e0, int32_t ne, const RowStatsArgs &a,
+DEVI void long_sums(int64_t i, int64_t ui, int bin, int32_t e0, int32_t ne, const RowStatsArgs &a,
                     int64_t (&v)[kBlockStats]) {
   v[0] = v[0] > ui ? v[0] : ui;
   if (bin != LONG_BIN) return;
@@ -333,7 +333,10 @@ DEVI void long_sums(int64_t ui, int bin, int32_t e0, int32_t ne, const RowStatsA
   v[13] += wp.partial;
   v[14] += wp.dslots;
   v[15] += wp.mode == WIN_NONE ? 1 : 0;
-  if (wp.mode == WIN_DD) {  // the lengths of four of its rows of B
+  // the lengths of four of its rows of B: of every sixteenth long row, spread by
+  // its index, and of the longest (of all: 23.8 us for 300000 rows, now 22.5)
+  if (wp.mode == WIN_DD &&
+      (ne >= 1024 || (static_cast<uint32_t>(i) * 0x9e3779b1u) >> 28 == 0)) {
     int wide = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -455,7 +458,7 @@ __global__ __launch_bounds__(BIN_NT) void k_row_stats(RowStatsArgs a) {
     h += tilde_size(ui, bin, a);
     any_long |= bin == LONG_BIN;
     atomicAdd(&cnt[bin], 1);
-    long_sums(ui, bin, e0, e1 - e0, a, v);
+    long_sums(i, ui, bin, e0, e1 - e0, a, v);
   }
   int64_t hs;
   block_excl_sum<BIN_NT>(h, sm, hs);
@@ -588,7 +591,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_rows_small(RowStatsArgs a) {
     if (u[r] == 0) a.rownnz[i] = 0;
     any_long |= bin[r] == LONG_BIN;
     atomicAdd(&cnt[bin[r]], 1);
-    long_sums(u[r], bin[r], e0[r], ne[r], a, v);
+    long_sums(i, u[r], bin[r], e0[r], ne[r], a, v);
   }
   const int64_t st = block_stats<SMALL_NT>(v, any_long, narrow_b(a), red);  // (its barrier orders cnt too)
   if (t < kBlockStats) stats[t] = st;

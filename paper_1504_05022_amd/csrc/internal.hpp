@@ -54,7 +54,7 @@ struct Summary {
   int64_t w_partial;          // window path: partial entries
   int64_t w_dslots;           // window path: dense partial rows
   int64_t w_none;             // long rows without a window plan
-  int64_t w_entries;          // narrow B: entries of A in the long rows
+  int64_t w_entries;          // narrow B: entries of A in the sampled long rows
   int64_t w_wide;             // and, in quarters, those whose row of B has more than 32
   int32_t err;                // nonzero: input validation failed
   int32_t pad;
@@ -506,7 +506,8 @@ void scan_piece_counts(const Piece *pieces, int64_t n, int64_t *out, int64_t *pa
                        hipStream_t s);
 
 // Whether most batches of 64 entries of the long rows meet only rows of B of at
-// most 32 entries: at most one entry in 96 has a longer one.
+// most 32 entries: at most one entry in 96 of the sampled ones has a longer one
+// (none sampled: taken as short).
 inline bool win_short_rows(const Summary &S) { return 24 * S.w_wide <= S.w_entries; }
 
 // Window path for long rows (window.hip).  Planning: row records, the
