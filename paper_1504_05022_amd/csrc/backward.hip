@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void k_grad_b(const int64_t *tptr, const int32
 // lane, so the lanes stay full whatever the row lengths of B.
 //
 // What bounds it: latency and the B rows gathered past the L2 (one 128-byte
-// line or two per b_j* and array); the VALU is busy 57% of the time where B is
+// line or two per b_j* and array); the VALU is busy 58% of the time where B is
 // narrow.  One lane per entry of A, as before, left ragged rows waiting on their longest entry and
 // touched 64 lines per load: 2374 us where B is narrow (A 300000^2 with 6M
 // entries x B 300000x4096, 32 per row, binary32; now 1046), 1389 us where it
